@@ -19,18 +19,18 @@ namespace iodk {
 // Dynamics: eqs. cr3bp:x-z in the rotating barycentric frame.
 // ---------------------------------------------------------------------------
 
-// In-range forms of the device's correctly rounded FP64 sqrt and division.
-// They are the same instruction sequences the compiler emits for sqrt(x) and
-// a / b (hardware reciprocal-sqrt / reciprocal seed, one Goldschmidt step and
-// two Markstein corrections; two Newton steps and a corrected quotient)
-// without the operand rescaling and special-value fixups, which are
-// identities when x >= 2^-767 is finite and when b is normal, the quotient
-// is normal and exponent(a) - exponent(b) < 768.
-__device__ __forceinline__ double sqrt_inrange(double x)
+// In-range forms of the device's correctly rounded FP64 sqrt and reciprocal.
+// The square root is the instruction sequence the compiler emits for sqrt(x)
+// (hardware reciprocal-sqrt seed, one Goldschmidt step and two Markstein
+// corrections) without the operand rescaling and special-value fixups, which
+// are identities when x >= 2^-767 is finite. It also returns hh = 1/(2 sqrt x)
+// to about 2^-47 relative (the seed's error, at most 5.3e-8 over the device's
+// whole input range, enters as 1.5 times its square).
+__device__ __forceinline__ double sqrt_inrange(double x, double &hh)
 {
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y;
-    double hh = y * 0.5;
+    hh = y * 0.5;
     const double r = fma(-hh, g, 0.5);
     g = fma(g, r, g);
     hh = fma(hh, r, hh);
@@ -40,17 +40,51 @@ __device__ __forceinline__ double sqrt_inrange(double x)
     return fma(d, hh, g);
 }
 
-__device__ __forceinline__ double div_inrange(double a, double b)
+// 1 / D for D = (x1 sqrt(x1)) (x2 sqrt(x2)), correctly rounded, from the
+// halved inverse roots h1, h2 that the square roots leave behind: the seed
+// 64 (h1 h2)^3 is within 2^-44 of it, one Newton step brings that within an
+// ulp, and the last step then rounds correctly (Markstein's condition) unless
+// D's mantissa is all ones. That one shows in the last residual e = 1 - D r,
+// which is below 2^-53 for every other D and 2^-53 there (r = 2^k, whose
+// neighbour is the right answer and ties with it). It takes eight
+// instructions where the hardware reciprocal (four issue slots) and its two
+// Newton steps took ten slots.
+__device__ __forceinline__ double rcp_from_roots(double D, double h1, double h2, double &e)
 {
-    double r = __builtin_amdgcn_rcp(b);
-    double e = fma(-b, r, 1.0);
+    const double t = h1 * h2;
+    double r = (64.0 * t) * (t * t);
+    e = fma(-D, r, 1.0);
     r = fma(r, e, r);
-    e = fma(-b, r, 1.0);
-    r = fma(r, e, r);
-    const double q = a * r;
-    e = fma(-b, q, a);
-    return fma(e, r, q);
+    e = fma(-D, r, 1.0);
+    return fma(e, r, r);
 }
+
+// What certifies in-range results, from every D = D1 D2 and the residual e of
+// its reciprocal: D < 2^1000 and e < 2^-53, on the high words as integers
+// (which order as the values do where they matter: an infinite or NaN D is
+// above the range, and a NaN e, which is what a D too small for the
+// reciprocal or a zero D leaves, is above any residual). A NaN that came in
+// with the state may pass: the IEEE path returns NaN there as well. Two
+// three-way maxima per two values, 4 issue slots per RK4 step, where two
+// comparisons per value took 8. With the reciprocal above a step takes 262
+// slots instead of 274: an iteration of the single large swarm went from
+// 2.01 to 1.90 ms, and the uneven batch (two waves to a SIMD) gained 2%.
+struct Mark {
+    double D, e;
+};
+
+struct Cert {
+    int32_t D = -0x7fffffff - 1, e = -0x7fffffff - 1;
+    __device__ __forceinline__ void add(const Mark &a, const Mark &b)
+    {
+        D = max(max(__double2hiint(a.D), __double2hiint(b.D)), D);
+        e = max(max(__double2hiint(a.e), __double2hiint(b.e)), e);
+    }
+    __device__ __forceinline__ bool ok() const
+    {
+        return D < ((1023 + 1000) << 20) && e < ((1023 - 53) << 20);
+    }
+};
 
 // f(s) for s = (x, y, z, vx, vy, vz):
 //   ax =  2 vy + x - (1-mu)(x+mu)/r1^3 - mu (x-(1-mu))/r2^3
@@ -60,17 +94,17 @@ __device__ __forceinline__ double div_inrange(double a, double b)
 // R = 1/(D1 D2), c1 = (1-mu)(D2 R), c2 = mu (D1 R); sqrt and the reciprocal
 // correctly rounded.
 //
-// INRANGE = true uses the in-range sequences and returns whether the result
-// is certified equal to the IEEE one: 2^-760 <= D1 D2 <= 2^1000. The
-// reciprocal then has a normal operand, a normal result and an exponent gap
-// below 768. Both radicands are in range as well: r_j^2 < 2^-767 would need
-// the other primary's D above 2^390, but the primaries are one unit apart,
-// so r_j ~ 0 puts the other at r ~ 1; an infinite or NaN radicand makes
-// D1 D2 infinite or NaN. mu enters only through products, so every mu in
-// [0, 0.5] takes the in-range path. INRANGE = false is the IEEE path (always
-// certified).
+// INRANGE = true uses the in-range sequences; the result is certified equal
+// to the IEEE one if the returned mark passes Cert. A residual that is a
+// number says that the reciprocal's seed neither overflowed nor lost bits
+// below (D < 2^1000), so D >= 2^-1024 and x1 x2 = D^(2/3) >= 2^-683. Both
+// radicands are then in range as well: r_j^2 < 2^-767 would need the other
+// one above 2^84, but the primaries are one unit apart, so r_j ~ 0 puts the
+// other at r ~ 1; an infinite or NaN radicand makes D1 D2 infinite or NaN. mu
+// enters only through products, so every mu in [0, 0.5] takes the in-range
+// path. INRANGE = false is the IEEE path (always valid).
 template <bool INRANGE>
-__device__ __forceinline__ bool rhs(double mu, double mu1, const double s[6], double f[6])
+__device__ __forceinline__ Mark rhs(double mu, double mu1, const double s[6], double f[6])
 {
     const double x = s[0], y = s[1], z = s[2], vx = s[3], vy = s[4];
     const double d1 = x + mu;
@@ -78,10 +112,12 @@ __device__ __forceinline__ bool rhs(double mu, double mu1, const double s[6], do
     const double q = fma(z, z, y * y);
     const double r1s = fma(d1, d1, q);
     const double r2s = fma(d2, d2, q);
-    const double D1 = r1s * (INRANGE ? sqrt_inrange(r1s) : sqrt(r1s));
-    const double D2 = r2s * (INRANGE ? sqrt_inrange(r2s) : sqrt(r2s));
+    double h1 = 0.0, h2 = 0.0;
+    const double D1 = r1s * (INRANGE ? sqrt_inrange(r1s, h1) : sqrt(r1s));
+    const double D2 = r2s * (INRANGE ? sqrt_inrange(r2s, h2) : sqrt(r2s));
     const double D = D1 * D2;
-    const double R = INRANGE ? div_inrange(1.0, D) : 1.0 / D;
+    double e = 0.0;
+    const double R = INRANGE ? rcp_from_roots(D, h1, h2, e) : 1.0 / D;
     const double c1 = mu1 * (D2 * R);
     const double c2 = mu * (D1 * R);
     const double cs = c1 + c2;
@@ -91,40 +127,38 @@ __device__ __forceinline__ bool rhs(double mu, double mu1, const double s[6], do
     f[3] = fma(-c2, d2, fma(-c1, d1, fma(2.0, vy, x)));
     f[4] = fma(-cs, y, fma(-2.0, vx, y));
     f[5] = -(cs * z);
-    return !INRANGE || (D >= 0x1p-760 && D <= 0x1p1000);
+    return {D, e};
 }
 
 // Stage sum a = k1 + 2 k2 + 2 k3 + k4 of the classical RK4 step of size h
 // (h2 = h/2) from X, accumulated as the stages are produced, so only X, a,
-// the stage input and one derivative are live. Returns whether every stage
-// is certified.
+// the stage input and one derivative are live. cert takes in every stage.
 template <bool INRANGE>
-__device__ __forceinline__ bool rk4_sum(double mu, double mu1, double h, double h2,
-                                        const double X[6], double a[6])
+__device__ __forceinline__ void rk4_sum(double mu, double mu1, double h, double h2,
+                                        const double X[6], double a[6], Cert &cert)
 {
     double k[6], s[6];
-    bool ok = rhs<INRANGE>(mu, mu1, X, k);
+    Mark m = rhs<INRANGE>(mu, mu1, X, k);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = k[d];
         s[d] = fma(h2, k[d], X[d]);
     }
-    ok &= rhs<INRANGE>(mu, mu1, s, k);
+    cert.add(m, rhs<INRANGE>(mu, mu1, s, k));
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = fma(2.0, k[d], a[d]);
         s[d] = fma(h2, k[d], X[d]);
     }
-    ok &= rhs<INRANGE>(mu, mu1, s, k);
+    m = rhs<INRANGE>(mu, mu1, s, k);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = fma(2.0, k[d], a[d]);
         s[d] = fma(h, k[d], X[d]);
     }
-    ok &= rhs<INRANGE>(mu, mu1, s, k);
+    cert.add(m, rhs<INRANGE>(mu, mu1, s, k));
 #pragma unroll
     for (int d = 0; d < 6; ++d) a[d] = a[d] + k[d];
-    return ok;
 }
 
 // One RK4 step in place, X <- X + h6 a (h6 = h/6). The stage sum runs with
@@ -138,17 +172,24 @@ __device__ __forceinline__ void rk4(double mu, double mu1, bool fast, double h, 
 {
     double a[6];
     bool ok = false;
-    if (fast) ok = rk4_sum<true>(mu, mu1, h, h2, X, a);
-    if (!__all(ok)) rk4_sum<false>(mu, mu1, h, h2, X, a);
+    if (fast) {
+        Cert cert;
+        rk4_sum<true>(mu, mu1, h, h2, X, a, cert);
+        ok = cert.ok();
+    }
+    if (!__all(ok)) {
+        Cert ieee;
+        rk4_sum<false>(mu, mu1, h, h2, X, a, ieee);
+    }
 #pragma unroll
     for (int d = 0; d < 6; ++d) X[d] = fma(h6, a[d], X[d]);
 }
 
 // n steps of size h in place. The in-range sequences run all n steps with no
-// vote in between: each lane only accumulates whether every stage of every
-// step was certified, and the wave votes once at the end. If some lane was
-// not, the wave restores the state it started from and redoes the n steps on
-// the IEEE path. Either way the result is that of correctly rounded sqrt and
+// vote in between: each lane only accumulates the certificate of every stage
+// of every step, and the wave votes once at the end. If some lane was
+// not certified, the wave restores the state it started from and redoes the
+// n steps on the IEEE path. Either way the result is that of correctly rounded sqrt and
 // division, bit for bit, as with a vote per step; without a branch between
 // steps the scheduler can overlap one step's distance chains with the end
 // of the previous step. U steps per loop trip: a wave that has its SIMD to
@@ -161,21 +202,22 @@ __device__ __forceinline__ void rk4_steps(const KArgs &A, int32_t n, double X[6]
         double X0[6];
 #pragma unroll
         for (int d = 0; d < 6; ++d) X0[d] = X[d];
-        bool ok = true;
+        Cert cert;
 #pragma unroll U
         for (int32_t j = 0; j < n; ++j) {
             double a[6];
-            ok &= rk4_sum<true>(A.mu, A.mu1, A.h, A.h2, X, a);
+            rk4_sum<true>(A.mu, A.mu1, A.h, A.h2, X, a, cert);
 #pragma unroll
             for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
         }
-        if (__all(ok)) return;
+        if (__all(cert.ok())) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
     }
     for (int32_t j = 0; j < n; ++j) {
         double a[6];
-        rk4_sum<false>(A.mu, A.mu1, A.h, A.h2, X, a);
+        Cert ieee;
+        rk4_sum<false>(A.mu, A.mu1, A.h, A.h2, X, a, ieee);
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
     }

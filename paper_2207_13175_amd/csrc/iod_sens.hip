@@ -51,13 +51,13 @@ struct JacData {
 
 // f(s) exactly as the propagation's right-hand side computes it (rhs: one
 // reciprocal R = 1/(D1 D2), D_j = r_j^2 sqrt(r_j^2), correctly rounded sqrt
-// and reciprocal; INRANGE selects the in-range sequences and returns their
-// certificate), and the Jacobian data at s from the same intermediates:
+// and reciprocal; INRANGE selects the in-range sequences; returns the mark
+// for their certificate), and the Jacobian data at s from the same intermediates:
 // c1 = (1-mu) D2 R, c2 = mu D1 R, and, since D2 R = 1 / (r1^2 sqrt(r1^2)),
 // 1 / r1^2 = sqrt(r1^2) D2 R, so e1 = 3 c1 sqrt(r1^2) (D2 R) and likewise
 // e2, with no further square root or division.
 template <bool INRANGE>
-__device__ __forceinline__ bool rhs_jac(double mu, double mu1, const double s[6], double f[6],
+__device__ __forceinline__ Mark rhs_jac(double mu, double mu1, const double s[6], double f[6],
                                         JacData &J)
 {
     const double x = s[0], y = s[1], z = s[2], vx = s[3], vy = s[4];
@@ -66,12 +66,14 @@ __device__ __forceinline__ bool rhs_jac(double mu, double mu1, const double s[6]
     const double q = fma(z, z, y * y);
     const double r1s = fma(d1, d1, q);
     const double r2s = fma(d2, d2, q);
-    const double q1 = INRANGE ? sqrt_inrange(r1s) : sqrt(r1s);
-    const double q2 = INRANGE ? sqrt_inrange(r2s) : sqrt(r2s);
+    double h1 = 0.0, h2 = 0.0;
+    const double q1 = INRANGE ? sqrt_inrange(r1s, h1) : sqrt(r1s);
+    const double q2 = INRANGE ? sqrt_inrange(r2s, h2) : sqrt(r2s);
     const double D1 = r1s * q1;
     const double D2 = r2s * q2;
     const double D = D1 * D2;
-    const double R = INRANGE ? div_inrange(1.0, D) : 1.0 / D;
+    double e = 0.0;
+    const double R = INRANGE ? rcp_from_roots(D, h1, h2, e) : 1.0 / D;
     const double i1 = D2 * R, i2 = D1 * R;
     const double c1 = mu1 * i1;
     const double c2 = mu * i2;
@@ -89,7 +91,7 @@ __device__ __forceinline__ bool rhs_jac(double mu, double mu1, const double s[6]
     J.d2 = d2;
     J.y = y;
     J.z = z;
-    return !INRANGE || (D >= 0x1p-760 && D <= 0x1p1000);
+    return {D, e};
 }
 
 // G u for the symmetric gravity block.
@@ -134,34 +136,33 @@ __device__ __forceinline__ void atmul(const JacData &J, const double v[6], doubl
 // the stage inputs are those of the propagation bit for bit wherever the
 // result is certified.
 template <bool INRANGE>
-__device__ __forceinline__ bool stages_jac(double mu, double mu1, double h, double h2, double h6,
-                                           const double X[6], JacData J[4], double *Y)
+__device__ __forceinline__ void stages_jac(double mu, double mu1, double h, double h2, double h6,
+                                           const double X[6], JacData J[4], double *Y, Cert &cert)
 {
     double k[6], a[6], s[6];
-    bool ok = rhs_jac<INRANGE>(mu, mu1, X, k, J[0]);
+    Mark m = rhs_jac<INRANGE>(mu, mu1, X, k, J[0]);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = k[d];
         s[d] = fma(h2, k[d], X[d]);
     }
-    ok &= rhs_jac<INRANGE>(mu, mu1, s, k, J[1]);
+    cert.add(m, rhs_jac<INRANGE>(mu, mu1, s, k, J[1]));
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = fma(2.0, k[d], a[d]);
         s[d] = fma(h2, k[d], X[d]);
     }
-    ok &= rhs_jac<INRANGE>(mu, mu1, s, k, J[2]);
+    m = rhs_jac<INRANGE>(mu, mu1, s, k, J[2]);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = fma(2.0, k[d], a[d]);
         s[d] = fma(h, k[d], X[d]);
     }
-    ok &= rhs_jac<INRANGE>(mu, mu1, s, k, J[3]);
+    cert.add(m, rhs_jac<INRANGE>(mu, mu1, s, k, J[3]));
     if (Y) {
 #pragma unroll
         for (int d = 0; d < 6; ++d) Y[d] = fma(h6, a[d] + k[d], X[d]);
     }
-    return ok;
 }
 
 // The same with the in-range sequences where the whole wave is certified,
@@ -170,8 +171,15 @@ __device__ __forceinline__ void stages_jac(double mu, double mu1, bool fast, dou
                                            double h6, const double X[6], JacData J[4], double *Y)
 {
     bool ok = false;
-    if (fast) ok = stages_jac<true>(mu, mu1, h, h2, h6, X, J, Y);
-    if (!__all(ok)) stages_jac<false>(mu, mu1, h, h2, h6, X, J, Y);
+    if (fast) {
+        Cert cert;
+        stages_jac<true>(mu, mu1, h, h2, h6, X, J, Y, cert);
+        ok = cert.ok();
+    }
+    if (!__all(ok)) {
+        Cert ieee;
+        stages_jac<false>(mu, mu1, h, h2, h6, X, J, Y, ieee);
+    }
 }
 
 // Reverse (transposed tangent) of one RK4 step taken from X: lam <- (dX'/dX)^T lam.
@@ -358,7 +366,7 @@ __device__ __forceinline__ void grad_body(int64_t blk, const ProbDesc &d0, const
             double Z[6];
 #pragma unroll
             for (int d = 0; d < 6; ++d) Z[d] = Y[d];
-            ok = true;
+            Cert cert;
 #pragma unroll 2
             for (int32_t j = a; j < b; ++j) {
                 if (valid) {
@@ -367,11 +375,12 @@ __device__ __forceinline__ void grad_body(int64_t blk, const ProbDesc &d0, const
                 }
                 if (j + 1 < b) {
                     double q[6];
-                    ok &= rk4_sum<true>(A.mu, A.mu1, A.h, A.h2, Z, q);
+                    rk4_sum<true>(A.mu, A.mu1, A.h, A.h2, Z, q, cert);
 #pragma unroll
                     for (int d = 0; d < 6; ++d) Z[d] = fma(A.h6, q[d], Z[d]);
                 }
             }
+            ok = b - a < 2 || cert.ok();
         }
         if (!__all(ok)) {
             for (int32_t j = a; j < b; ++j) {
@@ -381,7 +390,8 @@ __device__ __forceinline__ void grad_body(int64_t blk, const ProbDesc &d0, const
                 }
                 if (j + 1 < b) {
                     double q[6];
-                    rk4_sum<false>(A.mu, A.mu1, A.h, A.h2, Y, q);
+                    Cert ieee;
+                    rk4_sum<false>(A.mu, A.mu1, A.h, A.h2, Y, q, ieee);
 #pragma unroll
                     for (int d = 0; d < 6; ++d) Y[d] = fma(A.h6, q[d], Y[d]);
                 }

@@ -1,0 +1,83 @@
+"""The in-range square root and reciprocal of the step loop against IEEE.
+
+The RK4 loop runs the square roots and the reciprocal without operand
+rescaling, and certifies each interval by the size of D = D1 D2 and by the
+last residual of its reciprocal. States therefore equal the oracle's bit for
+bit, also where the certificate fails: next to a primary and far out, where D
+leaves the range, and at a D whose mantissa is all ones, where the
+reciprocal's last step would round to the wrong neighbour."""
+from fractions import Fraction
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2207_13175_amd as iod
+
+pytestmark = pytest.mark.gpu
+
+
+def first_step(mu, xs):
+    """State after one step of 1e-3 TU from each of xs [n, 6], by the library."""
+    import torch
+    h = iod.iod_create(mu, [0.9, 0.1, 0, 0, 0.2, 0], [1e-3], np.zeros((1, 2)), 1e-5, h=1e-3)
+    ld = (len(xs) + 63) // 64 * 64
+    x = torch.zeros((6, ld), dtype=torch.float64, device="cuda")
+    x[:, :len(xs)] = torch.from_numpy(np.ascontiguousarray(xs.T)).cuda()
+    out = torch.zeros((1, 6, ld), dtype=torch.float64, device="cuda")
+    iod.iod_propagate(h, x, len(xs), out)
+    torch.cuda.synchronize()
+    return out[0, :, :len(xs)].cpu().numpy().T
+
+
+def reference(mu, xs):
+    return np.stack([oracle.propagate(mu, 1e-3, x, [1e-3])[0] for x in xs])
+
+
+def all_ones_state():
+    """A position whose D1 D2 is 2 - 2^-52, with mu = 0.5: pairs of radicands
+    near r2^2 = 1 whose product of r^2 fl(sqrt(r^2)) rounds there, then x and y
+    searched by single units so that both come out exactly."""
+    top = 2.0 - 2.0 ** -52
+    j = np.arange(-400, 401)
+    for r2 in 1.0 + np.arange(1, 400) * 2.0 ** -52:
+        D2 = r2 * np.sqrt(r2)
+        r1 = 2.0 ** (2 / 3) + j * 2.0 ** -52
+        for t1 in r1[(r1 * np.sqrt(r1)) * D2 == top]:
+            d1 = (t1 - r2 + 1.0) / 2
+            y0 = np.sqrt(t1 - d1 * d1)
+            for i in range(-12, 13):
+                x = d1 - 0.5 + i * 2.0 ** -54
+                a, b = Fraction(x + 0.5) ** 2, Fraction(x - 0.5) ** 2
+                for k in range(-12, 13):
+                    y = y0 + k * np.spacing(y0)
+                    q = Fraction(y * y)
+                    if float(a + q) == t1 and float(b + q) == r2:
+                        return np.array([x, y, 0.0]), t1, r2
+    raise AssertionError("no such state found")
+
+
+def test_states_at_the_edges_of_the_certificate():
+    rng = np.random.default_rng(5)
+    xs = []
+    for e in (-1, -60, -126, -127, -200, -253, -254, -300, -340, 30, 110, 166, 167, 168, 250, 300, 340):
+        # next to the second primary (1 - mu = 0.75 exactly) and far from both
+        s = rng.normal(0, 1, 6)
+        s[:3] *= 2.0 ** e
+        s[3:] *= 0.1
+        if e < 0:
+            s[0] += 0.75
+        xs.append(s)
+    xs = np.array(xs)
+    for x in xs:   # one at a time: each decides its own wave's path
+        a, b = first_step(0.25, x[None]), reference(0.25, x[None])
+        assert np.array_equal(a, b, equal_nan=True), (x, a, b)
+    a, b = first_step(0.25, xs), reference(0.25, xs)
+    assert np.array_equal(a, b, equal_nan=True)
+
+
+def test_mantissa_of_all_ones():
+    p, r1, r2 = all_ones_state()
+    assert (r1 * np.sqrt(r1)) * (r2 * np.sqrt(r2)) == 2.0 - 2.0 ** -52
+    xs = np.concatenate([p, [0.0, 0.1, 0.0]])[None]
+    assert np.array_equal(first_step(0.5, xs), reference(0.5, xs))
