@@ -10,9 +10,11 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <numeric>
+#include <utility>
 #include <vector>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -239,6 +241,7 @@ ProbDesc desc_of(const KArgs &A, const double chief[6], const iod_pso_params *p)
     D.k = A;
     std::memcpy(D.chief, chief, sizeof D.chief);
     D.kappa = 1.0;
+    D.lanes = 1;
     if (p) {
         D.omega = p->omega;
         D.eta1 = p->eta1;
@@ -277,6 +280,63 @@ int check_pso(const iod_pso_params *p)
     if (!std::isfinite(p->tol) || p->tol < 0.0) return fail(IOD_EINVAL, "tol must be finite and >= 0");
     if (p->tol > 0.0 && p->tol_lag < 1) return fail(IOD_EINVAL, "tol_lag must be >= 1");
     return IOD_OK;
+}
+
+// Lanes per particle of the FP64 propagations. A wave of one, two or four
+// lanes per particle holds 64, 32 or 16 of them, and its steps take about
+// SPLIT_COST times those of one lane per particle (measured on 500 steps to
+// 10 observations: 243, 184 and 165 us). So more lanes shorten a launch while
+// its waves have a SIMD each, and lengthen it once they share them: take the
+// number with the shortest estimate; several lanes must gain 5%. The estimate
+// is the largest of the longest wave, the SIMDs' mean load, and, since a wave
+// is not divided, n times the n-th wave that some SIMD must take: the
+// ((n - 1) simds + 1)-th longest (32,769 particles of one problem on 1,024
+// SIMDs: 316 us with two lanes each, 252 us with one).
+constexpr double SPLIT_COST[3] = {1.0, 0.76, 0.68};
+
+struct SplitLoad {
+    std::vector<std::pair<int64_t, int64_t>> work;   // (steps, particles) of each problem
+    void add(int64_t m, int64_t steps)
+    {
+        if (m > 0) work.emplace_back(std::max<int64_t>(steps, 1), m);
+    }
+    double estimate(int l, int simds) const
+    {
+        double total = 0.0, t = 0.0;
+        int64_t waves = 0;
+        for (const auto &w : work) {   // longest first
+            const int64_t n = ceil_div(w.second, 64 >> l);
+            // waves waves + 1 .. waves + n are of this length
+            t = std::max(t, (double)((waves + n - 1) / simds + 1) * (double)w.first);
+            waves += n;
+            total += (double)n * (double)w.first;
+        }
+        return SPLIT_COST[l] * std::max(t, total / simds);
+    }
+    // two: whether two lanes per particle are to be had
+    int lanes(int simds, bool two = true)
+    {
+        std::sort(work.begin(), work.end(), std::greater<std::pair<int64_t, int64_t>>());
+        int best = 1;
+        double t0 = 0.95 * estimate(0, simds);
+        for (int l = two ? 1 : 2; l < 3; ++l) {
+            const double t = estimate(l, simds);
+            if (t < t0) {
+                best = 1 << l;
+                t0 = t;
+            }
+        }
+        return best;
+    }
+};
+
+// SIMDs of the current device (four per compute unit).
+int device_simds(int device)
+{
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1)
+        return 1024;
+    return 4 * cus;
 }
 
 // RAII device buffers for the synchronous entry points.
@@ -463,6 +523,7 @@ int run_iterations(hipStream_t st, bool graph, int64_t n0, int64_t n_iter, F lau
 
 struct iod_handle {
     int device = 0;
+    int simds = 0;
     HostProblem P;
     double *d_tab = nullptr;   // [K][TAB_W]
     int32_t *d_ns = nullptr;   // [K]
@@ -488,6 +549,14 @@ struct iod_handle {
         }
         return kargs_of(P, d_tab, d_ns, T);
     }
+
+    // lanes per particle of a launch over m particles
+    int lanes(int64_t m) const
+    {
+        SplitLoad L;
+        L.add(m, P.steps);
+        return L.lanes(simds);
+    }
 };
 
 // Buffers of the batched refinement stage, kept across calls.
@@ -498,6 +567,7 @@ struct PolishBuffers {
 
 struct iod_batch {
     int device = 0;
+    int simds = 0;
     int32_t P = 0;
     std::vector<HostProblem> probs;
     std::vector<int64_t> tab_off;  // per problem, rows
@@ -635,7 +705,11 @@ int check_swarm(const iod_swarm *s, bool need_init)
 void single_view(const iod_handle *h, const iod_swarm *s, const iod_pso_params *p, ProbDesc &D,
                  SwarmArrays &B)
 {
-    const int64_t nslots = ceil_div(s->m, s->block);
+    // the lanes per particle follow from the problem, m and the device alone,
+    // so that every call on the swarm finds the slots of the one before
+    const int lanes = h->lanes(s->m);
+    const int32_t block = lanes > 1 ? SPLIT_BS / lanes : s->block;
+    const int64_t nslots = ceil_div(s->m, block);
     D = desc_of(h->kargs(), h->P.chief, p);
     D.hist = s->hist_len > 0 ? s->hist : nullptr;
     D.hist_len = s->hist_len;
@@ -643,7 +717,8 @@ void single_view(const iod_handle *h, const iod_swarm *s, const iod_pso_params *
     D.off = 0;
     D.slot_off = 0;
     D.nslots = nslots;
-    D.block = s->block;
+    D.block = block;
+    D.lanes = lanes;
     B.desc = nullptr;
     B.work = nullptr;
     B.x = s->x;
@@ -724,6 +799,7 @@ int iod_create_ranged(double mu, const double chief_state[6], const double *obs_
     };
     hipError_t e = hipGetDevice(&h->device);
     if (e != hipSuccess) return bail(hip_fail(e, "hipGetDevice"));
+    h->simds = device_simds(h->device);
     const size_t K = (size_t)h->P.K;
     if ((e = hipMalloc(&h->d_tab, K * TAB_W * sizeof(double))) != hipSuccess)
         return bail(hip_fail(e, "hipMalloc table"));
@@ -807,7 +883,7 @@ int iod_propagate(iod_handle *h, const double *x, int64_t ld, int64_t m, double 
     int rc = check_handle(h);
     if (rc == IOD_OK) rc = check_swarm_view(x, ld, m, states);
     if (rc != IOD_OK || m == 0) return rc;
-    HIP_TRY(launch_propagate(h->kargs(), x, ld, m, states, (hipStream_t)stream));
+    HIP_TRY(launch_propagate(h->kargs(), x, ld, m, states, h->lanes(m), (hipStream_t)stream));
     return IOD_OK;
 }
 
@@ -817,7 +893,7 @@ int iod_predict(iod_handle *h, const double *x, int64_t ld, int64_t m, double *a
     int rc = check_handle(h);
     if (rc == IOD_OK) rc = check_swarm_view(x, ld, m, angles);
     if (rc != IOD_OK || m == 0) return rc;
-    HIP_TRY(launch_predict(h->kargs(), x, ld, m, angles, (hipStream_t)stream));
+    HIP_TRY(launch_predict(h->kargs(), x, ld, m, angles, h->lanes(m), (hipStream_t)stream));
     return IOD_OK;
 }
 
@@ -827,7 +903,7 @@ int iod_predict_ranges(iod_handle *h, const double *x, int64_t ld, int64_t m, do
     int rc = check_handle(h);
     if (rc == IOD_OK) rc = check_swarm_view(x, ld, m, ranges);
     if (rc != IOD_OK || m == 0) return rc;
-    HIP_TRY(launch_predict_ranges(h->kargs(), x, ld, m, ranges, (hipStream_t)stream));
+    HIP_TRY(launch_predict_ranges(h->kargs(), x, ld, m, ranges, h->lanes(m), (hipStream_t)stream));
     return IOD_OK;
 }
 
@@ -840,8 +916,9 @@ int iod_eval_swarm(iod_handle *h, const double *x, int64_t ld, int64_t m, double
     const int bs = block_of(h->cfg);
     ProbDesc D = desc_of(h->kargs(), h->P.chief, nullptr);
     D.m = m;
-    D.nslots = ceil_div(m, bs);
-    D.block = bs;
+    D.lanes = h->lanes(m);
+    D.block = D.lanes > 1 ? SPLIT_BS / D.lanes : bs;
+    D.nslots = ceil_div(m, D.block);
     SwarmArrays B;
     std::memset(&B, 0, sizeof B);
     B.x = const_cast<double *>(x);
@@ -1024,6 +1101,7 @@ int iod_create_batch_ranged(int32_t n_problems, const double *mu, const double *
     }
     hipError_t e = hipGetDevice(&b->device);
     if (e != hipSuccess) return bail(hip_fail(e, "hipGetDevice"));
+    b->simds = device_simds(b->device);
     std::vector<double> tab((size_t)rows * TAB_W);
     std::vector<int32_t> ns((size_t)rows);
     for (int32_t p = 0; p < n_problems; ++p) {
@@ -1135,14 +1213,23 @@ struct BatchLayout {
     int64_t ld = 0, total_slots = 0, grid = 0;
 };
 
+// split: the launches are FP64 evaluations or swarms, which may give each
+// particle several lanes (the same number for all problems).
 int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t *m, int bs,
-                 int order, BatchLayout &L)
+                 int order, BatchLayout &L, bool split = false)
 {
     std::vector<int64_t> off(b->P + 1);
     int64_t ld = iod_batch_offsets(b, m, off.data());
     if (ld < 0) return (int)ld;
     L.ld = ld;
     L.descs.resize(b->P);
+    int lanes = 1;
+    if (split) {
+        SplitLoad S;
+        for (int32_t p = 0; p < b->P; ++p) S.add(m[p], b->probs[p].steps);
+        lanes = S.lanes(b->simds);
+        if (lanes > 1) bs = SPLIT_BS / lanes;
+    }
     int64_t slots = 0;
     for (int32_t p = 0; p < b->P; ++p) {
         ProbDesc &D = L.descs[p];
@@ -1153,6 +1240,7 @@ int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t
         D.slot_off = slots;
         D.nslots = ceil_div(m[p], bs);
         D.block = bs;
+        D.lanes = lanes;
         slots += D.nslots;
     }
     L.total_slots = slots;
@@ -1196,7 +1284,7 @@ int batch_run(iod_batch *b, const iod_pso_params *params, const int64_t *m, int6
     int rc = rel ? ensure_chief_tables(b) : IOD_OK;
     if (rc != IOD_OK) return rc;
     BatchLayout L;
-    rc = batch_layout(b, params, m, bs, cfg.order, L);
+    rc = batch_layout(b, params, m, bs, cfg.order, L, top_k == 0);
     if (rc != IOD_OK) return rc;
     Phase swarm_phase(top_k ? "iod_batch: mixed-precision swarm" : "iod_batch: FP64 swarm");
     const int64_t P = b->P, ld = L.ld;
@@ -1233,12 +1321,16 @@ int batch_run(iod_batch *b, const iod_pso_params *params, const int64_t *m, int6
     B.total_slots = L.total_slots;
     B.nprob = P;
     const ProbDesc &d0 = L.descs[0];
+    // the re-evaluation of up to top_k candidates per problem
+    SplitLoad re;
+    for (int32_t p = 0; p < b->P; ++p) re.add(std::min<int64_t>(top_k, 64), b->probs[p].steps);
+    const int re_lanes = re.lanes(b->simds, false);
     // one iteration: FP64 fused launch, or FP32 launch + top-k + FP64 re-evaluation
     auto iterate = [&](int64_t n) -> hipError_t {
         if (top_k == 0) return launch_swarm_iter(d0, B, bs, L.grid, n, st, cfg.waves);
         hipError_t e = launch_mixed_iter(d0, B, bs, L.grid, n, rel, st);
         if (e == hipSuccess) e = launch_topk(B, B.jp, top_k, cand, st);
-        if (e == hipSuccess) e = launch_reeval64(B, cand, top_k, n, st);
+        if (e == hipSuccess) e = launch_reeval64(B, cand, top_k, n, re_lanes, st);
         return e;
     };
     if (top_k == 0) {
@@ -1246,7 +1338,7 @@ int batch_run(iod_batch *b, const iod_pso_params *params, const int64_t *m, int6
     } else {
         HIP_TRY(launch_mixed_init(d0, B, bs, L.grid, rel, st));
         HIP_TRY(launch_topk(B, B.jp, top_k, cand, st));
-        HIP_TRY(launch_reeval64(B, cand, top_k, 0, st));
+        HIP_TRY(launch_reeval64(B, cand, top_k, 0, re_lanes, st));
     }
     if (iter_ms) {
         if (!b->ev0) HIP_TRY(hipEventCreate(&b->ev0));
@@ -1260,7 +1352,7 @@ int batch_run(iod_batch *b, const iod_pso_params *params, const int64_t *m, int6
     // from device tables (refreshed above when they change); the key holds
     // every launch argument
     Key key;
-    key.add(d0).add(B).add(bs).add(L.grid).add(cfg.waves).add(top_k).add(cand).add(rel);
+    key.add(d0).add(B).add(bs).add(L.grid).add(cfg.waves).add(top_k).add(cand).add(rel).add(re_lanes);
     rc = run_iterations(st, cfg.graph != 0, n0, n_iter - n0, iterate, &b->graphs, key);
     if (rc == IOD_OK && iter_ms) {
         hipError_t e = hipEventRecord(b->ev1, st);
@@ -1398,7 +1490,7 @@ int batch_eval_impl(iod_batch *b, const double *x, int64_t ld, const int64_t *m,
     if (!m) return fail(IOD_EINVAL, "null m");
     const int bs = block_of(b->cfg);
     BatchLayout L;
-    rc = batch_layout(b, nullptr, m, bs, b->cfg.order, L);
+    rc = batch_layout(b, nullptr, m, bs, b->cfg.order, L, !f32);
     if (rc != IOD_OK) return rc;
     if (ld < L.ld) return fail(IOD_EINVAL, "ld = %lld < %lld", (long long)ld, (long long)L.ld);
     if (L.grid == 0) return IOD_OK;
@@ -1407,7 +1499,7 @@ int batch_eval_impl(iod_batch *b, const double *x, int64_t ld, const int64_t *m,
     if (f32 && rel && !b->chief_built) {
         rc = ensure_chief_tables(b);
         if (rc != IOD_OK) return rc;
-        rc = batch_layout(b, nullptr, m, bs, b->cfg.order, L);
+        rc = batch_layout(b, nullptr, m, bs, b->cfg.order, L, !f32);
         if (rc != IOD_OK) return rc;
     }
     hipStream_t st = (hipStream_t)stream;

@@ -223,6 +223,187 @@ __device__ __forceinline__ void rk4_steps(const KArgs &A, int32_t n, double X[6]
     }
 }
 
+// ---------------------------------------------------------------------------
+// Several lanes to a particle. A launch that leaves SIMDs idle is bound by one
+// wave's instruction count (dependent FP64 instructions issue back to back,
+// so there is no latency to hide), and more lanes per particle shorten it:
+// the distance chains of stages 1 and 2 of an RK4 step do not depend on each
+// other (stage 2's position is X + h/2 V), nor do those of stages 3 and 4
+// once stage 2's acceleration is known. So the lanes of a particle take
+// stage 1 or 2 (then 3 or 4), and with four lanes also one primary each.
+// Every lane holds the whole state; values cross between adjacent lanes with
+// quad permutations. Each operation is the one-lane form's, on the same
+// operands, so the bits are the same. Per step 262 issue slots become 188
+// with two lanes and 172 with four: 256 particles over 500 steps went from 243
+// to 157 us, 5,001 over 2,257 from 1,098 to 727 us (four lanes), 32,768 over
+// 500 from 243 to 184 us (two). A wave then holds 32 or 16 particles, so this
+// pays only while the waves still have a SIMD each.
+// ---------------------------------------------------------------------------
+
+// x of another lane of the quad, two 32-bit moves (S0..S3: the source lane of
+// lanes 0..3).
+template <int S0, int S1, int S2, int S3>
+__device__ __forceinline__ double quad_perm(double x)
+{
+    constexpr int CTRL = S0 | S1 << 2 | S2 << 4 | S3 << 6;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// LPP lanes per particle, 2 or 4: lane = LPP/2 * stage + primary. early / late:
+// the value of the lane that holds stage 1 or 3 / stage 2 or 4 (with four
+// lanes, of the own primary's); first / second: the value of the own stage's
+// lane for primary 1 / 2 (four lanes only); other: of its other primary's.
+template <int LPP>
+struct Quad {
+    static __device__ __forceinline__ bool is_late() { return threadIdx.x & (LPP / 2); }
+    static __device__ __forceinline__ double early(double x)
+    {
+        return LPP == 2 ? quad_perm<0, 0, 2, 2>(x) : quad_perm<0, 1, 0, 1>(x);
+    }
+    static __device__ __forceinline__ double late(double x)
+    {
+        return LPP == 2 ? quad_perm<1, 1, 3, 3>(x) : quad_perm<2, 3, 2, 3>(x);
+    }
+    static __device__ __forceinline__ double first(double x) { return quad_perm<0, 0, 2, 2>(x); }
+    static __device__ __forceinline__ double second(double x) { return quad_perm<1, 1, 3, 3>(x); }
+    static __device__ __forceinline__ double other(double x) { return quad_perm<1, 0, 3, 2>(x); }
+};
+
+// The position-dependent part of rhs<true> at p, shared by a particle's
+// lanes: c1, c2, their sum and the offsets; returns the mark. xj, muj: with four
+// lanes, mu or -mu1 and mu1 or mu by the lane's primary.
+struct Attraction {
+    double d1, d2, c1, c2, cs;
+};
+
+template <int LPP>
+__device__ __forceinline__ Mark attraction(double mu, double mu1, double xj, double muj,
+                                         const double p[3], Attraction &o)
+{
+    o.d1 = p[0] + mu;
+    o.d2 = p[0] - mu1;
+    const double q = fma(p[2], p[2], p[1] * p[1]);
+    double D, e;
+    if (LPP == 4) {
+        const double dj = p[0] + xj;
+        const double rs = fma(dj, dj, q);
+        double hj;
+        const double Dj = rs * sqrt_inrange(rs, hj);
+        const double Do = Quad<4>::other(Dj);
+        const double ho = Quad<4>::other(hj);
+        D = Dj * Do;
+        const double cj = muj * (Do * rcp_from_roots(D, hj, ho, e));
+        o.c1 = Quad<4>::first(cj);
+        o.c2 = Quad<4>::second(cj);
+    } else {
+        const double r1s = fma(o.d1, o.d1, q);
+        const double r2s = fma(o.d2, o.d2, q);
+        double h1, h2;
+        const double D1 = r1s * sqrt_inrange(r1s, h1);
+        const double D2 = r2s * sqrt_inrange(r2s, h2);
+        D = D1 * D2;
+        const double R = rcp_from_roots(D, h1, h2, e);
+        o.c1 = mu1 * (D2 * R);
+        o.c2 = mu * (D1 * R);
+    }
+    o.cs = o.c1 + o.c2;
+    return {D, e};
+}
+
+// x and y of rhs's acceleration at p moving with (vx, vy).
+__device__ __forceinline__ void accel_xy(const Attraction &o, const double p[3], double vx,
+                                         double vy, double &ax, double &ay)
+{
+    ax = fma(-o.c2, o.d2, fma(-o.c1, o.d1, fma(2.0, vy, p[0])));
+    ay = fma(-o.cs, p[1], fma(-2.0, vx, p[1]));
+}
+
+// n steps as rk4_steps, by the LPP lanes of each particle. In each half of a
+// step the lanes evaluate their own stage's attraction, then the earlier
+// stage's acceleration (with the velocity all lanes know) passes to the later
+// stage's lanes, whose velocity and acceleration it completes.
+template <int LPP>
+__device__ __forceinline__ void rk4_steps_split(const KArgs &A, int32_t n, double X[6])
+{
+    using Q = Quad<LPP>;
+    const double mu = A.mu, mu1 = A.mu1, h = A.h, h2 = A.h2, h6 = A.h6;
+    if (A.fast) {
+        const bool late = Q::is_late(), second = LPP == 4 && (threadIdx.x & 1);
+        const double ha = late ? h2 : 0.0, hb = late ? h : h2;
+        const double xj = second ? -mu1 : mu, muj = second ? mu : mu1;
+        double X0[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X0[d] = X[d];
+        Cert cert;
+        auto step = [&]() __attribute__((always_inline)) {
+            const double *V = X + 3;
+            double p[3], a[3], w[3], k1[3], k2[3], k3[3], v2[3], v3[3], v4[3];
+            Attraction o;
+            // stages 1 and 2
+#pragma unroll
+            for (int d = 0; d < 3; ++d) p[d] = fma(ha, V[d], X[d]);
+            const Mark ma = attraction<LPP>(mu, mu1, xj, muj, p, o);
+            double ax, ay;
+            accel_xy(o, p, V[0], V[1], ax, ay);
+            k1[0] = Q::early(ax);
+            k1[1] = Q::early(ay);
+            // the own stage's velocity: V, or stage 2's V + h/2 k1
+            accel_xy(o, p, fma(ha, k1[0], V[0]), fma(ha, k1[1], V[1]), a[0], a[1]);
+            a[2] = -(o.cs * p[2]);
+            k1[2] = Q::early(a[2]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                // the next stage's velocity: stage 2's (early) or stage 3's (late)
+                w[d] = fma(h2, a[d], V[d]);
+                k2[d] = Q::late(a[d]);
+                v2[d] = fma(h2, k1[d], V[d]);
+                v3[d] = fma(h2, k2[d], V[d]);
+            }
+            // stages 3 and 4
+#pragma unroll
+            for (int d = 0; d < 3; ++d) p[d] = fma(hb, w[d], X[d]);
+            cert.add(ma, attraction<LPP>(mu, mu1, xj, muj, p, o));
+            accel_xy(o, p, v3[0], v3[1], ax, ay);
+            k3[0] = Q::early(ax);
+            k3[1] = Q::early(ay);
+            a[2] = -(o.cs * p[2]);
+            k3[2] = Q::early(a[2]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) v4[d] = fma(h, k3[d], V[d]);
+            accel_xy(o, p, v4[0], v4[1], a[0], a[1]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const double sx = fma(2.0, v3[d], fma(2.0, v2[d], V[d])) + v4[d];
+                const double sv = fma(2.0, k3[d], fma(2.0, k2[d], k1[d])) + Q::late(a[d]);
+                X[d] = fma(h6, sx, X[d]);
+                X[3 + d] = fma(h6, sv, X[3 + d]);
+            }
+        };
+        // (written out: the compiler does not unroll a loop of lane exchanges
+        // whose trip count it does not know)
+        int32_t j = 0;
+        for (; j + 4 <= n; j += 4) {
+            step();
+            step();
+            step();
+            step();
+        }
+        for (; j < n; ++j) step();
+        if (__all(cert.ok())) return;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = X0[d];
+    }
+    for (int32_t j = 0; j < n; ++j) {
+        double a[6];
+        Cert ieee;
+        rk4_sum<false>(mu, mu1, h, h2, X, a, ieee);
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = fma(h6, a[d], X[d]);
+    }
+}
+
 // Who stages the observation table into LDS together: the whole workgroup
 // (with barriers), or one wave on its own. A wave's lanes run in lockstep and
 // its LDS accesses complete in issue order, so a wave needs only a fence
@@ -246,8 +427,8 @@ struct WaveScope {
 // observation hand the state there (a side copy advanced by the partial step
 // when the time is off the grid) to `obs(row, S)`. Every thread of the scope
 // (the workgroup, or the wave) must call this: it stages the table through
-// LDS in chunks.
-template <class Scope = BlockScope, int U = 2, class Obs>
+// LDS in chunks. LPP adjacent lanes hold the same particle (1, 2 or 4).
+template <class Scope = BlockScope, int U = 2, int LPP = 1, class Obs>
 __device__ __forceinline__ void walk(const KArgs &A, double X[6], double *lds, int32_t *lds_ns,
                                      Obs &obs)
 {
@@ -263,7 +444,10 @@ __device__ __forceinline__ void walk(const KArgs &A, double X[6], double *lds, i
             const double *row = lds + kk * TAB_W;
             const int32_t target = __builtin_amdgcn_readfirstlane(lds_ns[kk]);
             if (target > step) {
-                rk4_steps<U>(A, target - step, X);
+                if constexpr (LPP == 1)
+                    rk4_steps<U>(A, target - step, X);
+                else
+                    rk4_steps_split<LPP>(A, target - step, X);
                 step = target;
             }
             const double tau = row[TAB_TAU];
@@ -325,7 +509,7 @@ struct CostAcc {
     }
 };
 
-template <class Scope = BlockScope, int U = 2>
+template <class Scope = BlockScope, int U = 2, int LPP = 1>
 __device__ __forceinline__ double eval_cost(const KArgs &A, const double x0[6], double *lds,
                                             int32_t *lds_ns)
 {
@@ -333,7 +517,7 @@ __device__ __forceinline__ double eval_cost(const KArgs &A, const double x0[6], 
 #pragma unroll
     for (int d = 0; d < 6; ++d) X[d] = x0[d];
     CostAcc acc{0.0, A.w, A.mode, A.wr};
-    walk<Scope, U>(A, X, lds, lds_ns, acc);
+    walk<Scope, U, LPP>(A, X, lds, lds_ns, acc);
     return acc.J;
 }
 
@@ -513,10 +697,10 @@ __device__ __forceinline__ void write_slot(double jp, int64_t i, bool valid, con
 // Global best of one problem: merge(record, the problem's slots). The slot
 // minimum replaces the record if the record is empty (index < 0) or the slot
 // cost is strictly lower. Slot s holds the minimum of particles
-// [s * blockDim, (s + 1) * blockDim). Every workgroup of the problem computes
+// [s * per_slot, (s + 1) * per_slot). Every workgroup of the problem computes
 // the same result.
 __device__ __forceinline__ void reduce_global(const double *slots, int64_t nslots,
-                                              const double *prev, double g[6], double &gkey,
+                                              int32_t per_slot, const double *prev, double g[6], double &gkey,
                                               double &gidx, double *red)
 {
     double key = INFINITY, idx = INFINITY;
@@ -530,7 +714,7 @@ __device__ __forceinline__ void reduce_global(const double *slots, int64_t nslot
     block_argmin(key, idx, red);
     const double pk = prev[0], pi = prev[1];
     if (pi < 0.0 || key < pk) {
-        const int64_t s = (int64_t)idx / blockDim.x;
+        const int64_t s = (int64_t)idx / per_slot;
         gkey = key;
         gidx = idx;
 #pragma unroll
@@ -643,6 +827,21 @@ static inline unsigned grid_for(int64_t m, int bs) { return (unsigned)((m + bs -
     case 64: { constexpr int BS_ = 64; __VA_ARGS__; break; }       \
     case 128: { constexpr int BS_ = 128; __VA_ARGS__; break; }     \
     case 256: { constexpr int BS_ = 256; __VA_ARGS__; break; }     \
+    default: return hipErrorInvalidValue;                          \
+    }
+
+#define IOD_DISPATCH_SPLIT(LPPV, ...)                              \
+    switch (LPPV) {                                                \
+    case 2: { constexpr int LPP_ = 2; __VA_ARGS__; break; }        \
+    case 4: { constexpr int LPP_ = 4; __VA_ARGS__; break; }        \
+    default: return hipErrorInvalidValue;                          \
+    }
+
+#define IOD_DISPATCH_LPP(LPPV, ...)                                \
+    switch (LPPV) {                                                \
+    case 1: { constexpr int LPP_ = 1; __VA_ARGS__; break; }        \
+    case 2: { constexpr int LPP_ = 2; __VA_ARGS__; break; }        \
+    case 4: { constexpr int LPP_ = 4; __VA_ARGS__; break; }        \
     default: return hipErrorInvalidValue;                          \
     }
 

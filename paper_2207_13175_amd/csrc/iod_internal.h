@@ -20,6 +20,12 @@ constexpr int TAB_RANGE = 9;
 // Rows staged in LDS at a time by every workgroup.
 constexpr int OBS_CHUNK = 64;
 
+// Threads per workgroup of the FP64 kernels that give a particle several
+// lanes: four waves, one for each SIMD of a compute unit (workgroups of two
+// waves were placed two to a unit on the same pair of SIMDs, and took 1.3
+// times as long as one lane per particle).
+constexpr int SPLIT_BS = 256;
+
 // Global-best record and argmin slot: [key, index, state[6]].
 constexpr int REC = 8;
 
@@ -74,8 +80,8 @@ struct ProbDesc {
     int64_t off;                // first particle in the swarm arrays
     int64_t slot_off;           // first argmin slot
     int64_t nslots;             // ceil(m / block)
-    int32_t block;              // threads per workgroup of the swarm kernels
-    int32_t pad;
+    int32_t block;              // particles per workgroup of the swarm kernels (and per argmin slot)
+    int32_t lanes;              // adjacent lanes per particle of the FP64 propagations: 1, 2 or 4
 };
 
 // Swarm storage of one launch. desc/work are null for a single problem.

@@ -4,7 +4,8 @@
 // rel:pos, meas:function, b:total, total:cost; Algorithm 1).
 //
 // Design (CDNA4, wave64):
-//   - One particle per lane. Its state, the RK4 stage input, the running
+//   - One particle per lane, or two or four lanes per particle in launches
+//     that would otherwise leave SIMDs idle (rk4_steps_split). Its state, the RK4 stage input, the running
 //     stage sum and the current derivative live in VGPRs for the whole
 //     propagation; nothing touches memory inside the step loop.
 //   - The observation table (step counts, chief positions, sin/cos of the
@@ -38,32 +39,34 @@
 
 namespace iodk {
 
+template <int LPP>
 __global__ __launch_bounds__(256) void k_propagate(KArgs A, const double *__restrict__ x,
                                                    int64_t ld, int64_t m,
                                                    double *__restrict__ states)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
     __shared__ int32_t lds_ns[OBS_CHUNK];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPP;
     const bool valid = i < m;
     double X[6];
     load_state(x, ld, valid ? i : m - 1, X);
-    StoreStates obs{states, ld, i, 0, valid};
-    walk(A, X, lds, lds_ns, obs);
+    StoreStates obs{states, ld, i, 0, valid && threadIdx.x % LPP == 0};
+    walk<BlockScope, 2, LPP>(A, X, lds, lds_ns, obs);
 }
 
+template <int LPP>
 __global__ __launch_bounds__(256) void k_predict(KArgs A, const double *__restrict__ x,
                                                  int64_t ld, int64_t m,
                                                  double *__restrict__ angles)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
     __shared__ int32_t lds_ns[OBS_CHUNK];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPP;
     const bool valid = i < m;
     double X[6];
     load_state(x, ld, valid ? i : m - 1, X);
-    StoreAngles obs{angles, ld, i, 0, valid};
-    walk(A, X, lds, lds_ns, obs);
+    StoreAngles obs{angles, ld, i, 0, valid && threadIdx.x % LPP == 0};
+    walk<BlockScope, 2, LPP>(A, X, lds, lds_ns, obs);
 }
 
 // Predicted angles of one state per problem (one workgroup per problem),
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(64) void k_predict_batch(const ProbDesc *__restrict
 #pragma unroll
     for (int d = 0; d < 6; ++d) X[d] = xs[6 * p + d];
     StoreAnglesRow obs{out + 2 * row_off[p], 0};
-    walk(D.k, X, lds, lds_ns, obs);
+    walk<BlockScope, 2, 4>(D.k, X, lds, lds_ns, obs);
 }
 
 hipError_t launch_predict_batch(const ProbDesc *descs, int64_t nprob, const double *xs,
@@ -147,18 +150,19 @@ struct StoreRangesRow {
     }
 };
 
+template <int LPP>
 __global__ __launch_bounds__(256) void k_predict_ranges(KArgs A, const double *__restrict__ x,
                                                         int64_t ld, int64_t m,
                                                         double *__restrict__ out)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
     __shared__ int32_t lds_ns[OBS_CHUNK];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LPP;
     const bool valid = i < m;
     double X[6];
     load_state(x, ld, valid ? i : m - 1, X);
-    StoreRanges obs{out, ld, i, 0, valid};
-    walk(A, X, lds, lds_ns, obs);
+    StoreRanges obs{out, ld, i, 0, valid && threadIdx.x % LPP == 0};
+    walk<BlockScope, 2, LPP>(A, X, lds, lds_ns, obs);
 }
 
 __global__ __launch_bounds__(64) void k_predict_ranges_batch(const ProbDesc *__restrict__ descs,
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(64) void k_predict_ranges_batch(const ProbDesc *__r
 #pragma unroll
     for (int d = 0; d < 6; ++d) X[d] = xs[6 * p + d];
     StoreRangesRow obs{out + row_off[p], 0};
-    walk(descs[p].k, X, lds, lds_ns, obs);
+    walk<BlockScope, 2, 4>(descs[p].k, X, lds, lds_ns, obs);
 }
 
 hipError_t launch_predict_ranges_batch(const ProbDesc *descs, int64_t nprob, const double *xs,
@@ -196,10 +200,11 @@ __global__ __launch_bounds__(64) void k_chief(ProbDesc d0, const ProbDesc *__res
 #pragma unroll
     for (int d = 0; d < 6; ++d) X[d] = D.chief[d];
     StoreChief obs{const_cast<double *>(D.k.tab), 0};
-    walk(D.k, X, lds, lds_ns, obs);
+    walk<BlockScope, 2, 4>(D.k, X, lds, lds_ns, obs);
 }
 
-template <int BS, bool SINGLE>
+// LPP lanes per particle: workgroups of BS threads hold BS / LPP particles.
+template <int BS, bool SINGLE, int LPP = 1>
 __global__ __launch_bounds__(BS) void k_eval(ProbDesc d0, SwarmArrays B)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
@@ -207,12 +212,12 @@ __global__ __launch_bounds__(BS) void k_eval(ProbDesc d0, SwarmArrays B)
     int64_t p, tile;
     const ProbDesc &D = locate<SINGLE>(d0, B, p, tile);
     if (B.active && !B.active[p]) return;   // whole workgroup
-    const int64_t i = tile * BS + threadIdx.x;
+    const int64_t i = tile * (BS / LPP) + threadIdx.x / LPP;
     const bool valid = i < D.m;
     double X[6];
     load_state(B.x, B.ld, D.off + (valid ? i : D.m - 1), X);
-    const double J = eval_cost(D.k, X, lds, lds_ns);
-    if (valid) B.cost[D.off + i] = J;
+    const double J = eval_cost<BlockScope, 2, LPP>(D.k, X, lds, lds_ns);
+    if (valid && threadIdx.x % LPP == 0) B.cost[D.off + i] = J;
 }
 
 // RK4 steps per loop trip of the swarm kernels (rk4_steps): a single
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(BS) void k_eval(ProbDesc d0, SwarmArrays B)
 constexpr int steps_per_trip(bool single) { return single ? 8 : 2; }
 
 // Algorithm 1 initialisation.
-template <int BS, bool SINGLE>
+template <int BS, bool SINGLE, int LPP = 1>
 __global__ __launch_bounds__(BS) void k_swarm_init(ProbDesc d0, SwarmArrays B)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
@@ -231,14 +236,14 @@ __global__ __launch_bounds__(BS) void k_swarm_init(ProbDesc d0, SwarmArrays B)
     __shared__ double wst[6];
     int64_t p, tile;
     const ProbDesc &D = locate<SINGLE>(d0, B, p, tile);
-    const int64_t i = tile * BS + threadIdx.x;
+    const int64_t i = tile * (BS / LPP) + threadIdx.x / LPP;
     const bool valid = i < D.m;
     const int64_t j = valid ? i : D.m - 1;
     double X[6];
     init_state(D, j, X);
-    const double J = eval_cost<BlockScope, steps_per_trip(SINGLE)>(D.k, X, lds, lds_ns);
+    const double J = eval_cost<BlockScope, steps_per_trip(SINGLE), LPP>(D.k, X, lds, lds_ns);
     const int64_t ld = B.ld, g = D.off + i;
-    if (valid) {
+    if (valid && threadIdx.x % LPP == 0) {
 #pragma unroll
         for (int d = 0; d < 6; ++d) {
             B.x[d * ld + g] = X[d];
@@ -256,7 +261,7 @@ __global__ __launch_bounds__(BS) void k_swarm_init(ProbDesc d0, SwarmArrays B)
 }
 
 // Algorithm 1, iteration n >= 1 (the body of the iteration kernels below).
-template <int BS, bool SINGLE>
+template <int BS, bool SINGLE, int LPP = 1>
 __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays &B, int64_t n)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
@@ -282,7 +287,7 @@ __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays
 
     // (a) global best of the previous iteration
     double g[6], gkey, gidx;
-    reduce_global(slots_prev, D.nslots, rec_old, g, gkey, gidx, red);
+    reduce_global(slots_prev, D.nslots, D.block, rec_old, g, gkey, gidx, red);
     if (tile == 0) {
         write_record(rec_prev, g, gkey, gidx);
         if (threadIdx.x == 0 && D.hist && n - 1 < D.hist_len) D.hist[n - 1] = gkey;
@@ -295,7 +300,7 @@ __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays
     }
 
     // (b) evaluate, personal best, velocity and position
-    const int64_t i = tile * BS + threadIdx.x;
+    const int64_t i = tile * (BS / LPP) + threadIdx.x / LPP;
     const bool valid = i < D.m;
     const int64_t j = valid ? i : D.m - 1;
     const int64_t ld = B.ld, gj = D.off + j, gi = D.off + i;
@@ -306,7 +311,7 @@ __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays
     double jp = B.jp[gj];
     double J;
     if (n >= 2)
-        J = eval_cost<BlockScope, steps_per_trip(SINGLE)>(D.k, X, lds, lds_ns);
+        J = eval_cost<BlockScope, steps_per_trip(SINGLE), LPP>(D.k, X, lds, lds_ns);
     else
         J = B.cost[gj];
     const bool better = cost_key(J) < cost_key(jp);
@@ -316,7 +321,7 @@ __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays
         for (int d = 0; d < 6; ++d) Pb[d] = X[d];
     }
     pso_update(D, n, j, X, V, Pb, g);
-    if (valid) {
+    if (valid && threadIdx.x % LPP == 0) {
 #pragma unroll
         for (int d = 0; d < 6; ++d) {
             B.x[d * ld + gi] = X[d];
@@ -335,10 +340,10 @@ __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays
 }
 
 // The iteration kernel with the compiler's register allocation ...
-template <int BS, bool SINGLE>
+template <int BS, bool SINGLE, int LPP = 1>
 __global__ __launch_bounds__(BS) void k_swarm_iter(ProbDesc d0, SwarmArrays B, int64_t n)
 {
-    swarm_iter<BS, SINGLE>(d0, B, n);
+    swarm_iter<BS, SINGLE, LPP>(d0, B, n);
 }
 
 // ... and with registers capped so that at least three waves fit per SIMD
@@ -400,24 +405,26 @@ __global__ __launch_bounds__(256) void k_swarm_final(ProbDesc d0, SwarmArrays B,
 // ---------------------------------------------------------------------------
 
 hipError_t launch_propagate(const KArgs &A, const double *x, int64_t ld, int64_t m,
-                            double *states, hipStream_t st)
+                            double *states, int lanes, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_propagate, dim3(grid_for(m, 256)), dim3(256), 0, st, A, x, ld, m, states);
+    IOD_DISPATCH_LPP(lanes, hipLaunchKernelGGL(k_propagate<LPP_>, dim3(grid_for(m, SPLIT_BS / LPP_)),
+                                               dim3(SPLIT_BS), 0, st, A, x, ld, m, states));
     return hipGetLastError();
 }
 
 hipError_t launch_predict(const KArgs &A, const double *x, int64_t ld, int64_t m,
-                          double *angles, hipStream_t st)
+                          double *angles, int lanes, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_predict, dim3(grid_for(m, 256)), dim3(256), 0, st, A, x, ld, m, angles);
+    IOD_DISPATCH_LPP(lanes, hipLaunchKernelGGL(k_predict<LPP_>, dim3(grid_for(m, SPLIT_BS / LPP_)),
+                                               dim3(SPLIT_BS), 0, st, A, x, ld, m, angles));
     return hipGetLastError();
 }
 
 hipError_t launch_predict_ranges(const KArgs &A, const double *x, int64_t ld, int64_t m,
-                                 double *ranges, hipStream_t st)
+                                 double *ranges, int lanes, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_predict_ranges, dim3(grid_for(m, 256)), dim3(256), 0, st, A, x, ld, m,
-                       ranges);
+    IOD_DISPATCH_LPP(lanes, hipLaunchKernelGGL(k_predict_ranges<LPP_>, dim3(grid_for(m, SPLIT_BS / LPP_)),
+                                               dim3(SPLIT_BS), 0, st, A, x, ld, m, ranges));
     return hipGetLastError();
 }
 
@@ -433,6 +440,11 @@ hipError_t launch_chief(const ProbDesc &d0, const ProbDesc *descs, int64_t nprob
 hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                        hipStream_t st)
 {
+    if (d0.lanes > 1) {
+        IOD_DISPATCH_SPLIT(d0.lanes, if (B.desc) hipLaunchKernelGGL((k_eval<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B);
+                           else hipLaunchKernelGGL((k_eval<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B));
+        return hipGetLastError();
+    }
     const bool single = B.desc == nullptr;
     IOD_DISPATCH_BS(bs, if (single) hipLaunchKernelGGL((k_eval<BS_, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B);
                         else hipLaunchKernelGGL((k_eval<BS_, false>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B));
@@ -442,6 +454,11 @@ hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t
 hipError_t launch_swarm_init(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                              hipStream_t st)
 {
+    if (d0.lanes > 1) {
+        IOD_DISPATCH_SPLIT(d0.lanes, if (B.desc) hipLaunchKernelGGL((k_swarm_init<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B);
+                           else hipLaunchKernelGGL((k_swarm_init<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B));
+        return hipGetLastError();
+    }
     const bool single = B.desc == nullptr;
     IOD_DISPATCH_BS(bs, if (single) hipLaunchKernelGGL((k_swarm_init<BS_, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B);
                         else hipLaunchKernelGGL((k_swarm_init<BS_, false>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B));
@@ -453,6 +470,11 @@ hipError_t launch_swarm_iter(const ProbDesc &d0, const SwarmArrays &B, int bs, i
 {
     const bool single = B.desc == nullptr;
     if (waves != 0 && waves != 3) return hipErrorInvalidValue;
+    if (d0.lanes > 1) {
+        IOD_DISPATCH_SPLIT(d0.lanes, if (single) hipLaunchKernelGGL((k_swarm_iter<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, n);
+                           else hipLaunchKernelGGL((k_swarm_iter<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, n));
+        return hipGetLastError();
+    }
     if (waves == 3) {
         IOD_DISPATCH_BS(bs, if (single) hipLaunchKernelGGL((k_swarm_iter_w3<BS_, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B, n);
                             else hipLaunchKernelGGL((k_swarm_iter_w3<BS_, false>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B, n));

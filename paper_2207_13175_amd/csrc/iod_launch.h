@@ -6,22 +6,25 @@
 
 namespace iodk {
 
+// lanes: adjacent lanes per particle, 1, 2 or 4.
 hipError_t launch_propagate(const KArgs &A, const double *x, int64_t ld, int64_t m,
-                            double *states, hipStream_t st);
+                            double *states, int lanes, hipStream_t st);
 hipError_t launch_predict(const KArgs &A, const double *x, int64_t ld, int64_t m,
-                          double *angles, hipStream_t st);
+                          double *angles, int lanes, hipStream_t st);
 // Angles of xs [nprob][6] at each problem's observations, out [rows][2]
 // (row_off [nprob] first row of each problem).
 hipError_t launch_predict_batch(const ProbDesc *descs, int64_t nprob, const double *xs,
                                 const int64_t *row_off, double *out, hipStream_t st);
 // Ranges |rho| instead of angles: out [K][ld] (single), [rows] (batch).
 hipError_t launch_predict_ranges(const KArgs &A, const double *x, int64_t ld, int64_t m,
-                                 double *ranges, hipStream_t st);
+                                 double *ranges, int lanes, hipStream_t st);
 hipError_t launch_predict_ranges_batch(const ProbDesc *descs, int64_t nprob, const double *xs,
                                        const int64_t *row_off, double *out, hipStream_t st);
 // descs == null: the single problem d0.
 hipError_t launch_chief(const ProbDesc &d0, const ProbDesc *descs, int64_t nprob, hipStream_t st);
-// bs in {64, 128, 256}; grid = workgroups (nslots for a single problem).
+// bs in {64, 128, 256}; grid = workgroups (nslots for a single problem). With
+// d0.lanes > 1 (the same for every problem of a batch) the workgroups hold
+// SPLIT_BS / lanes particles (ProbDesc::block) whatever bs and waves.
 hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                        hipStream_t st);
 hipError_t launch_swarm_init(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
@@ -49,8 +52,9 @@ hipError_t launch_mixed_iter(const ProbDesc &d0, const SwarmArrays &B, int bs, i
 // out: device [nprob][top_k] particle indices (-1 past m), top_k <= TOPK_MAX.
 hipError_t launch_topk(const SwarmArrays &B, const double *keys, int32_t top_k, int32_t *out,
                        hipStream_t st);
+// lanes: adjacent lanes per candidate, 1 or 4.
 hipError_t launch_reeval64(const SwarmArrays &B, const int32_t *cand, int32_t top_k, int64_t n,
-                           hipStream_t st);
+                           int lanes, hipStream_t st);
 
 // Sensitivities. Adjoint scratch per particle column: (ceil(S / ADJ_CKPT) +
 // ADJ_CKPT) rows of 6 doubles, S the steps of one evaluation; mode >= 0

@@ -739,12 +739,80 @@ __global__ __launch_bounds__(TOPK_BS) void k_topk(SwarmArrays B, const double *_
     if (t < top_k) out[p * top_k + t] = si[t] < (double)D.m ? (int32_t)si[t] : -1;
 }
 
-// Per problem (one wave; RE_WAVES problems to a workgroup, so they run on
-// the SIMDs of one compute unit instead of sharing one): FP64 costs of the
-// personal bests of the selected candidates; the lowest (cost, index)
-// replaces the record of iteration n-1 if the record is empty or the cost is
-// strictly lower. Writes record n and hist[n]. The waves never wait for each
-// other: each stages its own problem's observation table.
+// FP64 costs of the personal bests of a problem's selected candidates, LPP
+// lanes per candidate, `rank` of the scope's threads: each thread's best
+// (cost, index) and its state.
+template <class Scope, int LPP>
+__device__ __forceinline__ void reeval_candidates(const ProbDesc &D, const SwarmArrays &B,
+                                                  const int32_t *cand, int32_t top_k, double *lds,
+                                                  int32_t *lds_ns, double &bkey, double &bidx,
+                                                  double bst[6])
+{
+    bkey = INFINITY;
+    bidx = INFINITY;
+#pragma unroll
+    for (int d = 0; d < 6; ++d) bst[d] = 0.0;
+    for (int c0 = 0; c0 < top_k; c0 += Scope::size() / LPP) {
+        const int c = c0 + Scope::rank() / LPP;
+        const int32_t i = c < top_k ? cand[c] : -1;
+        const bool valid = i >= 0;
+        double X[6];
+        load_state(B.p, B.ld, D.off + (valid ? i : 0), X);
+        const double J = eval_cost<Scope, 2, LPP>(D.k, X, lds, lds_ns);
+        const double k = valid ? cost_key(J) : INFINITY, ix = valid ? (double)i : INFINITY;
+        if (lex_less(k, ix, bkey, bidx)) {
+            bkey = k;
+            bidx = ix;
+#pragma unroll
+            for (int d = 0; d < 6; ++d) bst[d] = X[d];
+        }
+    }
+}
+
+// The record of iteration n of problem p from that of n - 1 and the lowest
+// re-evaluated (key, idx) with its state w: it replaces the record if the
+// record is empty or its cost is strictly lower. Then hist[n] and Algorithm
+// 2's decision. `rank`: the thread within those of the problem.
+__device__ __forceinline__ void reeval_record(const ProbDesc &D, const SwarmArrays &B, int64_t p,
+                                              int64_t n, double key, double idx, const double w[6],
+                                              int rank)
+{
+    const double *prev = B.recs + (((n - 1) & 1) * B.nprob + p) * REC;
+    double *cur = B.recs + ((n & 1) * B.nprob + p) * REC;
+    double g[6], gkey, gidx;
+    if (idx < INFINITY && (prev[1] < 0.0 || key < prev[0])) {
+        gkey = key;
+        gidx = idx;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) g[d] = w[d];
+    } else {
+        gkey = prev[0];
+        gidx = prev[1];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) g[d] = prev[2 + d];
+    }
+    if (rank < REC) cur[rank] = rank == 0 ? gkey : rank == 1 ? gidx : g[rank - 2];
+    if (rank == 0 && D.hist && n < D.hist_len) D.hist[n] = gkey;
+    // Algorithm 2 after iteration n
+    if (rank == 0 && D.tol > 0.0 && n > D.tol_lag &&
+        tolerance_met(gkey, D.hist[n - D.tol_lag], D.tol))
+        B.stop[p] = (double)n;
+}
+
+// A problem that Algorithm 2 ended: carry its final record forward.
+__device__ __forceinline__ void reeval_stopped(const ProbDesc &D, const SwarmArrays &B, int64_t p,
+                                               int64_t n, int rank)
+{
+    const double *prev = B.recs + (((n - 1) & 1) * B.nprob + p) * REC;
+    double *cur = B.recs + ((n & 1) * B.nprob + p) * REC;
+    if (rank < REC) cur[rank] = prev[rank];
+    if (rank == 0 && D.hist && n < D.hist_len) D.hist[n] = NAN;
+}
+
+// FP64 re-evaluation, one wave per problem; RE_WAVES problems to a workgroup,
+// so they run on the SIMDs of one compute unit instead of sharing one. The
+// waves never wait for each other: each stages its own problem's observation
+// table.
 constexpr int RE_WAVES = 4;
 
 __global__ __launch_bounds__(64 * RE_WAVES) void k_reeval64(SwarmArrays B,
@@ -758,34 +826,15 @@ __global__ __launch_bounds__(64 * RE_WAVES) void k_reeval64(SwarmArrays B,
     const int lane = (int)(threadIdx.x & 63);
     const int64_t q = (int64_t)blockIdx.x * RE_WAVES + wave;
     if (q >= B.nprob) return;
-    double *lds = lds_w[wave];
-    int32_t *lds_ns = ns_w[wave];
     const int64_t p = B.porder ? B.porder[q] : q;
     const ProbDesc &D = B.desc[p];
-    const double *prev = B.recs + (((n - 1) & 1) * B.nprob + p) * REC;
-    double *cur = B.recs + ((n & 1) * B.nprob + p) * REC;
     if (B.stop[p] >= 0.0) {
-        // ended by Algorithm 2: carry the final record forward
-        if (lane < REC) cur[lane] = prev[lane];
-        if (lane == 0 && D.hist && n < D.hist_len) D.hist[n] = NAN;
+        reeval_stopped(D, B, p, n, lane);
         return;
     }
-    double bkey = INFINITY, bidx = INFINITY, bst[6] = {0, 0, 0, 0, 0, 0};
-    for (int c0 = 0; c0 < top_k; c0 += 64) {
-        const int c = c0 + lane;
-        const int32_t i = c < top_k ? cand[p * top_k + c] : -1;
-        const bool valid = i >= 0;
-        double X[6];
-        load_state(B.p, B.ld, D.off + (valid ? i : 0), X);
-        const double J = eval_cost<WaveScope>(D.k, X, lds, lds_ns);
-        const double k = valid ? cost_key(J) : INFINITY, ix = valid ? (double)i : INFINITY;
-        if (lex_less(k, ix, bkey, bidx)) {
-            bkey = k;
-            bidx = ix;
-#pragma unroll
-            for (int d = 0; d < 6; ++d) bst[d] = X[d];
-        }
-    }
+    double bkey, bidx, bst[6];
+    reeval_candidates<WaveScope, 1>(D, B, cand + p * top_k, top_k, lds_w[wave], ns_w[wave], bkey,
+                                    bidx, bst);
     double key = bkey, idx = bidx;
     wave_argmin(key, idx);
     // the winner's state from the one lane that holds it (candidate indices
@@ -795,24 +844,42 @@ __global__ __launch_bounds__(64 * RE_WAVES) void k_reeval64(SwarmArrays B,
     double w[6];
 #pragma unroll
     for (int d = 0; d < 6; ++d) w[d] = __shfl(bst[d], src, 64);
-    double g[6], gkey, gidx;
-    if (idx < INFINITY && (prev[1] < 0.0 || key < prev[0])) {
-        gkey = key;
-        gidx = idx;
-#pragma unroll
-        for (int d = 0; d < 6; ++d) g[d] = w[d];
-    } else {
-        gkey = prev[0];
-        gidx = prev[1];
-#pragma unroll
-        for (int d = 0; d < 6; ++d) g[d] = prev[2 + d];
+    reeval_record(D, B, p, n, key, idx, w, lane);
+}
+
+// The same with LPP lanes per candidate, one workgroup of 64 LPP threads (64
+// candidates at a time) per problem: the longest problem's wave sets the
+// launch's time, and with few problems most SIMDs would idle (256 problems
+// of up to 2,960 steps: 1.51 -> 1.0 ms).
+template <int LPP>
+__global__ __launch_bounds__(64 * LPP) void k_reeval64_split(SwarmArrays B,
+                                                             const int32_t *__restrict__ cand,
+                                                             int32_t top_k, int64_t n)
+{
+    __shared__ double lds[OBS_CHUNK * TAB_W];
+    __shared__ int32_t lds_ns[OBS_CHUNK];
+    __shared__ double red[2 * LPP];
+    __shared__ double wst[6];
+    const int64_t p = B.porder ? B.porder[blockIdx.x] : blockIdx.x;
+    const ProbDesc &D = B.desc[p];
+    if (B.stop[p] >= 0.0) {
+        reeval_stopped(D, B, p, n, (int)threadIdx.x);
+        return;
     }
-    if (lane < REC) cur[lane] = lane == 0 ? gkey : lane == 1 ? gidx : g[lane - 2];
-    if (lane == 0 && D.hist && n < D.hist_len) D.hist[n] = gkey;
-    // Algorithm 2 after iteration n
-    if (lane == 0 && D.tol > 0.0 && n > D.tol_lag &&
-        tolerance_met(gkey, D.hist[n - D.tol_lag], D.tol))
-        B.stop[p] = (double)n;
+    double bkey, bidx, bst[6];
+    reeval_candidates<BlockScope, LPP>(D, B, cand + p * top_k, top_k, lds, lds_ns, bkey, bidx, bst);
+    double key = bkey, idx = bidx;
+    block_argmin(key, idx, red);
+    // a candidate's lanes hold the same state
+    if (idx < INFINITY && bidx == idx) {
+#pragma unroll
+        for (int d = 0; d < 6; ++d) wst[d] = bst[d];
+    }
+    __syncthreads();
+    double w[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) w[d] = idx < INFINITY ? wst[d] : 0.0;
+    reeval_record(D, B, p, n, key, idx, w, (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -877,8 +944,13 @@ hipError_t launch_topk(const SwarmArrays &B, const double *keys, int32_t top_k, 
 }
 
 hipError_t launch_reeval64(const SwarmArrays &B, const int32_t *cand, int32_t top_k, int64_t n,
-                           hipStream_t st)
+                           int lanes, hipStream_t st)
 {
+    if (lanes > 1) {
+        if (lanes != 4) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_reeval64_split<4>, dim3((unsigned)B.nprob), dim3(64 * 4), 0, st, B, cand, top_k, n);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_reeval64, dim3((unsigned)((B.nprob + RE_WAVES - 1) / RE_WAVES)),
                        dim3(64 * RE_WAVES), 0, st, B, cand, top_k, n);
     return hipGetLastError();

@@ -1,0 +1,75 @@
+"""Several lanes to a particle, and one: the same bits.
+
+Launches that would leave SIMDs idle give each particle two or four lanes.
+A particle's result does not depend on how many others it is launched with,
+so every size is compared, bit for bit, with the same particles inside a
+launch of one lane per particle. Intervals of 1 to 9 steps between the
+observations, off-grid times, and particles that leave the certified range
+(their waves redo the interval on the IEEE path) are among them."""
+import numpy as np
+import pytest
+
+import paper_2207_13175_amd as iod
+from paper_2207_13175_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+FULL = 65536
+
+
+@pytest.fixture(scope="module")
+def setup():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = W.tiny(3)
+    steps = np.cumsum([1, 2, 3, 4, 5, 6, 7, 8, 9, 4])
+    t = steps * 1e-3
+    t[3] += 0.0004
+    t[7] += 0.0007
+    rng = np.random.default_rng(11)
+    h = iod.iod_create_ranged(wl.mu, wl.chief, t, rng.normal(0, 0.3, (len(t), 2)),
+                              rng.uniform(1e-3, 2e-3, len(t)), 1e-5, 1e-7, h=1e-3)
+    x = torch.from_numpy(np.ascontiguousarray(W.random_swarm(7, FULL, wl.lo, wl.hi).T)).cuda()
+    # scattered particles on a primary, next to it, far away and not finite
+    x[:3, 70] = torch.tensor([1 - wl.mu, 0.0, 0.0], dtype=torch.float64, device="cuda")
+    x[:3, 5000] = torch.tensor([1 - wl.mu + 1e-80, 0.0, 0.0], dtype=torch.float64, device="cuda")
+    x[0, 16383] = 1e120
+    x[4, 31] = float("nan")
+
+    def run(m):
+        kw = dict(dtype=torch.float64, device="cuda")
+        K, xm = len(t), x[:, :m].contiguous()
+        out = [torch.full((K, 6, m), 7.0, **kw), torch.full((K, 2, m), 7.0, **kw),
+               torch.full((K, m), 7.0, **kw), torch.full((m,), 7.0, **kw)]
+        iod.iod_propagate(h, xm, m, out[0])
+        iod.iod_predict(h, xm, m, out[1])
+        iod.iod_predict_ranges(h, xm, m, out[2])
+        iod.iod_eval_swarm(h, xm, m, out[3])
+        torch.cuda.synchronize()
+        return [o.cpu().numpy() for o in out]
+    return run, run(FULL)
+
+
+@pytest.mark.parametrize("m", [1, 16, 63, 64, 65, 129, 1000, 16383, 16384, 16385, 32767, 32768, 32769])
+def test_any_lane_count_gives_the_same_bits(setup, m):
+    run, full = setup
+    for got, want in zip(run(m), full):
+        assert np.array_equal(got, want[..., :m], equal_nan=True)
+
+
+@pytest.mark.parametrize("m", [200, 20000])
+def test_swarm_of_split_particles_in_a_batch(m):
+    """A problem alone (several lanes per particle) and inside a batch large
+    enough for one lane per particle: the same global bests."""
+    wl = W.tiny(4, K=4, T=0.02)
+    rng = np.random.default_rng(3)
+    ang = rng.normal(0, 0.3, (wl.K, 2))
+    p = iod.pso_params(0.7, 1.5, 1.5, 5, wl.lo, wl.hi, problem=0)
+    h = iod.iod_create(wl.mu, wl.chief, wl.t, ang, wl.sigma, h=wl.h)
+    g, J, hist = iod.iod_solve(h, p, m, 3)
+    n = 1 + 90000 // m
+    b = iod.iod_create_batch([wl.mu] * n, [wl.chief] * n, [wl.t] * n, [ang] * n, [wl.sigma] * n, h=wl.h)
+    gs, Js, hists = iod.iod_batch_solve(b, [p] * n, np.full(n, m), 3)
+    assert all(np.array_equal(gs[q], g) and Js[q] == J and np.array_equal(hists[q], hist)
+               for q in range(n))
