@@ -1603,11 +1603,46 @@ int64_t adj_rows(const HostProblem &P)
 // jtj 21, jtr 6, grad 6, trial 6, chi2 at trial 1, damping 1, cost 1.
 constexpr int64_t POLISH_COLS = 42;
 
+// The problems of a sensitivity launch, and which of its sweeps are pipelined.
+// The pipelined form shortens a step about four times (normal equations) or
+// three times (gradient) while its workgroups (PIPE_P particles of one
+// problem) have a compute unit each, and the launch grows with every further
+// one to a unit: the normal equations by about half, the gradient by a third
+// if their LDS lets several share a unit, else by its whole time.
+// Over 2,000 steps the normal equations take 0.94, 1.48, 2.16 and 2.81 ms with
+// one to four workgroups to a unit against 4.1 ms otherwise; the gradient 1.60,
+// 3.18 and 4.7 ms against 4.7 ms, and over 500 steps (two share a unit) 0.45,
+// 0.60 and 0.95 ms against 1.2 ms.
+struct PipePlan {
+    int64_t groups = 0, steps = 0, grid = 0;
+    int32_t sub = 1, seg = PIPE_SUB;
+    bool tan = false, adj = false;
+    void add(int64_t m, int64_t s)
+    {
+        if (m < 1) return;
+        groups += ceil_div(m, PIPE_P);
+        steps = std::max(steps, s);
+        if (s <= PIPE_MAX_STEPS) seg = std::max(seg, pipe_segment((int32_t)s));
+    }
+    // the most workgroups for which the gradient's sweep is pipelined
+    int64_t adj_limit(int simds, bool tan_too = false) const
+    {
+        const int64_t shared = (160 << 10) / pipe_lds_bytes(seg, tan_too, true);
+        return (shared > 1 ? 3 : 2) * (simds / 4);
+    }
+    void decide(int simds)
+    {
+        if (steps > PIPE_MAX_STEPS) return;
+        tan = groups <= 4 * (simds / 4);
+        adj = groups <= adj_limit(simds);
+    }
+};
+
 // Damped Gauss-Newton on the columns of B.x (in place): the normal matrix
 // from the forward tangent, the gradient from the discrete adjoint; d0 / the
 // descriptors in B must carry the least-squares cost (mode 1).
 int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t n_iter,
-               double *chi2, double *work, int64_t ld, hipStream_t st)
+               double *chi2, double *work, int64_t ld, const PipePlan &plan, hipStream_t st)
 {
     double *jtj = work;
     double *jtr = jtj + 21 * ld;
@@ -1618,12 +1653,26 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
     double *cost = lam + ld;
     double *adj = cost + ld;
     double *x = B.x;
+    PipeArgs Q;
+    Q.sub = plan.sub;
+    Q.mode = 1;
+    Q.chi2 = chi2;
+    Q.jtj = jtj;
+    Q.jtr = jtr;
+    Q.grad = g;
+    Q.work = adj;
+    Q.wld = ld;
+    auto normal = [&]() {
+        return plan.tan ? launch_sens_pipe(d0, B, Q, plan.grid, plan.seg, true, false, st)
+                        : launch_normal(d0, B, bs, grid, chi2, jtj, jtr, st);
+    };
     HIP_TRY(launch_fill_cols(d0, B, bs, grid, lam, 1e-3, st));
     for (int32_t it = 0; it < n_iter; ++it) {
         B.x = x;
-        HIP_TRY(launch_normal(d0, B, bs, grid, chi2, jtj, jtr, st));
+        HIP_TRY(normal());
         B.cost = cost;
-        HIP_TRY(launch_grad(d0, B, bs, grid, g, adj, ld, 1, st));
+        HIP_TRY(plan.adj ? launch_sens_pipe(d0, B, Q, plan.grid, plan.seg, false, true, st)
+                         : launch_grad(d0, B, bs, grid, g, adj, ld, 1, st));
         HIP_TRY(launch_gn_solve(d0, B, bs, grid, jtj, g, 0.5, lam, xt, st));
         B.x = xt;
         B.cost = chi2t;
@@ -1633,7 +1682,7 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
     }
     if (n_iter == 0) {
         B.x = x;
-        HIP_TRY(launch_normal(d0, B, bs, grid, chi2, jtj, jtr, st));
+        HIP_TRY(normal());
     }
     return IOD_OK;
 }
@@ -1656,7 +1705,8 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
                       const int32_t *n, int64_t P, int32_t T, int32_t n_iter, double *chi2,
                       double *work, double *vt, double *jrows, int32_t n_cand, int32_t *active,
                       int32_t *done, const int32_t *lanes, int64_t nlanes, int32_t *live,
-                      int64_t *live_count, int64_t ld, hipStream_t st)
+                      int64_t *live_count, int64_t ld, const PipePlan &plan, int simds,
+                      hipStream_t st)
 {
     const int64_t jld = P * n_cand;
     double *jtj = work;
@@ -1674,6 +1724,35 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     TB.desc = tdesc;
     TB.x = xt;
     TB.cost = chi2t;
+    // While few problems are active, the pipelined sweeps and several lanes
+    // per trial shorten the launches, which then last as long as one wave;
+    // with many, the forms that fill every lane win. The number of active
+    // problems is on the device, so both forms are launched with complementary
+    // gates (the one whose turn it is not exits at once) unless even all
+    // problems are few. Tried lanes: one workgroup of four waves per problem.
+    int32_t *problems = (int32_t *)(live_count + 1);
+    const int32_t sub = plan.sub;
+    const bool pipe = plan.steps <= PIPE_MAX_STEPS;
+    Gate few, many, split, whole;
+    few.count = many.count = split.count = whole.count = problems;
+    few.upto = many.above = pipe ? (int32_t)(plan.adj_limit(simds, true) / sub) : 0;
+    split.upto = whole.above = simds / 4;
+    PipeArgs Q;
+    Q.sub = sub;
+    Q.mode = 1;
+    Q.done = done;
+    Q.gate = few;
+    Q.chi2 = chi2;
+    Q.jtj = jtj;
+    Q.jtr = jtr;
+    Q.jrows = jrows;
+    Q.jstride = n_cand;
+    Q.jld = jld;
+    Q.grad = g;
+    Q.work = adj;
+    Q.wld = ld;
+    ProbDesc dsplit = d0;   // only its lane count is read by a batch's launch
+    dsplit.lanes = 4;
     // the normal equations and the gradient see only the candidates: packed,
     // several problems' candidates to a wave, problems with the most RK4
     // steps first. Each iteration they take only the live pairs (problem
@@ -1690,20 +1769,26 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     LL.n = nlanes;
     LL.count = live_count;
     const int64_t kgrid = (nlanes + 63) / 64;
-    HIP_TRY(launch_live_lanes(lanes, nlanes, active, done, live, live_count, st));
+    HIP_TRY(launch_live_lanes(lanes, nlanes, active, P, done, live, live_count, problems, st));
     for (int32_t it = 0; it < n_iter; ++it) {
         SwarmArrays GB = PB;
         GB.cost = cost;
-        HIP_TRY(launch_normal_grad(d0, PB, GB, kgrid, chi2, jtj, jtr, jrows, n_cand, jld, g, adj,
-                                   ld, 1, st, LL));
+        if (pipe) HIP_TRY(launch_sens_pipe(d0, PB, Q, P * sub, plan.seg, true, true, st));
+        if (P > many.above)
+            HIP_TRY(launch_normal_grad(d0, PB, GB, kgrid, chi2, jtj, jtr, jrows, n_cand, jld, g,
+                                       adj, ld, 1, st, LL, many));
         HIP_TRY(launch_gn_trials(x, jtj, g, lam, n, active, done, T, P, ld, xt, vt, st));
         HIP_TRY(launch_geo(PB.desc, x, jtj, jtr, jrows, n_cand, jld, lam, n, active, done, T, P,
-                           ld, GEO_HD, GEO_ALPHA, vt, xt, st));
-        HIP_TRY(launch_eval(d0, TB, 64, P, st));
+                           ld, GEO_HD, GEO_ALPHA, vt, xt, 4, split, st));
+        if (P > whole.above)
+            HIP_TRY(launch_geo(PB.desc, x, jtj, jtr, jrows, n_cand, jld, lam, n, active, done, T,
+                               P, ld, GEO_HD, GEO_ALPHA, vt, xt, 1, whole, st));
+        HIP_TRY(launch_eval(dsplit, TB, 64, P, st, split));
+        if (P > whole.above) HIP_TRY(launch_eval(d0, TB, 64, P, st, whole));
         HIP_TRY(launch_gn_select(x, chi2, lam, done, active, xt, chi2t, n, T, P, ld,
                                  POLISH_STEP_TOL, st));
         if (it + 1 < n_iter)
-            HIP_TRY(launch_live_lanes(lanes, nlanes, active, done, live, live_count, st));
+            HIP_TRY(launch_live_lanes(lanes, nlanes, active, P, done, live, live_count, problems, st));
     }
     if (n_iter == 0) {
         HIP_TRY(launch_normal(d0, PB, 64, P, chi2, jtj, jtr, st));
@@ -1718,8 +1803,16 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     // at the final states.
     SwarmArrays AB = PB;
     AB.active = nullptr;
+    PipeArgs F;
+    F.sub = sub;
+    F.chi2 = chi2;
+    F.jtj = jtj;
+    F.jtr = jtr;
     for (int f = 0; f < 2; ++f) {
-        HIP_TRY(launch_normal(d0, AB, 64, kgrid, chi2, jtj, jtr, st, nullptr, 0, 0, KL));
+        if (plan.tan)
+            HIP_TRY(launch_sens_pipe(d0, AB, F, P * sub, plan.seg, true, false, st));
+        else
+            HIP_TRY(launch_normal(d0, AB, 64, kgrid, chi2, jtj, jtr, st, nullptr, 0, 0, KL));
         HIP_TRY(launch_gn_final(x, jtj, jtr, n, P, ld, GN_FINAL_MAX_STEP, st));
     }
     AB.cost = chi2;
@@ -1800,9 +1893,13 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
             lanes.push_back(j);
         }
     const int64_t nlanes = (int64_t)lanes.size() / 2;
+    PipePlan plan;
+    plan.sub = (S.n_cand + PIPE_P - 1) / PIPE_P;
+    for (int64_t p = 0; p < P; ++p) plan.add(n[p], b->probs[p].ns[b->probs[p].K - 1]);
+    plan.decide(b->simds);
     HIP_TRY(Q.lanes.upload(lanes, st));
     HIP_TRY(Q.live.ensure(std::max<size_t>(lanes.size(), 2) * sizeof(int32_t)));
-    HIP_TRY(Q.live_count.ensure(sizeof(int64_t)));
+    HIP_TRY(Q.live_count.ensure(2 * sizeof(int64_t)));   // live pairs, active problems
     // the retirement flags start cleared on every call (the kernels change them)
     HIP_TRY(hipMemsetD32Async((hipDeviceptr_t)Q.act.p, 1, (size_t)P, st));
     HIP_TRY(hipMemsetAsync(Q.done.p, 0, (size_t)ldp * sizeof(int32_t), st));
@@ -1818,7 +1915,7 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
                                Q.vt.as<double>(), Q.jrows.as<double>(), S.n_cand,
                                Q.act.as<int32_t>(), Q.done.as<int32_t>(),
                                Q.lanes.as<const int32_t>(), nlanes, Q.live.as<int32_t>(),
-                               Q.live_count.as<int64_t>(), ldp, st);
+                               Q.live_count.as<int64_t>(), ldp, plan, b->simds, st);
     if (rc != IOD_OK) return rc;
     HIP_TRY(launch_pick_best(Q.x.as<const double>(), Q.chi.as<const double>(),
                              Q.nn.as<const int32_t>(), P, ldp, stride, Q.best.as<double>(),
@@ -1858,6 +1955,30 @@ void single_cols(const iod_handle *h, const double *x, int64_t ld, int64_t m, in
     B.x = const_cast<double *>(x);
     B.ld = ld;
     B.nprob = 1;
+}
+
+// The sensitivity sweeps of m columns of one problem.
+PipePlan single_plan(const iod_handle *h, int64_t m)
+{
+    PipePlan plan;
+    plan.add(m, h->P.ns[h->P.K - 1]);
+    plan.grid = plan.groups;
+    plan.decide(h->simds);
+    return plan;
+}
+
+// Cost and gradient of the columns of B.
+int single_grad(const iod_handle *h, const ProbDesc &D, const SwarmArrays &B, int bs, double *grad,
+                double *work, int64_t ld, hipStream_t st)
+{
+    const PipePlan plan = single_plan(h, D.m);
+    PipeArgs Q;
+    Q.grad = grad;
+    Q.work = work;
+    Q.wld = ld;
+    HIP_TRY(plan.adj ? launch_sens_pipe(D, B, Q, plan.grid, plan.seg, false, true, st)
+                     : launch_grad(D, B, bs, D.nslots, grad, work, ld, -1, st));
+    return IOD_OK;
 }
 
 // Static device scratch of iod_grad_noalloc (adjoint checkpoints and segment
@@ -1954,8 +2075,7 @@ int iod_grad(iod_handle *h, const double *x, int64_t ld, int64_t m, double *cost
     SwarmArrays B;
     single_cols(h, x, ld, m, bs, D, B);
     B.cost = cost;
-    HIP_TRY(launch_grad(D, B, bs, D.nslots, grad, work, ld, -1, (hipStream_t)stream));
-    return IOD_OK;
+    return single_grad(h, D, B, bs, grad, work, ld, (hipStream_t)stream);
 }
 
 int iod_grad_noalloc(iod_handle *h, const double *x, int64_t ld, int64_t m, double *cost,
@@ -1980,8 +2100,7 @@ int iod_grad_noalloc(iod_handle *h, const double *x, int64_t ld, int64_t m, doub
     SwarmArrays B;
     single_cols(h, x, ld, m, bs, D, B);
     B.cost = cost;
-    HIP_TRY(launch_grad(D, B, bs, D.nslots, grad, work, ld, -1, (hipStream_t)stream));
-    return IOD_OK;
+    return single_grad(h, D, B, bs, grad, work, ld, (hipStream_t)stream);
 }
 
 int iod_normal_eq(iod_handle *h, const double *x, int64_t ld, int64_t m, double *chi2,
@@ -1995,7 +2114,13 @@ int iod_normal_eq(iod_handle *h, const double *x, int64_t ld, int64_t m, double 
     ProbDesc D;
     SwarmArrays B;
     single_cols(h, x, ld, m, bs, D, B);
-    HIP_TRY(launch_normal(D, B, bs, D.nslots, chi2, jtj, jtr, (hipStream_t)stream));
+    const PipePlan plan = single_plan(h, m);
+    PipeArgs Q;
+    Q.chi2 = chi2;
+    Q.jtj = jtj;
+    Q.jtr = jtr;
+    HIP_TRY(plan.tan ? launch_sens_pipe(D, B, Q, plan.grid, plan.seg, true, false, (hipStream_t)stream)
+                     : launch_normal(D, B, bs, D.nslots, chi2, jtj, jtr, (hipStream_t)stream));
     return IOD_OK;
 }
 
@@ -2019,7 +2144,8 @@ int iod_polish(iod_handle *h, double *x, int64_t ld, int64_t m, int32_t n_iter, 
     SwarmArrays B;
     single_cols(h, x, ld, m, bs, D, B);
     D.k.mode = IOD_COST_CHI2;
-    return polish_run(D, B, bs, D.nslots, n_iter, chi2, work, ld, (hipStream_t)stream);
+    return polish_run(D, B, bs, D.nslots, n_iter, chi2, work, ld, single_plan(h, m),
+                      (hipStream_t)stream);
 }
 
 int64_t iod_batch_polish_work_len(const iod_batch *b, int64_t ld)
@@ -2056,7 +2182,12 @@ int iod_batch_polish(iod_batch *b, double *x, int64_t ld, const int64_t *m, int3
     B.x = x;
     B.ld = ld;
     B.nprob = b->P;
-    return polish_run(L.descs[0], B, bs, L.grid, n_iter, chi2, work, ld, st);
+    PipePlan plan;
+    for (int32_t p = 0; p < b->P; ++p) plan.add(m[p], b->probs[p].ns[b->probs[p].K - 1]);
+    plan.sub = bs / PIPE_P;
+    plan.grid = L.grid * plan.sub;
+    plan.decide(b->simds);
+    return polish_run(L.descs[0], B, bs, L.grid, n_iter, chi2, work, ld, plan, st);
 }
 
 // PSO (FP64 or mixed precision), then the Gauss-Newton polish of n_cand

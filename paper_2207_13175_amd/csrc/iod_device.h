@@ -273,12 +273,13 @@ struct Quad {
 
 // The position-dependent part of rhs<true> at p, shared by a particle's
 // lanes: c1, c2, their sum and the offsets; returns the mark. xj, muj: with four
-// lanes, mu or -mu1 and mu1 or mu by the lane's primary.
+// lanes, mu or -mu1 and mu1 or mu by the lane's primary. JAC (four lanes): also
+// the own primary's Jacobian factor e_j = 3 c_j / r_j^2 (rhs_jac).
 struct Attraction {
-    double d1, d2, c1, c2, cs;
+    double d1, d2, c1, c2, cs, ej;
 };
 
-template <int LPP>
+template <int LPP, bool JAC = false>
 __device__ __forceinline__ Mark attraction(double mu, double mu1, double xj, double muj,
                                          const double p[3], Attraction &o)
 {
@@ -290,11 +291,14 @@ __device__ __forceinline__ Mark attraction(double mu, double mu1, double xj, dou
         const double dj = p[0] + xj;
         const double rs = fma(dj, dj, q);
         double hj;
-        const double Dj = rs * sqrt_inrange(rs, hj);
+        const double qj = sqrt_inrange(rs, hj);
+        const double Dj = rs * qj;
         const double Do = Quad<4>::other(Dj);
         const double ho = Quad<4>::other(hj);
         D = Dj * Do;
-        const double cj = muj * (Do * rcp_from_roots(D, hj, ho, e));
+        const double ij = Do * rcp_from_roots(D, hj, ho, e);
+        const double cj = muj * ij;
+        if (JAC) o.ej = 3.0 * cj * (qj * ij);
         o.c1 = Quad<4>::first(cj);
         o.c2 = Quad<4>::second(cj);
     } else {
@@ -320,66 +324,83 @@ __device__ __forceinline__ void accel_xy(const Attraction &o, const double p[3],
     ay = fma(-o.cs, p[1], fma(-2.0, vx, p[1]));
 }
 
-// n steps as rk4_steps, by the LPP lanes of each particle. In each half of a
-// step the lanes evaluate their own stage's attraction, then the earlier
-// stage's acceleration (with the velocity all lanes know) passes to the later
-// stage's lanes, whose velocity and acceleration it completes.
+// What a particle's lanes see of the stages on the way: sink(half, p, o), the
+// own stage's position and attraction (stages 1 and 2 in half 0, 3 and 4 in 1).
+struct NoSink {
+    static constexpr bool JAC = false;
+    __device__ __forceinline__ void operator()(int, const double *, const Attraction &) {}
+};
+
+// One RK4 step on the in-range path by the LPP lanes of each particle. In each
+// half of the step the lanes evaluate their own stage's attraction, then the
+// earlier stage's acceleration (with the velocity all lanes know) passes to
+// the later stage's lanes, whose velocity and acceleration it completes.
+template <int LPP, class Sink>
+__device__ __forceinline__ void split_step(double mu, double mu1, double h, double h2, double h6,
+                                           double X[6], Cert &cert, Sink &sink)
+{
+    using Q = Quad<LPP>;
+    const bool is_late = Q::is_late(), second = LPP == 4 && (threadIdx.x & 1);
+    const double ha = is_late ? h2 : 0.0, hb = is_late ? h : h2;
+    const double xj = second ? -mu1 : mu, muj = second ? mu : mu1;
+    const double *V = X + 3;
+    double p[3], a[3], w[3], k1[3], k2[3], k3[3], v2[3], v3[3], v4[3];
+    Attraction o;
+    // stages 1 and 2
+#pragma unroll
+    for (int d = 0; d < 3; ++d) p[d] = fma(ha, V[d], X[d]);
+    const Mark m = attraction<LPP, Sink::JAC>(mu, mu1, xj, muj, p, o);
+    sink(0, p, o);
+    double ax, ay;
+    accel_xy(o, p, V[0], V[1], ax, ay);
+    k1[0] = Q::early(ax);
+    k1[1] = Q::early(ay);
+    // the own stage's velocity: V, or stage 2's V + h/2 k1
+    accel_xy(o, p, fma(ha, k1[0], V[0]), fma(ha, k1[1], V[1]), a[0], a[1]);
+    a[2] = -(o.cs * p[2]);
+    k1[2] = Q::early(a[2]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        // the next stage's velocity: stage 2's (early) or stage 3's (late)
+        w[d] = fma(h2, a[d], V[d]);
+        k2[d] = Q::late(a[d]);
+        v2[d] = fma(h2, k1[d], V[d]);
+        v3[d] = fma(h2, k2[d], V[d]);
+    }
+    // stages 3 and 4
+#pragma unroll
+    for (int d = 0; d < 3; ++d) p[d] = fma(hb, w[d], X[d]);
+    cert.add(m, attraction<LPP, Sink::JAC>(mu, mu1, xj, muj, p, o));
+    sink(1, p, o);
+    accel_xy(o, p, v3[0], v3[1], ax, ay);
+    k3[0] = Q::early(ax);
+    k3[1] = Q::early(ay);
+    a[2] = -(o.cs * p[2]);
+    k3[2] = Q::early(a[2]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) v4[d] = fma(h, k3[d], V[d]);
+    accel_xy(o, p, v4[0], v4[1], a[0], a[1]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double sx = fma(2.0, v3[d], fma(2.0, v2[d], V[d])) + v4[d];
+        const double sv = fma(2.0, k3[d], fma(2.0, k2[d], k1[d])) + Q::late(a[d]);
+        X[d] = fma(h6, sx, X[d]);
+        X[3 + d] = fma(h6, sv, X[3 + d]);
+    }
+}
+
+// n steps as rk4_steps, by the LPP lanes of each particle.
 template <int LPP>
 __device__ __forceinline__ void rk4_steps_split(const KArgs &A, int32_t n, double X[6])
 {
-    using Q = Quad<LPP>;
-    const double mu = A.mu, mu1 = A.mu1, h = A.h, h2 = A.h2, h6 = A.h6;
     if (A.fast) {
-        const bool late = Q::is_late(), second = LPP == 4 && (threadIdx.x & 1);
-        const double ha = late ? h2 : 0.0, hb = late ? h : h2;
-        const double xj = second ? -mu1 : mu, muj = second ? mu : mu1;
         double X0[6];
 #pragma unroll
         for (int d = 0; d < 6; ++d) X0[d] = X[d];
         Cert cert;
+        NoSink none;
         auto step = [&]() __attribute__((always_inline)) {
-            const double *V = X + 3;
-            double p[3], a[3], w[3], k1[3], k2[3], k3[3], v2[3], v3[3], v4[3];
-            Attraction o;
-            // stages 1 and 2
-#pragma unroll
-            for (int d = 0; d < 3; ++d) p[d] = fma(ha, V[d], X[d]);
-            const Mark ma = attraction<LPP>(mu, mu1, xj, muj, p, o);
-            double ax, ay;
-            accel_xy(o, p, V[0], V[1], ax, ay);
-            k1[0] = Q::early(ax);
-            k1[1] = Q::early(ay);
-            // the own stage's velocity: V, or stage 2's V + h/2 k1
-            accel_xy(o, p, fma(ha, k1[0], V[0]), fma(ha, k1[1], V[1]), a[0], a[1]);
-            a[2] = -(o.cs * p[2]);
-            k1[2] = Q::early(a[2]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                // the next stage's velocity: stage 2's (early) or stage 3's (late)
-                w[d] = fma(h2, a[d], V[d]);
-                k2[d] = Q::late(a[d]);
-                v2[d] = fma(h2, k1[d], V[d]);
-                v3[d] = fma(h2, k2[d], V[d]);
-            }
-            // stages 3 and 4
-#pragma unroll
-            for (int d = 0; d < 3; ++d) p[d] = fma(hb, w[d], X[d]);
-            cert.add(ma, attraction<LPP>(mu, mu1, xj, muj, p, o));
-            accel_xy(o, p, v3[0], v3[1], ax, ay);
-            k3[0] = Q::early(ax);
-            k3[1] = Q::early(ay);
-            a[2] = -(o.cs * p[2]);
-            k3[2] = Q::early(a[2]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) v4[d] = fma(h, k3[d], V[d]);
-            accel_xy(o, p, v4[0], v4[1], a[0], a[1]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const double sx = fma(2.0, v3[d], fma(2.0, v2[d], V[d])) + v4[d];
-                const double sv = fma(2.0, k3[d], fma(2.0, k2[d], k1[d])) + Q::late(a[d]);
-                X[d] = fma(h6, sx, X[d]);
-                X[3 + d] = fma(h6, sv, X[3 + d]);
-            }
+            split_step<LPP>(A.mu, A.mu1, A.h, A.h2, A.h6, X, cert, none);
         };
         // (written out: the compiler does not unroll a loop of lane exchanges
         // whose trip count it does not know)
@@ -398,9 +419,9 @@ __device__ __forceinline__ void rk4_steps_split(const KArgs &A, int32_t n, doubl
     for (int32_t j = 0; j < n; ++j) {
         double a[6];
         Cert ieee;
-        rk4_sum<false>(mu, mu1, h, h2, X, a, ieee);
+        rk4_sum<false>(A.mu, A.mu1, A.h, A.h2, X, a, ieee);
 #pragma unroll
-        for (int d = 0; d < 6; ++d) X[d] = fma(h6, a[d], X[d]);
+        for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
     }
 }
 
@@ -819,6 +840,11 @@ __device__ __forceinline__ const ProbDesc &locate(const ProbDesc &d0, const Swar
 // ---------------------------------------------------------------------------
 // Launch helpers.
 // ---------------------------------------------------------------------------
+
+__device__ __forceinline__ bool closed(const Gate &g)
+{
+    return g.count && !(*g.count > g.above && *g.count <= g.upto);
+}
 
 static inline unsigned grid_for(int64_t m, int bs) { return (unsigned)((m + bs - 1) / bs); }
 

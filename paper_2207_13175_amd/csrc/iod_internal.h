@@ -113,4 +113,51 @@ constexpr int TOPK_MAX = 256;
 // Steps between adjoint checkpoints.
 constexpr int ADJ_CKPT = 64;
 
+// Pipelined sensitivities (k_sens_pipe): particles per workgroup, steps handed
+// over at a time forward and back, and the most steps of an evaluation that
+// they take: a segment of the reverse sweep and one block more have to fit a
+// compute unit's LDS.
+constexpr int PIPE_P = 16;
+constexpr int PIPE_FWD = 8, PIPE_SUB = 8;
+constexpr int32_t PIPE_MAX_STEPS = 4096, PIPE_MAX_SEG = 32;
+// One step of stage data and the two hand-over states, in double2.
+constexpr int PIPE_STEP = 12 * PIPE_P + PIPE_P + PIPE_P / 2;
+constexpr int PIPE_XEND = 2 * 6 * PIPE_P / 2;
+
+// Steps between its checkpoints: as few as the adjoint's scratch rows (one per
+// ADJ_CKPT steps and ADJ_CKPT more) can hold, in whole blocks; at most 32.
+__host__ __device__ inline int32_t pipe_segment(int32_t steps)
+{
+    const int32_t rows = (steps + ADJ_CKPT - 1) / ADJ_CKPT + ADJ_CKPT;
+    const int32_t n = (steps + rows - 1) / rows;
+    return n <= PIPE_SUB ? PIPE_SUB : (n + PIPE_SUB - 1) / PIPE_SUB * PIPE_SUB;
+}
+
+// A launch's turn, decided by a number on the device: it runs only while
+// above < *count <= upto. Two forms of a launch with complementary gates let
+// the refinement switch between them as its problems retire, with no host
+// round trip. A null count: always runs.
+struct Gate {
+    const int32_t *count = nullptr;
+    int32_t above = 0, upto = 0x7fffffff;
+};
+
+// LDS of a workgroup whose longest segment has seg steps.
+inline int64_t pipe_lds_bytes(int32_t seg, bool tan, bool adj)
+{
+    const int64_t fwd = tan ? 2 * PIPE_FWD : 0, rev = adj ? seg + PIPE_SUB : 0;
+    return (PIPE_XEND + (fwd > rev ? fwd : rev) * PIPE_STEP) * 16;
+}
+
+struct PipeArgs {
+    int32_t sub = 1;                 // workgroups per work entry (a batch)
+    int32_t mode = -1;               // >= 0 overrides the cost mode
+    const int32_t *done = nullptr;   // [columns]: results not wanted, or null
+    Gate gate;
+    double *chi2 = nullptr, *jtj = nullptr, *jtr = nullptr, *jrows = nullptr;
+    int64_t jstride = 0, jld = 0;
+    double *grad = nullptr, *work = nullptr;
+    int64_t wld = 0;
+};
+
 }  // namespace iodk

@@ -26,7 +26,7 @@ hipError_t launch_chief(const ProbDesc &d0, const ProbDesc *descs, int64_t nprob
 // d0.lanes > 1 (the same for every problem of a batch) the workgroups hold
 // SPLIT_BS / lanes particles (ProbDesc::block) whatever bs and waves.
 hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
-                       hipStream_t st);
+                       hipStream_t st, const Gate &G = Gate());
 hipError_t launch_swarm_init(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                              hipStream_t st);
 // waves: 0 = the compiler's register allocation, 3 = registers capped so
@@ -76,7 +76,17 @@ hipError_t launch_normal(const ProbDesc &d0, const SwarmArrays &B, int bs, int64
 hipError_t launch_normal_grad(const ProbDesc &d0, const SwarmArrays &NB, const SwarmArrays &GB,
                               int64_t grid, double *chi2, double *jtj, double *jtr, double *jrows,
                               int64_t jstride, int64_t jld, double *grad, double *work,
-                              int64_t wld, int32_t mode, hipStream_t st, const Lanes &L);
+                              int64_t wld, int32_t mode, hipStream_t st, const Lanes &L,
+                              const Gate &G);
+// The pipelined form of the two for few particles (same results): tan, the
+// normal equations into Q.chi2, jtj, jtr (and jrows); adj, the gradient into
+// Q.grad with scratch Q.work [rows][6][Q.wld], and, without tan, the cost into
+// B.cost. Both together: batches only. One workgroup per PIPE_P particles: grid =
+// ceil(m / PIPE_P) for a single problem, work entries * Q.sub for a batch.
+// seg: the largest pipe_segment of its problems (none of more than
+// PIPE_MAX_STEPS steps).
+hipError_t launch_sens_pipe(const ProbDesc &d0, const SwarmArrays &B, const PipeArgs &Q,
+                            int64_t grid, int32_t seg, bool tan, bool adj, hipStream_t st);
 // Per-column Gauss-Newton step (on B.x) and acceptance, over B's layout.
 hipError_t launch_gn_solve(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                            const double *jtj, const double *g, double gscale, const double *lam,
@@ -100,16 +110,18 @@ hipError_t launch_gn_trials(const double *x, const double *jtj, const double *g,
 // updated in place where the correction is accepted); descs the candidates'
 // problem descriptors, jtj / jtr the normal equations at the candidates and
 // jrows their rows of J (launch_normal's layout, candidate j of problem p in
-// column p jstride + j).
+// column p jstride + j). lanes: adjacent lanes per trial, 1 or 4.
 hipError_t launch_geo(const ProbDesc *descs, const double *x, const double *jtj, const double *jtr,
                       const double *jrows, int64_t jstride, int64_t jld, const double *lam,
                       const int32_t *n, const int32_t *active, const int32_t *done, int32_t T,
                       int64_t nprob, int64_t ld, double hd, double alpha, const double *vt,
-                      double *xt, hipStream_t st);
+                      double *xt, int lanes, const Gate &G, hipStream_t st);
 // The pairs of lanes [n][2] whose problem is active and candidate not done,
-// in order, into out [n][2]; their number into *count (device).
-hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active,
-                            const int32_t *done, int32_t *out, int64_t *count, hipStream_t st);
+// in order, into out [n][2]; their number into *count and that of the active
+// ones of the nprob problems into *problems (device).
+hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active, int64_t nprob,
+                            const int32_t *done, int32_t *out, int64_t *count, int32_t *problems,
+                            hipStream_t st);
 // Undamped Gauss-Newton step of each candidate (column p * 64 + j, j < n[p])
 // from the normal equations jtj, jtr at x, applied in place where no
 // component exceeds max_step.

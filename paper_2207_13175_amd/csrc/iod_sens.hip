@@ -5,6 +5,8 @@
 // acceptance that refine the swarm's best (in place of the paper's
 // Levenberg-Marquardt Local Minimization, eqs. non:linear:lsq and
 // nonlinlsq:cost).
+#include <algorithm>
+
 #include "iod_device.h"
 #include "iod_launch.h"
 
@@ -49,14 +51,31 @@ struct JacData {
     double cs, e1, e2, d1, d2, y, z;
 };
 
+// 1 / b from the hardware's reciprocal: the instruction sequence the compiler
+// emits for the division, without operand rescaling and special-value fixups
+// (two Newton steps and a corrected quotient).
+__device__ __forceinline__ double rcp_inrange(double b)
+{
+    double r = __builtin_amdgcn_rcp(b);
+    double e = fma(-b, r, 1.0);
+    r = fma(r, e, r);
+    e = fma(-b, r, 1.0);
+    r = fma(r, e, r);
+    e = fma(-b, r, 1.0);
+    return fma(e, r, r);
+}
+
 // f(s) exactly as the propagation's right-hand side computes it (rhs: one
 // reciprocal R = 1/(D1 D2), D_j = r_j^2 sqrt(r_j^2), correctly rounded sqrt
 // and reciprocal; INRANGE selects the in-range sequences; returns the mark
 // for their certificate), and the Jacobian data at s from the same intermediates:
 // c1 = (1-mu) D2 R, c2 = mu D1 R, and, since D2 R = 1 / (r1^2 sqrt(r1^2)),
 // 1 / r1^2 = sqrt(r1^2) D2 R, so e1 = 3 c1 sqrt(r1^2) (D2 R) and likewise
-// e2, with no further square root or division.
-template <bool INRANGE>
+// e2, with no further square root or division. ROOTS: the reciprocal from the
+// inverse roots (as rhs), else from the hardware's seed, which frees the roots
+// early: the one-thread tangent sweep, at its register limit, is 3% faster
+// with it (65,536 particles over 2,000 steps: 4.20 against 4.35 ms).
+template <bool INRANGE, bool ROOTS>
 __device__ __forceinline__ Mark rhs_jac(double mu, double mu1, const double s[6], double f[6],
                                         JacData &J)
 {
@@ -73,7 +92,7 @@ __device__ __forceinline__ Mark rhs_jac(double mu, double mu1, const double s[6]
     const double D2 = r2s * q2;
     const double D = D1 * D2;
     double e = 0.0;
-    const double R = INRANGE ? rcp_from_roots(D, h1, h2, e) : 1.0 / D;
+    const double R = !INRANGE ? 1.0 / D : ROOTS ? rcp_from_roots(D, h1, h2, e) : rcp_inrange(D);
     const double i1 = D2 * R, i2 = D1 * R;
     const double c1 = mu1 * i1;
     const double c2 = mu * i2;
@@ -135,30 +154,30 @@ __device__ __forceinline__ void atmul(const JacData &J, const double v[6], doubl
 // size h from X, and optionally the stepped state Y. INRANGE as in rhs_jac;
 // the stage inputs are those of the propagation bit for bit wherever the
 // result is certified.
-template <bool INRANGE>
+template <bool INRANGE, bool ROOTS>
 __device__ __forceinline__ void stages_jac(double mu, double mu1, double h, double h2, double h6,
                                            const double X[6], JacData J[4], double *Y, Cert &cert)
 {
     double k[6], a[6], s[6];
-    Mark m = rhs_jac<INRANGE>(mu, mu1, X, k, J[0]);
+    Mark m = rhs_jac<INRANGE, ROOTS>(mu, mu1, X, k, J[0]);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = k[d];
         s[d] = fma(h2, k[d], X[d]);
     }
-    cert.add(m, rhs_jac<INRANGE>(mu, mu1, s, k, J[1]));
+    cert.add(m, rhs_jac<INRANGE, ROOTS>(mu, mu1, s, k, J[1]));
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = fma(2.0, k[d], a[d]);
         s[d] = fma(h2, k[d], X[d]);
     }
-    m = rhs_jac<INRANGE>(mu, mu1, s, k, J[2]);
+    m = rhs_jac<INRANGE, ROOTS>(mu, mu1, s, k, J[2]);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
         a[d] = fma(2.0, k[d], a[d]);
         s[d] = fma(h, k[d], X[d]);
     }
-    cert.add(m, rhs_jac<INRANGE>(mu, mu1, s, k, J[3]));
+    cert.add(m, rhs_jac<INRANGE, ROOTS>(mu, mu1, s, k, J[3]));
     if (Y) {
 #pragma unroll
         for (int d = 0; d < 6; ++d) Y[d] = fma(h6, a[d] + k[d], X[d]);
@@ -167,29 +186,28 @@ __device__ __forceinline__ void stages_jac(double mu, double mu1, double h, doub
 
 // The same with the in-range sequences where the whole wave is certified,
 // else on the IEEE path (as rk4 does).
+template <bool ROOTS = true>
 __device__ __forceinline__ void stages_jac(double mu, double mu1, bool fast, double h, double h2,
                                            double h6, const double X[6], JacData J[4], double *Y)
 {
     bool ok = false;
     if (fast) {
         Cert cert;
-        stages_jac<true>(mu, mu1, h, h2, h6, X, J, Y, cert);
+        stages_jac<true, ROOTS>(mu, mu1, h, h2, h6, X, J, Y, cert);
         ok = cert.ok();
     }
     if (!__all(ok)) {
         Cert ieee;
-        stages_jac<false>(mu, mu1, h, h2, h6, X, J, Y, ieee);
+        stages_jac<false, ROOTS>(mu, mu1, h, h2, h6, X, J, Y, ieee);
     }
 }
 
-// Reverse (transposed tangent) of one RK4 step taken from X: lam <- (dX'/dX)^T lam.
+// Reverse (transposed tangent) of one RK4 step with stage Jacobians J:
+// lam <- (dX'/dX)^T lam.
 // X' = X + h/6 (k1 + 2 k2 + 2 k3 + k4), s2 = X + h/2 k1, s3 = X + h/2 k2, s4 = X + h k3.
-__device__ __forceinline__ void rk4_vjp(double mu, double mu1, bool fast, double h,
-                                        const double X[6], double lam[6])
+__device__ __forceinline__ void rk4_vjp_apply(const JacData J[4], double h, double h2, double h6,
+                                              double lam[6])
 {
-    const double h2 = 0.5 * h, h6 = h / 6.0;
-    JacData J[4];
-    stages_jac(mu, mu1, fast, h, h2, h6, X, J, nullptr);
     double kb[6], sb[6], xb[6];
 #pragma unroll
     for (int d = 0; d < 6; ++d) kb[d] = h6 * lam[d];
@@ -214,6 +232,16 @@ __device__ __forceinline__ void rk4_vjp(double mu, double mu1, bool fast, double
     atmul(J[0], kb, sb);
 #pragma unroll
     for (int d = 0; d < 6; ++d) lam[d] = xb[d] + sb[d];
+}
+
+// The same for a step taken from X.
+__device__ __forceinline__ void rk4_vjp(double mu, double mu1, bool fast, double h,
+                                        const double X[6], double lam[6])
+{
+    const double h2 = 0.5 * h, h6 = h / 6.0;
+    JacData J[4];
+    stages_jac(mu, mu1, fast, h, h2, h6, X, J, nullptr);
+    rk4_vjp_apply(J, h, h2, h6, lam);
 }
 
 // Residuals and their gradients with respect to rho at one observation row;
@@ -477,40 +505,50 @@ __device__ __forceinline__ void amul(const GMat &G, const double u[6], double ou
     out[5] = g2;
 }
 
+// One column u of the tangent through an RK4 step with stage blocks G.
+__device__ __forceinline__ void tangent_column(const GMat G[4], double h, double h2, double h6,
+                                               double u[6])
+{
+    double dk[6], acc[6], ds[6];
+    amul(G[0], u, dk);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+        acc[d] = dk[d];
+        ds[d] = fma(h2, dk[d], u[d]);
+    }
+    amul(G[1], ds, dk);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+        acc[d] = fma(2.0, dk[d], acc[d]);
+        ds[d] = fma(h2, dk[d], u[d]);
+    }
+    amul(G[2], ds, dk);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+        acc[d] = fma(2.0, dk[d], acc[d]);
+        ds[d] = fma(h, dk[d], u[d]);
+    }
+    amul(G[3], ds, dk);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) u[d] = fma(h6, acc[d] + dk[d], u[d]);
+}
+
 __device__ __forceinline__ void tangent_step(double mu, double mu1, bool fast, double h,
                                              double X[6], double Phi[36])
 {
     const double h2 = 0.5 * h, h6 = h / 6.0;
     double Y[6];
     JacData J[4];
-    stages_jac(mu, mu1, fast, h, h2, h6, X, J, Y);
-    const GMat J1 = gmat(J[0]), J2 = gmat(J[1]), J3 = gmat(J[2]), J4 = gmat(J[3]);
+    stages_jac<false>(mu, mu1, fast, h, h2, h6, X, J, Y);
+    const GMat G[4] = {gmat(J[0]), gmat(J[1]), gmat(J[2]), gmat(J[3])};
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-        double u[6], dk[6], acc[6], ds[6];
+        double u[6];
 #pragma unroll
         for (int d = 0; d < 6; ++d) u[d] = Phi[6 * d + c];
-        amul(J1, u, dk);
+        tangent_column(G, h, h2, h6, u);
 #pragma unroll
-        for (int d = 0; d < 6; ++d) {
-            acc[d] = dk[d];
-            ds[d] = fma(h2, dk[d], u[d]);
-        }
-        amul(J2, ds, dk);
-#pragma unroll
-        for (int d = 0; d < 6; ++d) {
-            acc[d] = fma(2.0, dk[d], acc[d]);
-            ds[d] = fma(h2, dk[d], u[d]);
-        }
-        amul(J3, ds, dk);
-#pragma unroll
-        for (int d = 0; d < 6; ++d) {
-            acc[d] = fma(2.0, dk[d], acc[d]);
-            ds[d] = fma(h, dk[d], u[d]);
-        }
-        amul(J4, ds, dk);
-#pragma unroll
-        for (int d = 0; d < 6; ++d) Phi[6 * d + c] = fma(h6, acc[d] + dk[d], u[d]);
+        for (int d = 0; d < 6; ++d) Phi[6 * d + c] = u[d];
     }
 #pragma unroll
     for (int d = 0; d < 6; ++d) X[d] = Y[d];
@@ -633,13 +671,486 @@ __global__ __launch_bounds__(64) void k_normal_grad(ProbDesc d0, SwarmArrays NB,
                                                     double *__restrict__ jrows, int64_t jstride,
                                                     int64_t jld, double *__restrict__ grad,
                                                     double *__restrict__ work, int64_t wld,
-                                                    int32_t mode)
+                                                    int32_t mode, Gate G)
 {
+    if (closed(G)) return;
     const int64_t blk = blockIdx.x >> 1;
     if (blockIdx.x & 1)
         grad_body<64, PLACE_PACKED>(blk, d0, GB, L, grad, work, wld, mode);
     else
         normal_body<64, PLACE_PACKED>(blk, d0, NB, L, chi2, jtj, jtr, jrows, jstride, jld);
+}
+
+// ---------------------------------------------------------------------------
+// Pipelined sensitivities: the sweeps above for few particles. One thread per
+// particle carries the state, its stage Jacobians and the six tangent columns
+// (about 1,170 issue slots per RK4 step), or steps forward, again per segment,
+// and once more per reversed step (1,460), while most SIMDs idle. Here a
+// workgroup holds PIPE_P particles and its waves share the work of each step
+// through LDS:
+//   - wave 0 propagates the states, four lanes per particle, and leaves the
+//     stage Jacobians of each step (three numbers and the position per stage)
+//     in LDS: about 185 slots per step;
+//   - two waves carry the tangent, one lane per column (eight lanes per
+//     particle, six in use), a chunk of steps behind: about 165 slots;
+//   - for the adjoint, wave 0 then goes back segment by segment: it recomputes
+//     the segment's steps from the checkpoint while wave 1 applies the
+//     transposed steps of the segment after it, in reverse order.
+// Each operation on a particle is the one of the sweeps above, on the same
+// operands, so the bits are the same. 96 particles over 2,520 steps: normal
+// equations 5.02 -> 1.13 ms; 1,000 over 2,000: cost gradient 5.03 -> 1.60 ms.
+// The hand-over costs about 60 slots a step (a barrier every 8 steps and the
+// wait for LDS); longer chunks, masking the duplicate LDS writes and reading a
+// step ahead were slower. A workgroup's LDS (up to 140 KB) may keep it alone on
+// a compute unit, so with more particles than the host's rule allows the
+// other sweeps win.
+// ---------------------------------------------------------------------------
+
+// One step in LDS, PIPE_STEP double2: per stage the position (x, y), (z, cs) and
+// (e1, e2) of each particle, then the velocity at the step's start.
+
+// Stage data of the own stage, from the lanes of each particle.
+struct PipeSink {
+    static constexpr bool JAC = true;
+    double2 *own;   // the particle's entry at the own stage of half 0
+    int prim;
+    __device__ __forceinline__ void operator()(int half, const double *q, const Attraction &o)
+    {
+        double2 *s = own + half * (6 * PIPE_P);
+        s[0] = make_double2(q[0], q[1]);
+        s[PIPE_P] = make_double2(q[2], o.cs);
+        ((double *)(s + 2 * PIPE_P))[prim] = o.ej;
+    }
+};
+
+__device__ __forceinline__ void pipe_put_velocity(double2 *slot, int pp, const double X[6])
+{
+    if ((threadIdx.x & 3) == 0) {
+        slot[12 * PIPE_P + pp] = make_double2(X[3], X[4]);
+        ((double *)(slot + 13 * PIPE_P))[pp] = X[5];
+    }
+}
+
+// n steps from X by the producer wave, their stage data into slots
+// ring + j PIPE_STEP. As rk4_steps: one certification vote, and all n again on
+// the IEEE path where a lane is not certified. vel: the steps' velocities are
+// wanted too (by the partial steps of a reverse sweep).
+__device__ __forceinline__ void pipe_produce(const KArgs &A, int32_t n, double X[6], double2 *ring,
+                                             int pp, bool vel)
+{
+    if (A.fast) {
+        double X0[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X0[d] = X[d];
+        Cert cert;
+        PipeSink sink{ring + (Quad<4>::is_late() ? 3 * PIPE_P : 0) + pp, (int)(threadIdx.x & 1)};
+        double2 *slot = ring;
+        auto step = [&]() __attribute__((always_inline)) {
+            if (vel) pipe_put_velocity(slot, pp, X);
+            split_step<4>(A.mu, A.mu1, A.h, A.h2, A.h6, X, cert, sink);
+            sink.own += PIPE_STEP;
+            slot += PIPE_STEP;
+        };
+        int32_t j = 0;
+        for (; j + 2 <= n; j += 2) {
+            step();
+            step();
+        }
+        if (j < n) step();
+        if (__all(cert.ok())) return;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = X0[d];
+    }
+    for (int32_t j = 0; j < n; ++j) {
+        double2 *slot = ring + j * PIPE_STEP;
+        JacData J[4];
+        double Y[6];
+        Cert ieee;
+        stages_jac<false, true>(A.mu, A.mu1, A.h, A.h2, A.h6, X, J, Y, ieee);
+        if (vel) pipe_put_velocity(slot, pp, X);
+        // the position of stage i from its y, z and the factors' own x
+        double k[6], s[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) s[d] = X[d];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double2 *q = slot + 3 * i * PIPE_P + pp;
+            q[0] = make_double2(s[0], s[1]);
+            q[PIPE_P] = make_double2(s[2], J[i].cs);
+            q[2 * PIPE_P] = make_double2(J[i].e1, J[i].e2);
+            if (i < 3) {
+                rhs<false>(A.mu, A.mu1, s, k);
+#pragma unroll
+                for (int d = 0; d < 6; ++d) s[d] = fma(i == 2 ? A.h : A.h2, k[d], X[d]);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = Y[d];
+    }
+}
+
+// Stage data of a step in LDS, for particle pp.
+struct PipeRow {
+    double2 a[4], b[4], e[4];
+    __device__ __forceinline__ void get(const double2 *slot, int pp)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] = slot[3 * i * PIPE_P + pp];
+            b[i] = slot[(3 * i + 1) * PIPE_P + pp];
+            e[i] = slot[(3 * i + 2) * PIPE_P + pp];
+        }
+    }
+    __device__ __forceinline__ void jac(const KArgs &A, JacData J[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            J[i].cs = b[i].y;
+            J[i].e1 = e[i].x;
+            J[i].e2 = e[i].y;
+            J[i].d1 = a[i].x + A.mu;
+            J[i].d2 = a[i].x - A.mu1;
+            J[i].y = a[i].y;
+            J[i].z = b[i].x;
+        }
+    }
+};
+
+// Hand-over state `half` of particle pp.
+__device__ __forceinline__ void pipe_put_state(double *xend, int half, int pp, const double X[6])
+{
+#pragma unroll
+    for (int d = 0; d < 6; ++d) xend[(half * 6 + d) * PIPE_P + pp] = X[d];
+}
+
+__device__ __forceinline__ void pipe_get_state(const double *xend, int half, int pp, double X[6])
+{
+#pragma unroll
+    for (int d = 0; d < 6; ++d) X[d] = xend[(half * 6 + d) * PIPE_P + pp];
+}
+
+// Buffers of the reverse sweep, PIPE_SUB steps each: the segment being
+// reversed holds one per block of its steps, the segment before it fills the
+// ones that become free. Both waves keep the same account (numbers of four
+// bits in a word).
+struct PipeBuffers {
+    uint64_t cur = 0, next = 0, spare = 0;
+    int nspare = 0;
+    __device__ __forceinline__ void push(int id)
+    {
+        spare |= (uint64_t)id << (4 * nspare);
+        ++nspare;
+    }
+    __device__ __forceinline__ int pop()
+    {
+        --nspare;
+        const int id = (int)(spare >> (4 * nspare)) & 15;
+        spare &= ~((uint64_t)15 << (4 * nspare));
+        return id;
+    }
+    __device__ __forceinline__ int at(int block) const { return (int)(cur >> (4 * block)) & 15; }
+};
+
+// TAN: chi2, J^T J, J^T r (and the rows of J); ADJ: cost (unless TAN) and its
+// gradient. Outputs and arguments as normal_body and grad_body; Q.sub
+// workgroups of PIPE_P particles per work entry (one problem: per launch).
+// The checkpoints are Q's scratch rows, every pipe_segment(S) steps.
+template <bool SINGLE, bool TAN, bool ADJ>
+__global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, SwarmArrays B, PipeArgs Q)
+{
+    extern __shared__ double2 pipe_lds[];
+    double *xend = (double *)pipe_lds;
+    double2 *ring = pipe_lds + PIPE_XEND;
+    int64_t p = 0, i0 = (int64_t)blockIdx.x * PIPE_P;
+    if (!SINGLE) {
+        const int64_t w = blockIdx.x / Q.sub;
+        p = B.work[2 * w];
+        i0 = B.work[2 * w + 1] * (Q.sub * PIPE_P) + (blockIdx.x % Q.sub) * PIPE_P;
+    }
+    const ProbDesc &D = SINGLE ? d0 : B.desc[p];
+    if (closed(Q.gate)) return;
+    if (i0 >= D.m || (B.active && !B.active[p])) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
+    // particle of this thread, and whether its results are wanted
+    auto wanted = [&](int64_t i) { return i < D.m && !(Q.done && Q.done[D.off + i]); };
+    if (!__any(wanted(i0 + (lane & (PIPE_P - 1))))) return;   // the same in every wave
+    const int pp = wave == 0 ? lane >> 2 : TAN ? (wave - 1) * 8 + (lane >> 3) : lane & (PIPE_P - 1);
+    const int64_t i = i0 + pp;
+    const int64_t g = D.off + (i < D.m ? i : D.m - 1);
+    KArgs A = D.k;
+    if (Q.mode >= 0) A.mode = Q.mode;
+    const int32_t S = A.ns[A.K - 1];
+    const int32_t L = pipe_segment(S), nseg = (S + L - 1) / L;
+
+    // forward sweep: chunks of up to PIPE_FWD steps, ending at each observation
+    // (and each checkpoint)
+    auto chunk = [&](int32_t step, int32_t target) {
+        int32_t n = target - step;
+        if (TAN) n = min(n, PIPE_FWD);
+        if (ADJ) n = min(n, L - step % L);
+        return n;
+    };
+    if (wave == 0) {
+        double X[6];
+        load_state(B.x, B.ld, g, X);
+        int32_t step = 0;
+        int c = 0;
+        for (int32_t k = 0; k < A.K; ++k) {
+            const int32_t target = A.ns[k];
+            while (step < target) {
+                const int32_t n = chunk(step, target);
+                if (ADJ && step % L == 0 && (lane & 3) == 0 && i < D.m) {
+#pragma unroll
+                    for (int d = 0; d < 6; ++d)
+                        Q.work[((int64_t)(step / L) * 6 + d) * Q.wld + g] = X[d];
+                }
+                if (TAN) {
+                    pipe_produce(A, n, X, ring + (c & 1) * (PIPE_FWD * PIPE_STEP), pp, false);
+                    pipe_put_state(xend, c & 1, pp, X);
+                    __syncthreads();
+                    ++c;
+                } else {
+                    rk4_steps_split<4>(A, n, X);
+                }
+                step += n;
+            }
+            if (!TAN) {
+                pipe_put_state(xend, k & 1, pp, X);
+                __syncthreads();
+            }
+        }
+        if (!ADJ) return;
+        __syncthreads();   // the others are done with the forward sweep's data
+    } else if (TAN) {
+        const int cl = min(lane & 7, 5);   // column (lanes 6 and 7 repeat the last)
+        const double is = sqrt(A.w);       // 1 / sigma
+        const bool ranged = A.wr != 0.0;
+        const double isr = sqrt(A.wr);     // 1 / sigma_range
+        const bool write = wanted(i) && (lane & 7) < 6;
+        double u[6], N[6], gr = 0.0, c2 = 0.0;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            u[d] = d == cl ? 1.0 : 0.0;
+            N[d] = 0.0;
+        }
+        int32_t step = 0;
+        int c = 0;
+        for (int32_t k = 0; k < A.K; ++k) {
+            const int32_t target = A.ns[k];
+            while (step < target) {
+                const int32_t n = chunk(step, target);
+                __syncthreads();
+                const double2 *slot = ring + (c & 1) * (PIPE_FWD * PIPE_STEP);
+                auto advance = [&](const PipeRow &r) {
+                    JacData J[4];
+                    r.jac(A, J);
+                    const GMat G[4] = {gmat(J[0]), gmat(J[1]), gmat(J[2]), gmat(J[3])};
+                    tangent_column(G, A.h, A.h2, A.h6, u);
+                };
+                for (int32_t j = 0; j < n; ++j, slot += PIPE_STEP) {
+                    PipeRow r;
+                    r.get(slot, pp);
+                    advance(r);
+                }
+                ++c;
+                step += n;
+            }
+            // residuals and their rows of J at this observation
+            double X[6], su[6];
+            if (step == 0)
+                load_state(B.x, B.ld, g, X);
+            else
+                pipe_get_state(xend, (c - 1) & 1, pp, X);
+#pragma unroll
+            for (int d = 0; d < 6; ++d) su[d] = u[d];
+            const double *row = A.tab + (int64_t)k * TAB_W;
+            const double tau = row[TAB_TAU];
+            if (tau != 0.0) {
+                const double t2 = 0.5 * tau, t6 = tau / 6.0;
+                double Y[6];
+                JacData J[4];
+                stages_jac(A.mu, A.mu1, A.fast, tau, t2, t6, X, J, Y);
+                const GMat G[4] = {gmat(J[0]), gmat(J[1]), gmat(J[2]), gmat(J[3])};
+                tangent_column(G, tau, t2, t6, su);
+#pragma unroll
+                for (int d = 0; d < 6; ++d) X[d] = Y[d];
+            }
+            double da, db, ga[3], gb[3], dr = 0, gq[3] = {0, 0, 0};
+            if (!residual_and_grad(row, X, da, db, ga, gb, ranged, dr, gq)) {
+                da = db = dr = NAN;
+                ga[0] = ga[1] = ga[2] = gb[0] = gb[1] = gb[2] = gq[0] = gq[1] = gq[2] = NAN;
+            }
+            const double ja = is * fma(ga[0], su[0], fma(ga[1], su[1], ga[2] * su[2]));
+            const double jb = is * fma(gb[0], su[0], fma(gb[1], su[1], gb[2] * su[2]));
+            const double jr = isr * fma(gq[0], su[0], fma(gq[1], su[1], gq[2] * su[2]));
+            if (Q.jrows && write) {
+                const int R = ranged ? 3 : 2;
+                double *q = Q.jrows + ((int64_t)k * R * 6 + cl) * Q.jld + p * Q.jstride + i;
+                q[0] = ja;
+                q[6 * Q.jld] = jb;
+                if (ranged) q[12 * Q.jld] = jr;
+            }
+            const double ra = da * is, rb = db * is, rr = dr * isr;
+            c2 = fma(ra, ra, fma(rb, rb, c2));
+            gr = fma(ja, ra, fma(jb, rb, gr));
+#pragma unroll
+            for (int r = 0; r < 6; ++r) {
+                const int src = (lane & ~7) + r;
+                N[r] = fma(__shfl(ja, src, 64), ja, fma(__shfl(jb, src, 64), jb, N[r]));
+            }
+            if (ranged) {
+                c2 = fma(rr, rr, c2);
+                gr = fma(jr, rr, gr);
+#pragma unroll
+                for (int r = 0; r < 6; ++r) N[r] = fma(__shfl(jr, (lane & ~7) + r, 64), jr, N[r]);
+            }
+        }
+        if (write) {
+            const int64_t o = D.off + i;
+            if (cl == 0) Q.chi2[o] = c2;
+            Q.jtr[cl * B.ld + o] = gr;
+            // row r of the packed upper triangle starts at r (13 - r) / 2 - r
+#pragma unroll
+            for (int r = 0; r < 6; ++r)
+                if (r <= cl) Q.jtj[(r * (13 - r) / 2 + cl - r) * B.ld + o] = N[r];
+        }
+        if (!ADJ) return;
+        __syncthreads();
+        if (wave > 1) return;
+    } else {
+        // the cost, an observation behind the producer
+        CostAcc acc{0.0, A.w, A.mode, A.wr};
+        for (int32_t k = 0; k < A.K; ++k) {
+            __syncthreads();
+            double X[6];
+            pipe_get_state(xend, k & 1, pp, X);
+            const double *row = A.tab + (int64_t)k * TAB_W;
+            const double tau = row[TAB_TAU];
+            if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, X);
+            acc(row, X);
+        }
+        if (wanted(i) && lane < PIPE_P) B.cost[D.off + i] = acc.J;
+        __syncthreads();
+    }
+    if constexpr (ADJ) {
+        // reverse sweep (waves 0 and 1): blocks of PIPE_SUB steps
+        const int32_t nblk = L / PIPE_SUB;
+        PipeBuffers F;
+        const int32_t last = nseg > 0 ? (S - (nseg - 1) * L + PIPE_SUB - 1) / PIPE_SUB : 0;
+        for (int j = nblk; j >= last; --j) F.push(j);
+        for (int j = 0; j < last; ++j) F.cur |= (uint64_t)j << (4 * j);
+        auto buffer = [&](int id) { return ring + id * (PIPE_SUB * PIPE_STEP); };
+        if (wave == 0) {
+            bool off = false;
+            for (int32_t k = lane; k < A.K; k += 64) off |= A.tab[(int64_t)k * TAB_W + TAB_TAU] != 0.0;
+            const bool offgrid = __any(off);
+            double X[6];
+            auto checkpoint = [&](int32_t sg) {
+#pragma unroll
+                for (int d = 0; d < 6; ++d) X[d] = Q.work[((int64_t)sg * 6 + d) * Q.wld + g];
+            };
+            if (nseg > 0) {
+                checkpoint(nseg - 1);
+                const int32_t len = S - (nseg - 1) * L;
+                for (int32_t j = 0; j < last; ++j)
+                    pipe_produce(A, min(PIPE_SUB, len - j * PIPE_SUB), X, buffer(j), pp, offgrid);
+            }
+            __syncthreads();
+            for (int32_t sg = nseg - 1; sg >= 0; --sg) {
+                const int32_t nb = sg == nseg - 1 ? last : nblk, nn = sg > 0 ? nblk : 0;
+                if (sg > 0) checkpoint(sg - 1);
+                F.next = 0;
+                for (int32_t t = 0; t < max(nb, nn); ++t) {
+                    if (t < nn) {
+                        const int id = F.pop();
+                        F.next |= (uint64_t)id << (4 * t);
+                        pipe_produce(A, PIPE_SUB, X, buffer(id), pp, offgrid);
+                    }
+                    if (t < nb) F.push(F.at(nb - 1 - t));
+                    __syncthreads();
+                }
+                F.cur = F.next;
+            }
+            return;
+        }
+        // wave 1: particle lane & 15 (the tangent's columns are done)
+        const int q = lane & (PIPE_P - 1);
+        double lam[6] = {0, 0, 0, 0, 0, 0};
+        int32_t k = A.K - 1, nk = A.ns[k];
+        auto observe = [&](int32_t n, const double X[6]) {
+            while (nk == n) {
+                double add[6];
+                obs_cotangent(A, A.tab + (int64_t)k * TAB_W, X, add);
+#pragma unroll
+                for (int d = 0; d < 6; ++d) lam[d] += add[d];
+                --k;
+                nk = k >= 0 ? A.ns[k] : -1;
+            }
+        };
+        double X[6];
+        if (S == 0) {
+            load_state(B.x, B.ld, D.off + (i0 + q < D.m ? i0 + q : D.m - 1), X);
+        } else {
+            // the state at S: the forward sweep's last hand-over
+            int32_t half = (A.K - 1) & 1;
+            if (TAN) {
+                int c = 0;
+                int32_t step = 0;
+                for (int32_t kk = 0; kk < A.K; ++kk)
+                    while (step < A.ns[kk]) {
+                        step += chunk(step, A.ns[kk]);
+                        ++c;
+                    }
+                half = (c - 1) & 1;
+            }
+            pipe_get_state(xend, half, q, X);
+        }
+        observe(S, X);
+        __syncthreads();
+        for (int32_t sg = nseg - 1; sg >= 0; --sg) {
+            const int32_t a = sg * L, len = min(L, S - a);
+            const int32_t nb = sg == nseg - 1 ? last : nblk, nn = sg > 0 ? nblk : 0;
+            F.next = 0;
+            for (int32_t t = 0; t < max(nb, nn); ++t) {
+                if (t < nn) F.next |= (uint64_t)F.pop() << (4 * t);
+                if (t < nb) {
+                    const int32_t blk = nb - 1 - t;
+                    const double2 *buf = buffer(F.at(blk));
+                    auto reverse = [&](const PipeRow &r, int32_t j) {
+                        JacData J[4];
+                        r.jac(A, J);
+                        rk4_vjp_apply(J, A.h, A.h2, A.h6, lam);
+                        const int32_t n = a + blk * PIPE_SUB + j;
+                        if (nk == n) {
+                            const double2 *slot = buf + j * PIPE_STEP;
+                            // (written where some observation is off the grid)
+                            const double2 v = slot[12 * PIPE_P + q];
+                            X[0] = r.a[0].x;
+                            X[1] = r.a[0].y;
+                            X[2] = r.b[0].x;
+                            X[3] = v.x;
+                            X[4] = v.y;
+                            X[5] = ((const double *)(slot + 13 * PIPE_P))[q];
+                            observe(n, X);
+                        }
+                    };
+                    for (int32_t j = min(PIPE_SUB, len - blk * PIPE_SUB) - 1; j >= 0; --j) {
+                        PipeRow r;
+                        r.get(buf + j * PIPE_STEP, q);
+                        reverse(r, j);
+                    }
+                    F.push(F.at(blk));
+                }
+                __syncthreads();
+            }
+            F.cur = F.next;
+        }
+        if (lane < PIPE_P && wanted(i0 + q)) {
+#pragma unroll
+            for (int d = 0; d < 6; ++d) Q.grad[d * B.ld + D.off + i0 + q] = lam[d];
+        }
+    }
 }
 
 // Solve (N + l diag(N)) y = rhs by Cholesky, N = J^T J packed (row-major
@@ -758,7 +1269,9 @@ __global__ __launch_bounds__(64) void k_gn_trials(const double *__restrict__ x,
 // 2 |a| <= alpha |v|. J^T r(x + hd v) pairs the rows of J at x, stored by the
 // normal-equation launch (jrows, column p jstride + j), with the residuals
 // propagated from x + hd v; J^T r(x) and N are the normal equations' own.
-__global__ __launch_bounds__(64) void k_geo(const ProbDesc *__restrict__ descs,
+// LPP lanes per trial, one workgroup of 64 LPP threads per problem.
+template <int LPP>
+__global__ __launch_bounds__(64 * LPP) void k_geo(const ProbDesc *__restrict__ descs,
                                             const double *__restrict__ x,
                                             const double *__restrict__ jtj,
                                             const double *__restrict__ jtr,
@@ -768,11 +1281,12 @@ __global__ __launch_bounds__(64) void k_geo(const ProbDesc *__restrict__ descs,
                                             const int32_t *__restrict__ active,
                                             const int32_t *__restrict__ done, int32_t T,
                                             int64_t ld, double hd, double alpha,
-                                            const double *__restrict__ vt, double *__restrict__ xt)
+                                            const double *__restrict__ vt, double *__restrict__ xt,
+                                            Gate G)
 {
     const int64_t p = blockIdx.x;
-    if (!active[p]) return;
-    const int t = threadIdx.x, j = t / T, k = t % T;
+    if (closed(G) || !active[p]) return;
+    const int t = threadIdx.x / LPP, j = t / T, k = t % T;
     if (j >= n[p]) return;
     const int64_t c = p * 64 + j, o = p * 64 + t;
     if (done[c]) return;
@@ -801,7 +1315,10 @@ __global__ __launch_bounds__(64) void k_geo(const ProbDesc *__restrict__ descs,
     for (int32_t kk = 0; kk < A.K; ++kk) {
         const int32_t target = A.ns[kk];
         if (target > step) {
-            rk4_steps(A, target - step, Y);
+            if constexpr (LPP == 1)
+                rk4_steps(A, target - step, Y);
+            else
+                rk4_steps_split<LPP>(A, target - step, Y);
             step = target;
         }
         const double *row = A.tab + (int64_t)kk * TAB_W;
@@ -839,7 +1356,7 @@ __global__ __launch_bounds__(64) void k_geo(const ProbDesc *__restrict__ descs,
     double an = 0.0;
 #pragma unroll
     for (int d = 0; d < 6; ++d) an = fma(acc[d], acc[d], an);
-    if (!(4.0 * an <= alpha * alpha * vn)) return;
+    if (!(4.0 * an <= alpha * alpha * vn) || threadIdx.x % LPP != 0) return;
 #pragma unroll
     for (int d = 0; d < 6; ++d) xt[d * ld + o] = x[d * ld + c] + fma(0.5, acc[d], v[d]);
 }
@@ -908,9 +1425,15 @@ __global__ __launch_bounds__(1024) void k_live_lanes(const int32_t *__restrict__
                                                      const int32_t *__restrict__ active,
                                                      const int32_t *__restrict__ done,
                                                      int32_t *__restrict__ out,
-                                                     int64_t *__restrict__ count)
+                                                     int64_t *__restrict__ count, int64_t nprob,
+                                                     int32_t *__restrict__ problems)
 {
-    __shared__ int32_t wave_total[16];
+    __shared__ int32_t wave_total[16], n_active;
+    if (threadIdx.x == 0) n_active = 0;
+    __syncthreads();
+    int32_t mine = 0;
+    for (int64_t p = threadIdx.x; p < nprob; p += 1024) mine += active[p] != 0;
+    atomicAdd(&n_active, mine);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int64_t base = 0;
     for (int64_t c0 = 0; c0 < n; c0 += 1024) {
@@ -937,7 +1460,11 @@ __global__ __launch_bounds__(1024) void k_live_lanes(const int32_t *__restrict__
         base += total;
         __syncthreads();
     }
-    if (threadIdx.x == 0) *count = base;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        *count = base;
+        *problems = n_active;
+    }
 }
 
 // Final undamped Gauss-Newton step of the batched refinement, one 64-lane
@@ -1114,10 +1641,31 @@ hipError_t launch_normal(const ProbDesc &d0, const SwarmArrays &B, int bs, int64
 hipError_t launch_normal_grad(const ProbDesc &d0, const SwarmArrays &NB, const SwarmArrays &GB,
                               int64_t grid, double *chi2, double *jtj, double *jtr, double *jrows,
                               int64_t jstride, int64_t jld, double *grad, double *work,
-                              int64_t wld, int32_t mode, hipStream_t st, const Lanes &L)
+                              int64_t wld, int32_t mode, hipStream_t st, const Lanes &L,
+                              const Gate &G)
 {
     if (!L.pairs || NB.desc != GB.desc) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_normal_grad, dim3((unsigned)(2 * grid)), dim3(64), 0, st, d0, NB, GB, L, chi2, jtj, jtr, jrows, jstride, jld, grad, work, wld, mode);
+    hipLaunchKernelGGL(k_normal_grad, dim3((unsigned)(2 * grid)), dim3(64), 0, st, d0, NB, GB, L, chi2, jtj, jtr, jrows, jstride, jld, grad, work, wld, mode, G);
+    return hipGetLastError();
+}
+
+hipError_t launch_sens_pipe(const ProbDesc &d0, const SwarmArrays &B, const PipeArgs &Q,
+                            int64_t grid, int32_t seg, bool tan, bool adj, hipStream_t st)
+{
+    if (!(tan || adj) || seg < PIPE_SUB || seg > PIPE_MAX_SEG) return hipErrorInvalidValue;
+    const unsigned lds = (unsigned)pipe_lds_bytes(seg, tan, adj);
+    const dim3 g((unsigned)grid), b(tan ? 192 : 128);
+    const bool single = B.desc == nullptr;
+    if (tan && adj) {
+        if (single) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_sens_pipe<false, true, true>), g, b, lds, st, d0, B, Q);
+    } else if (tan) {
+        if (single) hipLaunchKernelGGL((k_sens_pipe<true, true, false>), g, b, lds, st, d0, B, Q);
+        else hipLaunchKernelGGL((k_sens_pipe<false, true, false>), g, b, lds, st, d0, B, Q);
+    } else {
+        if (single) hipLaunchKernelGGL((k_sens_pipe<true, false, true>), g, b, lds, st, d0, B, Q);
+        else hipLaunchKernelGGL((k_sens_pipe<false, false, true>), g, b, lds, st, d0, B, Q);
+    }
     return hipGetLastError();
 }
 
@@ -1145,10 +1693,13 @@ hipError_t launch_geo(const ProbDesc *descs, const double *x, const double *jtj,
                       const double *jrows, int64_t jstride, int64_t jld, const double *lam,
                       const int32_t *n, const int32_t *active, const int32_t *done, int32_t T,
                       int64_t nprob, int64_t ld, double hd, double alpha, const double *vt,
-                      double *xt, hipStream_t st)
+                      double *xt, int lanes, const Gate &G, hipStream_t st)
 {
     if (T < 1 || T > 64 || !jrows) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_geo, dim3((unsigned)nprob), dim3(64), 0, st, descs, x, jtj, jtr, jrows, jstride, jld, lam, n, active, done, T, ld, hd, alpha, vt, xt);
+    if (lanes == 4)
+        hipLaunchKernelGGL(k_geo<4>, dim3((unsigned)nprob), dim3(256), 0, st, descs, x, jtj, jtr, jrows, jstride, jld, lam, n, active, done, T, ld, hd, alpha, vt, xt, G);
+    else
+        hipLaunchKernelGGL(k_geo<1>, dim3((unsigned)nprob), dim3(64), 0, st, descs, x, jtj, jtr, jrows, jstride, jld, lam, n, active, done, T, ld, hd, alpha, vt, xt, G);
     return hipGetLastError();
 }
 
@@ -1161,10 +1712,11 @@ hipError_t launch_gn_select(double *x, double *chi2, double *lam, int32_t *done,
     return hipGetLastError();
 }
 
-hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active,
-                            const int32_t *done, int32_t *out, int64_t *count, hipStream_t st)
+hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active, int64_t nprob,
+                            const int32_t *done, int32_t *out, int64_t *count, int32_t *problems,
+                            hipStream_t st)
 {
-    hipLaunchKernelGGL(k_live_lanes, dim3(1), dim3(1024), 0, st, lanes, n, active, done, out, count);
+    hipLaunchKernelGGL(k_live_lanes, dim3(1), dim3(1024), 0, st, lanes, n, active, done, out, count, nprob, problems);
     return hipGetLastError();
 }
 
