@@ -622,7 +622,7 @@ int check_batch(iod_batch *b)
 }
 
 // Build the chief data of the FP32 propagation (once per handle or batch):
-// allocate the three tables, then one thread per problem propagates its
+// allocate the three tables, then one wave per problem propagates its
 // chief in FP64 and fills them. Synchronous.
 int build_chief_tables(const std::vector<ProbDesc> &descs)
 {

@@ -35,8 +35,8 @@ hipError_t launch_swarm_iter(const ProbDesc &d0, const SwarmArrays &B, int bs, i
                              int64_t n, hipStream_t st, int waves = 0);
 hipError_t launch_swarm_final(const ProbDesc &d0, const SwarmArrays &B, int64_t n, hipStream_t st);
 
-// Chief data of the FP32 propagation for each problem (one thread each):
-// fills the cst, cpt and cobs tables that descs[p].k points to.
+// Chief data of the FP32 propagation for each problem (one wave each): fills
+// the cst, cpt and cobs tables that descs[p].k points to.
 hipError_t launch_chief_stages(const ProbDesc *descs, int64_t nprob, hipStream_t st);
 // Mixed precision (FP32 ranking, FP64 global best); batched launches only.
 // rel: the offset-from-the-chief formulation (the problems' chief tables

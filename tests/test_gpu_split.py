@@ -73,3 +73,27 @@ def test_swarm_of_split_particles_in_a_batch(m):
     gs, Js, hists = iod.iod_batch_solve(b, [p] * n, np.full(n, m), 3)
     assert all(np.array_equal(gs[q], g) and Js[q] == J and np.array_equal(hists[q], hist)
                for q in range(n))
+
+
+@pytest.mark.parametrize("steps", [1, 15, 16, 17, 32, 50])
+@pytest.mark.parametrize("tau", [0.0, 0.0003])
+def test_chief_tables_of_the_offset_formulation(steps, tau):
+    """The chief's own state has offset zero, so its FP32 propagation returns
+    the chief states of the tables: the FP64 ones, bit for bit. A particle near
+    it, which reads every stage row, stays within the offset formulation's
+    rounding (2^-24 of an offset of 1e-3 per step, times the growth of a
+    deviation over so short an arc, below 2)."""
+    import torch
+    wl = W.tiny(5)
+    t = np.unique([1e-3, max(1, steps // 2) * 1e-3 + tau, steps * 1e-3 + tau])
+    h = iod.iod_create(wl.mu, wl.chief, t, np.zeros((len(t), 2)), 1e-5, h=1e-3)
+    x = torch.zeros((6, 64), dtype=torch.float64, device="cuda")
+    x[:] = torch.from_numpy(wl.chief).cuda()[:, None]
+    x[:, 1] += 1e-3
+    a, b = (torch.zeros((len(t), 6, 64), dtype=torch.float64, device="cuda") for _ in range(2))
+    iod.iod_propagate(h, x, 2, a)
+    iod.iod_propagate_f32(h, x, 2, b)
+    torch.cuda.synchronize()
+    a, b = a.cpu().numpy(), b.cpu().numpy()
+    assert np.array_equal(a[:, :, 0], b[:, :, 0])
+    assert np.max(np.abs(a[:, :, 1] - b[:, :, 1])) <= 2 * steps * 2.0 ** -24 * 1e-3
