@@ -561,8 +561,9 @@ struct iod_handle {
 
 // Buffers of the batched refinement stage, kept across calls.
 struct PolishBuffers {
-    DevCache cand, x, chi, work, best, bchi, cost, act, done, vt, jrows, live, live_count;
-    DevTable desc, edesc, tdesc, list, lanes, nn;
+    DevCache cand, x, chi, work, best, bchi, cost, act, done, jrows, live, live_count,
+        order, stored;
+    DevTable desc, edesc, list, lanes, nn;
 };
 
 struct iod_batch {
@@ -1602,6 +1603,8 @@ int64_t adj_rows(const HostProblem &P)
 // Doubles of polish workspace per column besides the adjoint rows:
 // jtj 21, jtr 6, grad 6, trial 6, chi2 at trial 1, damping 1, cost 1.
 constexpr int64_t POLISH_COLS = 42;
+// Most scratch for which the trials' checkpoints are the closest.
+constexpr int64_t POLISH_CKPT_BYTES = (int64_t)2 << 30;
 
 // The problems of a sensitivity launch, and which of its sweeps are pipelined.
 // The pipelined form shortens a step about four times (normal equations) or
@@ -1655,6 +1658,7 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
     double *x = B.x;
     PipeArgs Q;
     Q.sub = plan.sub;
+    Q.seg = plan.seg;
     Q.mode = 1;
     Q.chi2 = chi2;
     Q.jtj = jtj;
@@ -1663,7 +1667,7 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
     Q.work = adj;
     Q.wld = ld;
     auto normal = [&]() {
-        return plan.tan ? launch_sens_pipe(d0, B, Q, plan.grid, plan.seg, true, false, st)
+        return plan.tan ? launch_sens_pipe(d0, B, Q, plan.grid, true, st)
                         : launch_normal(d0, B, bs, grid, chi2, jtj, jtr, st);
     };
     HIP_TRY(launch_fill_cols(d0, B, bs, grid, lam, 1e-3, st));
@@ -1671,7 +1675,7 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
         B.x = x;
         HIP_TRY(normal());
         B.cost = cost;
-        HIP_TRY(plan.adj ? launch_sens_pipe(d0, B, Q, plan.grid, plan.seg, false, true, st)
+        HIP_TRY(plan.adj ? launch_sens_pipe(d0, B, Q, plan.grid, false, st)
                          : launch_grad(d0, B, bs, grid, g, adj, ld, 1, st));
         HIP_TRY(launch_gn_solve(d0, B, bs, grid, jtj, g, 0.5, lam, xt, st));
         B.x = xt;
@@ -1688,25 +1692,26 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
 }
 
 // The batched refinement loop: each iteration forms the normal equations and
-// the adjoint gradient of every live candidate (packed: lanes lists the
-// (problem, candidate) pairs, several problems to a wave), tries T dampings
-// per candidate side by side (one wave per problem, in the lanes that the
-// candidates leave free), adds the geodesic correction, keeps the best
-// trial, and retires problems whose candidates have all stopped moving. PB
-// holds the candidate columns (p * 64 + j, j < n[p]); tdesc the trial
-// descriptors (n[p] * T columns); jrows the candidates' rows of J.
+// the adjoint gradient of every live candidate, tries T dampings per candidate
+// side by side (one wave per problem, in the lanes that the candidates leave
+// free) with the geodesic correction, keeps the best trial, and retires
+// problems whose candidates have all stopped moving. PB holds the candidate
+// columns (p * 64 + j, j < n[p]); jrows the candidates' rows of J; order [P][2]
+// and stored [columns] are scratch. The adjoint rows of work hold the
+// checkpoints of the trials, a column each: a trial's evaluation leaves its
+// states there, so that the next iteration's gradient needs no forward sweep
+// and runs beside the normal equations.
 constexpr double POLISH_STEP_TOL = 1e-12;
 
 constexpr double GN_FINAL_MAX_STEP = 1e-6;  // largest component of a final undamped step
 constexpr double GEO_HD = 0.1;      // finite-difference step along v, as a fraction of v
 constexpr double GEO_ALPHA = 0.75;  // accept the correction a if 2 |a| <= alpha |v|
 
-int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
-                      const int32_t *n, int64_t P, int32_t T, int32_t n_iter, double *chi2,
-                      double *work, double *vt, double *jrows, int32_t n_cand, int32_t *active,
-                      int32_t *done, const int32_t *lanes, int64_t nlanes, int32_t *live,
-                      int64_t *live_count, int64_t ld, const PipePlan &plan, int simds,
-                      hipStream_t st)
+int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const int32_t *n, int64_t P, int32_t T,
+                      int32_t n_iter, double *chi2, double *work, double *jrows, int32_t n_cand,
+                      int32_t *active, int32_t *done, const int32_t *lanes, int64_t nlanes,
+                      int32_t *live, int64_t *live_count, int32_t *order, int32_t *stored,
+                      int64_t ld, const PipePlan &plan, int simds, hipStream_t st)
 {
     const int64_t jld = P * n_cand;
     double *jtj = work;
@@ -1720,25 +1725,20 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     double *x = PB.x;
     PB.active = active;
     HIP_TRY(launch_fill_cols(d0, PB, 64, P, lam, 1e-3, st));
-    SwarmArrays TB = PB;
-    TB.desc = tdesc;
-    TB.x = xt;
-    TB.cost = chi2t;
-    // While few problems are active, the pipelined sweeps and several lanes
-    // per trial shorten the launches, which then last as long as one wave;
-    // with many, the forms that fill every lane win. The number of active
-    // problems is on the device, so both forms are launched with complementary
-    // gates (the one whose turn it is not exits at once) unless even all
-    // problems are few. Tried lanes: one workgroup of four waves per problem.
+    // While few problems are active, the pipelined sweeps shorten a launch,
+    // which then lasts as long as one wave; with many, the forms that fill
+    // every lane win. The number of active problems is on the device, so both
+    // forms are launched with complementary gates (the one whose turn it is not
+    // exits at once) unless even all problems are few.
     int32_t *problems = (int32_t *)(live_count + 1);
     const int32_t sub = plan.sub;
     const bool pipe = plan.steps <= PIPE_MAX_STEPS;
-    Gate few, many, split, whole;
-    few.count = many.count = split.count = whole.count = problems;
+    Gate few, many;
+    few.count = many.count = problems;
     few.upto = many.above = pipe ? (int32_t)(plan.adj_limit(simds, true) / sub) : 0;
-    split.upto = whole.above = simds / 4;
     PipeArgs Q;
     Q.sub = sub;
+    Q.seg = plan.seg;
     Q.mode = 1;
     Q.done = done;
     Q.gate = few;
@@ -1751,16 +1751,40 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     Q.grad = g;
     Q.work = adj;
     Q.wld = ld;
-    ProbDesc dsplit = d0;   // only its lane count is read by a batch's launch
-    dsplit.lanes = 4;
-    // the normal equations and the gradient see only the candidates: packed,
-    // several problems' candidates to a wave, problems with the most RK4
-    // steps first. Each iteration they take only the live pairs (problem
-    // active, candidate not done), compacted in that order after the select
-    // step, so retired pairs leave the waves; the grid stays that of all
-    // pairs and the waves past the live count exit at once. Both sweeps go
-    // in one launch, so that the tangent and the adjoint sweep of the last
-    // live pairs run at the same time.
+    Q.stored = stored;
+    TrialArgs R;
+    R.descs = PB.desc;
+    R.work = order;
+    R.count = problems;
+    R.simds = simds;
+    R.T = T;
+    R.ld = ld;
+    R.x = x;
+    R.jtj = jtj;
+    R.jtr = jtr;
+    R.grad = g;
+    R.lam = lam;
+    R.jrows = jrows;
+    R.jstride = n_cand;
+    R.jld = jld;
+    R.done = done;
+    R.hd = GEO_HD;
+    R.alpha = GEO_ALPHA;
+    R.xt = xt;
+    R.chi2t = chi2t;
+    R.ckpt = pipe ? adj : nullptr;
+    R.seg = plan.seg;
+    R.stored = stored;
+    // the packed forms see only the candidates: several problems' candidates to
+    // a wave, problems with the most RK4 steps first. Each iteration they take
+    // only the live pairs (problem active, candidate not done), compacted in
+    // that order after the select step, so retired pairs leave the waves; the
+    // grid stays that of all pairs and the waves past the live count exit at
+    // once. Both sweeps go in one launch, so that the tangent and the adjoint
+    // sweep of the last live pairs run at the same time. The other launches
+    // take the active problems, compacted likewise (order): the workgroups of
+    // retired ones, if they came between, would leave compute units idle beside
+    // others that hold two.
     Lanes KL;
     KL.pairs = lanes;
     KL.n = nlanes;
@@ -1769,26 +1793,26 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     LL.n = nlanes;
     LL.count = live_count;
     const int64_t kgrid = (nlanes + 63) / 64;
-    HIP_TRY(launch_live_lanes(lanes, nlanes, active, P, done, live, live_count, problems, st));
+    HIP_TRY(launch_live_lanes(lanes, nlanes, active, done, live, live_count, order, problems, st));
+    if (n_iter > 0 && P <= few.upto) {
+        // the first sweeps' checkpoints
+        TrialArgs F = R;
+        F.first = true;
+        HIP_TRY(launch_gn_trials(F, P, st));
+    }
     for (int32_t it = 0; it < n_iter; ++it) {
-        SwarmArrays GB = PB;
+        SwarmArrays GB = PB, OB = PB;
         GB.cost = cost;
-        if (pipe) HIP_TRY(launch_sens_pipe(d0, PB, Q, P * sub, plan.seg, true, true, st));
+        OB.work = order;
+        if (pipe) HIP_TRY(launch_sens_stored(d0, OB, Q, std::min<int64_t>(P, few.upto) * sub, st));
         if (P > many.above)
             HIP_TRY(launch_normal_grad(d0, PB, GB, kgrid, chi2, jtj, jtr, jrows, n_cand, jld, g,
                                        adj, ld, 1, st, LL, many));
-        HIP_TRY(launch_gn_trials(x, jtj, g, lam, n, active, done, T, P, ld, xt, vt, st));
-        HIP_TRY(launch_geo(PB.desc, x, jtj, jtr, jrows, n_cand, jld, lam, n, active, done, T, P,
-                           ld, GEO_HD, GEO_ALPHA, vt, xt, 4, split, st));
-        if (P > whole.above)
-            HIP_TRY(launch_geo(PB.desc, x, jtj, jtr, jrows, n_cand, jld, lam, n, active, done, T,
-                               P, ld, GEO_HD, GEO_ALPHA, vt, xt, 1, whole, st));
-        HIP_TRY(launch_eval(dsplit, TB, 64, P, st, split));
-        if (P > whole.above) HIP_TRY(launch_eval(d0, TB, 64, P, st, whole));
+        HIP_TRY(launch_gn_trials(R, P, st));
         HIP_TRY(launch_gn_select(x, chi2, lam, done, active, xt, chi2t, n, T, P, ld,
-                                 POLISH_STEP_TOL, st));
+                                 POLISH_STEP_TOL, stored, st));
         if (it + 1 < n_iter)
-            HIP_TRY(launch_live_lanes(lanes, nlanes, active, P, done, live, live_count, problems, st));
+            HIP_TRY(launch_live_lanes(lanes, nlanes, active, done, live, live_count, order, problems, st));
     }
     if (n_iter == 0) {
         HIP_TRY(launch_normal(d0, PB, 64, P, chi2, jtj, jtr, st));
@@ -1810,7 +1834,7 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const ProbDesc *tdesc,
     F.jtr = jtr;
     for (int f = 0; f < 2; ++f) {
         if (plan.tan)
-            HIP_TRY(launch_sens_pipe(d0, AB, F, P * sub, plan.seg, true, false, st));
+            HIP_TRY(launch_sens_pipe(d0, AB, F, P * sub, true, st));
         else
             HIP_TRY(launch_normal(d0, AB, 64, kgrid, chi2, jtj, jtr, st, nullptr, 0, 0, KL));
         HIP_TRY(launch_gn_final(x, jtj, jtr, n, P, ld, GN_FINAL_MAX_STEP, st));
@@ -1826,6 +1850,20 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     const int64_t P = b->P, stride = 64, ldp = P * stride;
     int64_t rows = 0;
     for (const HostProblem &Pb : b->probs) rows = std::max(rows, adj_rows(Pb));
+    PipePlan plan;
+    plan.sub = (S.n_cand + PIPE_P - 1) / PIPE_P;
+    for (int64_t p = 0; p < P; ++p)
+        plan.add(std::min<int64_t>(S.n_cand, L.descs[p].m), b->probs[p].ns[b->probs[p].K - 1]);
+    plan.decide(b->simds);
+    if (plan.steps <= PIPE_MAX_STEPS) {
+        // Checkpoints of the trials: the shortest segments (of which two
+        // workgroups share a compute unit's LDS), or longer ones where many
+        // problems' checkpoints would take gigabytes.
+        const auto ckpt_rows = [&] { return ceil_div(plan.steps, plan.seg) + 1; };
+        for (plan.seg = PIPE_SUB; plan.seg < PIPE_MAX_SEG; plan.seg *= 2)
+            if (ckpt_rows() * 6 * ldp * (int64_t)sizeof(double) <= POLISH_CKPT_BYTES) break;
+        rows = std::max(rows, ckpt_rows());
+    }
     // trials per candidate: the free lanes of the problem's 64-lane wave, at most 8
     const int32_t T = std::max(1, std::min(8, 64 / S.n_cand));
     // rows of J of every candidate: max over problems of K R (R = 3 with ranges, else 2)
@@ -1838,12 +1876,13 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     HIP_TRY(Q.x.ensure((size_t)6 * ldp * sizeof(double)));
     HIP_TRY(Q.chi.ensure((size_t)ldp * sizeof(double)));
     HIP_TRY(Q.work.ensure((size_t)(POLISH_COLS + rows * 6) * ldp * sizeof(double)));
+    HIP_TRY(Q.order.ensure((size_t)2 * P * sizeof(int32_t)));
+    HIP_TRY(Q.stored.ensure((size_t)ldp * sizeof(int32_t)));
     HIP_TRY(Q.best.ensure((size_t)6 * P * sizeof(double)));
     HIP_TRY(Q.bchi.ensure((size_t)P * sizeof(double)));
     HIP_TRY(Q.cost.ensure((size_t)P * sizeof(double)));
     HIP_TRY(Q.act.ensure((size_t)P * sizeof(int32_t)));
     HIP_TRY(Q.done.ensure((size_t)ldp * sizeof(int32_t)));
-    HIP_TRY(Q.vt.ensure((size_t)6 * ldp * sizeof(double)));
     HIP_TRY(Q.jrows.ensure((size_t)jrow_max * 6 * P * S.n_cand * sizeof(double)));
     // candidates: each problem's global best, then its best personal bests
     // (in the mixed-precision swarm the first is decided by FP64 costs, the
@@ -1851,7 +1890,7 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     HIP_TRY(launch_topk(B, B.jp, S.n_cand, Q.cand.as<int32_t>(), st));
     HIP_TRY(launch_gather(B, Q.cand.as<const int32_t>(), S.n_cand, final_recs, Q.x.as<double>(),
                           ldp, stride, st));
-    std::vector<ProbDesc> pd(L.descs), ed(L.descs), td(L.descs);
+    std::vector<ProbDesc> pd(L.descs), ed(L.descs);
     std::vector<int32_t> list(2 * P), n(P);
     for (int64_t p = 0; p < P; ++p) {
         ProbDesc &D = pd[p];
@@ -1863,9 +1902,7 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
         D.hist = nullptr;
         D.hist_len = 0;
         D.k.mode = IOD_COST_CHI2;
-        td[p] = D;
-        td[p].m = D.m * T;
-        if (td[p].m > stride) return fail(IOD_EINVAL, "trial columns exceed the stride");
+        if (D.m * T > stride) return fail(IOD_EINVAL, "trial columns exceed the stride");
         ed[p] = D;
         ed[p].k.mode = L.descs[p].k.mode;
         ed[p].m = 1;
@@ -1878,7 +1915,6 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     HIP_TRY(Q.edesc.upload(ed, st));
     HIP_TRY(Q.list.upload(list, st));
     HIP_TRY(Q.nn.upload(n, st));
-    HIP_TRY(Q.tdesc.upload(td, st));
     // packed lanes: (problem, candidate), problems with the most RK4 steps first
     std::vector<int32_t> by_steps(P);
     std::iota(by_steps.begin(), by_steps.end(), 0);
@@ -1893,10 +1929,6 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
             lanes.push_back(j);
         }
     const int64_t nlanes = (int64_t)lanes.size() / 2;
-    PipePlan plan;
-    plan.sub = (S.n_cand + PIPE_P - 1) / PIPE_P;
-    for (int64_t p = 0; p < P; ++p) plan.add(n[p], b->probs[p].ns[b->probs[p].K - 1]);
-    plan.decide(b->simds);
     HIP_TRY(Q.lanes.upload(lanes, st));
     HIP_TRY(Q.live.ensure(std::max<size_t>(lanes.size(), 2) * sizeof(int32_t)));
     HIP_TRY(Q.live_count.ensure(2 * sizeof(int64_t)));   // live pairs, active problems
@@ -1910,12 +1942,12 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     PB.x = Q.x.as<double>();
     PB.ld = ldp;
     PB.nprob = P;
-    int rc = polish_trials_run(pd[0], PB, Q.tdesc.as<const ProbDesc>(), Q.nn.as<const int32_t>(), P,
-                               T, S.n_gn, Q.chi.as<double>(), Q.work.as<double>(),
-                               Q.vt.as<double>(), Q.jrows.as<double>(), S.n_cand,
-                               Q.act.as<int32_t>(), Q.done.as<int32_t>(),
+    int rc = polish_trials_run(pd[0], PB, Q.nn.as<const int32_t>(), P, T, S.n_gn,
+                               Q.chi.as<double>(), Q.work.as<double>(), Q.jrows.as<double>(),
+                               S.n_cand, Q.act.as<int32_t>(), Q.done.as<int32_t>(),
                                Q.lanes.as<const int32_t>(), nlanes, Q.live.as<int32_t>(),
-                               Q.live_count.as<int64_t>(), ldp, plan, b->simds, st);
+                               Q.live_count.as<int64_t>(), Q.order.as<int32_t>(),
+                               Q.stored.as<int32_t>(), ldp, plan, b->simds, st);
     if (rc != IOD_OK) return rc;
     HIP_TRY(launch_pick_best(Q.x.as<const double>(), Q.chi.as<const double>(),
                              Q.nn.as<const int32_t>(), P, ldp, stride, Q.best.as<double>(),
@@ -1973,10 +2005,11 @@ int single_grad(const iod_handle *h, const ProbDesc &D, const SwarmArrays &B, in
 {
     const PipePlan plan = single_plan(h, D.m);
     PipeArgs Q;
+    Q.seg = plan.seg;
     Q.grad = grad;
     Q.work = work;
     Q.wld = ld;
-    HIP_TRY(plan.adj ? launch_sens_pipe(D, B, Q, plan.grid, plan.seg, false, true, st)
+    HIP_TRY(plan.adj ? launch_sens_pipe(D, B, Q, plan.grid, false, st)
                      : launch_grad(D, B, bs, D.nslots, grad, work, ld, -1, st));
     return IOD_OK;
 }
@@ -2119,7 +2152,7 @@ int iod_normal_eq(iod_handle *h, const double *x, int64_t ld, int64_t m, double 
     Q.chi2 = chi2;
     Q.jtj = jtj;
     Q.jtr = jtr;
-    HIP_TRY(plan.tan ? launch_sens_pipe(D, B, Q, plan.grid, plan.seg, true, false, (hipStream_t)stream)
+    HIP_TRY(plan.tan ? launch_sens_pipe(D, B, Q, plan.grid, true, (hipStream_t)stream)
                      : launch_normal(D, B, bs, D.nslots, chi2, jtj, jtr, (hipStream_t)stream));
     return IOD_OK;
 }

@@ -151,6 +151,7 @@ inline int64_t pipe_lds_bytes(int32_t seg, bool tan, bool adj)
 
 struct PipeArgs {
     int32_t sub = 1;                 // workgroups per work entry (a batch)
+    int32_t seg = PIPE_SUB;          // steps between checkpoints
     int32_t mode = -1;               // >= 0 overrides the cost mode
     const int32_t *done = nullptr;   // [columns]: results not wanted, or null
     Gate gate;
@@ -158,6 +159,28 @@ struct PipeArgs {
     int64_t jstride = 0, jld = 0;
     double *grad = nullptr, *work = nullptr;
     int64_t wld = 0;
+    // launch_sens_stored: [columns] whose checkpoints are the column's (< 0: skipped)
+    const int32_t *stored = nullptr;
+};
+
+// The refinement's trials (launch_gn_trials).
+struct TrialArgs {
+    const ProbDesc *descs = nullptr;   // the candidates'
+    const int32_t *work = nullptr;     // active problems, [*count][2]
+    const int32_t *count = nullptr;
+    int simds = 0;
+    bool first = false;                // the candidates themselves: only chi2t and ckpt, and stored
+    int32_t T = 1;
+    int64_t ld = 0;
+    const double *x = nullptr, *jtj = nullptr, *jtr = nullptr, *grad = nullptr, *lam = nullptr;
+    const double *jrows = nullptr;
+    int64_t jstride = 0, jld = 0;
+    const int32_t *done = nullptr;
+    double hd = 0.0, alpha = 0.0;
+    double *xt = nullptr, *chi2t = nullptr;
+    double *ckpt = nullptr;            // [rows][6][ld], every seg steps and after the last; or null
+    int32_t seg = PIPE_SUB;            // a power of two
+    int32_t *stored = nullptr;
 };
 
 }  // namespace iodk

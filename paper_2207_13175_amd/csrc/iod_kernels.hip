@@ -205,13 +205,13 @@ __global__ __launch_bounds__(64) void k_chief(ProbDesc d0, const ProbDesc *__res
 
 // LPP lanes per particle: workgroups of BS threads hold BS / LPP particles.
 template <int BS, bool SINGLE, int LPP = 1>
-__global__ __launch_bounds__(BS) void k_eval(ProbDesc d0, SwarmArrays B, Gate G)
+__global__ __launch_bounds__(BS) void k_eval(ProbDesc d0, SwarmArrays B)
 {
     __shared__ double lds[OBS_CHUNK * TAB_W];
     __shared__ int32_t lds_ns[OBS_CHUNK];
     int64_t p, tile;
     const ProbDesc &D = locate<SINGLE>(d0, B, p, tile);
-    if (closed(G) || (B.active && !B.active[p])) return;   // whole workgroup
+    if (B.active && !B.active[p]) return;   // whole workgroup
     const int64_t i = tile * (BS / LPP) + threadIdx.x / LPP;
     const bool valid = i < D.m;
     double X[6];
@@ -438,16 +438,16 @@ hipError_t launch_chief(const ProbDesc &d0, const ProbDesc *descs, int64_t nprob
 }
 
 hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
-                       hipStream_t st, const Gate &G)
+                       hipStream_t st)
 {
     if (d0.lanes > 1) {
-        IOD_DISPATCH_SPLIT(d0.lanes, if (B.desc) hipLaunchKernelGGL((k_eval<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, G);
-                           else hipLaunchKernelGGL((k_eval<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, G));
+        IOD_DISPATCH_SPLIT(d0.lanes, if (B.desc) hipLaunchKernelGGL((k_eval<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B);
+                           else hipLaunchKernelGGL((k_eval<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B));
         return hipGetLastError();
     }
     const bool single = B.desc == nullptr;
-    IOD_DISPATCH_BS(bs, if (single) hipLaunchKernelGGL((k_eval<BS_, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B, G);
-                        else hipLaunchKernelGGL((k_eval<BS_, false>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B, G));
+    IOD_DISPATCH_BS(bs, if (single) hipLaunchKernelGGL((k_eval<BS_, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B);
+                        else hipLaunchKernelGGL((k_eval<BS_, false>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B));
     return hipGetLastError();
 }
 

@@ -26,7 +26,7 @@ hipError_t launch_chief(const ProbDesc &d0, const ProbDesc *descs, int64_t nprob
 // d0.lanes > 1 (the same for every problem of a batch) the workgroups hold
 // SPLIT_BS / lanes particles (ProbDesc::block) whatever bs and waves.
 hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
-                       hipStream_t st, const Gate &G = Gate());
+                       hipStream_t st);
 hipError_t launch_swarm_init(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                              hipStream_t st);
 // waves: 0 = the compiler's register allocation, 3 = registers capped so
@@ -78,15 +78,19 @@ hipError_t launch_normal_grad(const ProbDesc &d0, const SwarmArrays &NB, const S
                               int64_t jstride, int64_t jld, double *grad, double *work,
                               int64_t wld, int32_t mode, hipStream_t st, const Lanes &L,
                               const Gate &G);
-// The pipelined form of the two for few particles (same results): tan, the
-// normal equations into Q.chi2, jtj, jtr (and jrows); adj, the gradient into
-// Q.grad with scratch Q.work [rows][6][Q.wld], and, without tan, the cost into
-// B.cost. Both together: batches only. One workgroup per PIPE_P particles: grid =
-// ceil(m / PIPE_P) for a single problem, work entries * Q.sub for a batch.
-// seg: the largest pipe_segment of its problems (none of more than
-// PIPE_MAX_STEPS steps).
+// The pipelined form of each for few particles (same results): tan, the normal
+// equations into Q.chi2, jtj, jtr (and jrows); else the cost into B.cost and its
+// gradient into Q.grad with scratch Q.work [rows][6][Q.wld]. One workgroup per
+// PIPE_P particles: grid = ceil(m / PIPE_P) for a single problem, work entries *
+// Q.sub for a batch. Q.seg: the steps between the gradient's checkpoints (a
+// multiple of PIPE_SUB), no problem with more than PIPE_MAX_STEPS steps.
 hipError_t launch_sens_pipe(const ProbDesc &d0, const SwarmArrays &B, const PipeArgs &Q,
-                            int64_t grid, int32_t seg, bool tan, bool adj, hipStream_t st);
+                            int64_t grid, bool tan, hipStream_t st);
+// Both of a batch's candidates in one launch, from the checkpoints in Q.work
+// that launch_gn_trials left in the columns Q.stored names (candidates with a
+// negative one are skipped).
+hipError_t launch_sens_stored(const ProbDesc &d0, const SwarmArrays &B, const PipeArgs &Q,
+                              int64_t grid, hipStream_t st);
 // Per-column Gauss-Newton step (on B.x) and acceptance, over B's layout.
 hipError_t launch_gn_solve(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                            const double *jtj, const double *g, double gscale, const double *lam,
@@ -96,32 +100,19 @@ hipError_t launch_gn_accept(const ProbDesc &d0, const SwarmArrays &B, int bs, in
                             hipStream_t st);
 hipError_t launch_fill_cols(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                             double *out, double value, hipStream_t st);
-// Multi-trial damped Gauss-Newton of the batched refinement stage: one
-// 64-lane workgroup per problem p, candidate j < n[p] in column p * 64 + j,
-// its T trials (n[p] * T <= 64) in columns p * 64 + j * T + k with damping
-// lam * 10^(k - T / 2). Problems with active[p] == 0 are skipped; the select
-// step clears active[p] once none of the problem's candidates moves by more
-// than step_tol (or all sit at the damping cap).
-hipError_t launch_gn_trials(const double *x, const double *jtj, const double *g, const double *lam,
-                            const int32_t *n, const int32_t *active, const int32_t *done,
-                            int32_t T, int64_t nprob, int64_t ld, double *xt, double *vt,
-                            hipStream_t st);
-// Geodesic acceleration of the trials (vt the steps, xt the trial states,
-// updated in place where the correction is accepted); descs the candidates'
-// problem descriptors, jtj / jtr the normal equations at the candidates and
-// jrows their rows of J (launch_normal's layout, candidate j of problem p in
-// column p jstride + j). lanes: adjacent lanes per trial, 1 or 4.
-hipError_t launch_geo(const ProbDesc *descs, const double *x, const double *jtj, const double *jtr,
-                      const double *jrows, int64_t jstride, int64_t jld, const double *lam,
-                      const int32_t *n, const int32_t *active, const int32_t *done, int32_t T,
-                      int64_t nprob, int64_t ld, double hd, double alpha, const double *vt,
-                      double *xt, int lanes, const Gate &G, hipStream_t st);
-// The pairs of lanes [n][2] whose problem is active and candidate not done,
-// in order, into out [n][2]; their number into *count and that of the active
-// ones of the nprob problems into *problems (device).
-hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active, int64_t nprob,
-                            const int32_t *done, int32_t *out, int64_t *count, int32_t *problems,
-                            hipStream_t st);
+// Multi-trial damped Gauss-Newton of the batched refinement stage: candidate
+// j < n[p] of problem p in column p * 64 + j, its T trials (n[p] * T <= 64) in
+// columns p * 64 + j * T + k with damping lam * 10^(k - T / 2). Problems with
+// active[p] == 0 are skipped; the select step clears active[p] once none of the
+// problem's candidates moves by more than step_tol (or all sit at the damping
+// cap). nprob: the entries of Q.work.
+hipError_t launch_gn_trials(const TrialArgs &Q, int64_t nprob, hipStream_t st);
+// The pairs of lanes [n][2] whose problem is active and candidate not done, in
+// order, into out [n][2], and the active problems, as work entries (p, 0), into
+// work; their numbers into *count and *problems (device).
+hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active,
+                            const int32_t *done, int32_t *out, int64_t *count, int32_t *work,
+                            int32_t *problems, hipStream_t st);
 // Undamped Gauss-Newton step of each candidate (column p * 64 + j, j < n[p])
 // from the normal equations jtj, jtr at x, applied in place where no
 // component exceeds max_step.
@@ -129,7 +120,8 @@ hipError_t launch_gn_final(double *x, const double *jtj, const double *jtr, cons
                           int64_t nprob, int64_t ld, double max_step, hipStream_t st);
 hipError_t launch_gn_select(double *x, double *chi2, double *lam, int32_t *done, int32_t *active,
                             const double *xt, const double *chi2t, const int32_t *n, int32_t T,
-                            int64_t nprob, int64_t ld, double step_tol, hipStream_t st);
+                            int64_t nprob, int64_t ld, double step_tol, int32_t *stored,
+                            hipStream_t st);
 // Candidates of the refinement (stride <= 64, top_k <= stride): rec null,
 // the personal bests cand[p][j]; else the global best rec[p] first, then the
 // personal bests in rank order without its duplicate, top_k columns in all.

@@ -851,37 +851,47 @@ struct PipeBuffers {
     __device__ __forceinline__ int at(int block) const { return (int)(cur >> (4 * block)) & 15; }
 };
 
-// TAN: chi2, J^T J, J^T r (and the rows of J); ADJ: cost (unless TAN) and its
-// gradient. Outputs and arguments as normal_body and grad_body; Q.sub
-// workgroups of PIPE_P particles per work entry (one problem: per launch).
-// The checkpoints are Q's scratch rows, every pipe_segment(S) steps.
-template <bool SINGLE, bool TAN, bool ADJ>
-__global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, SwarmArrays B, PipeArgs Q)
+// TAN: chi2, J^T J, J^T r (and the rows of J); ADJ: the cost and its gradient;
+// either, not both. Outputs and arguments as normal_body and grad_body; Q.sub
+// workgroups (block of them: this one) of PIPE_P particles per work entry (one
+// problem: per launch). The checkpoints are Q's scratch rows, every Q.seg
+// steps; STORED: they are there already (with the state at the last step after
+// them), and only the gradient is formed, with no forward sweep.
+template <bool SINGLE, bool TAN, bool ADJ, bool STORED = false>
+__device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, const SwarmArrays &B,
+                                          const PipeArgs &Q)
 {
+    static_assert(TAN != ADJ && (ADJ || !STORED), "one sweep");
     extern __shared__ double2 pipe_lds[];
     double *xend = (double *)pipe_lds;
     double2 *ring = pipe_lds + PIPE_XEND;
-    int64_t p = 0, i0 = (int64_t)blockIdx.x * PIPE_P;
+    // with a gate, B.work lists the active problems
+    if (closed(Q.gate) || (Q.gate.count && block >= (int64_t)*Q.gate.count * Q.sub)) return;
+    int64_t p = 0, i0 = block * PIPE_P;
     if (!SINGLE) {
-        const int64_t w = blockIdx.x / Q.sub;
+        const int64_t w = block / Q.sub;
         p = B.work[2 * w];
-        i0 = B.work[2 * w + 1] * (Q.sub * PIPE_P) + (blockIdx.x % Q.sub) * PIPE_P;
+        i0 = B.work[2 * w + 1] * (Q.sub * PIPE_P) + (block % Q.sub) * PIPE_P;
     }
     const ProbDesc &D = SINGLE ? d0 : B.desc[p];
-    if (closed(Q.gate)) return;
     if (i0 >= D.m || (B.active && !B.active[p])) return;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
     // particle of this thread, and whether its results are wanted
-    auto wanted = [&](int64_t i) { return i < D.m && !(Q.done && Q.done[D.off + i]); };
+    auto wanted = [&](int64_t i) {
+        return i < D.m && !(Q.done && Q.done[D.off + i]) && !(Q.stored && Q.stored[D.off + i] < 0);
+    };
     if (!__any(wanted(i0 + (lane & (PIPE_P - 1))))) return;   // the same in every wave
+    if (wave > (TAN ? 2 : 1)) return;
     const int pp = wave == 0 ? lane >> 2 : TAN ? (wave - 1) * 8 + (lane >> 3) : lane & (PIPE_P - 1);
     const int64_t i = i0 + pp;
     const int64_t g = D.off + (i < D.m ? i : D.m - 1);
+    // column of its checkpoints
+    const int64_t cg = STORED && Q.stored[g] >= 0 ? (int64_t)Q.stored[g] : g;
     KArgs A = D.k;
     if (Q.mode >= 0) A.mode = Q.mode;
     const int32_t S = A.ns[A.K - 1];
-    const int32_t L = pipe_segment(S), nseg = (S + L - 1) / L;
+    const int32_t L = Q.seg, nseg = (S + L - 1) / L;
 
     // forward sweep: chunks of up to PIPE_FWD steps, ending at each observation
     // (and each checkpoint)
@@ -891,7 +901,9 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
         if (ADJ) n = min(n, L - step % L);
         return n;
     };
-    if (wave == 0) {
+    if constexpr (STORED) {
+        // no forward sweep
+    } else if (wave == 0) {
         double X[6];
         load_state(B.x, B.ld, g, X);
         int32_t step = 0;
@@ -1015,9 +1027,7 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
             for (int r = 0; r < 6; ++r)
                 if (r <= cl) Q.jtj[(r * (13 - r) / 2 + cl - r) * B.ld + o] = N[r];
         }
-        if (!ADJ) return;
-        __syncthreads();
-        if (wave > 1) return;
+        return;
     } else {
         // the cost, an observation behind the producer
         CostAcc acc{0.0, A.w, A.mode, A.wr};
@@ -1048,7 +1058,7 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
             double X[6];
             auto checkpoint = [&](int32_t sg) {
 #pragma unroll
-                for (int d = 0; d < 6; ++d) X[d] = Q.work[((int64_t)sg * 6 + d) * Q.wld + g];
+                for (int d = 0; d < 6; ++d) X[d] = Q.work[((int64_t)sg * 6 + d) * Q.wld + cg];
             };
             if (nseg > 0) {
                 checkpoint(nseg - 1);
@@ -1074,8 +1084,8 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
             }
             return;
         }
-        // wave 1: particle lane & 15 (the tangent's columns are done)
-        const int q = lane & (PIPE_P - 1);
+        // wave 1
+        const int q = pp;
         double lam[6] = {0, 0, 0, 0, 0, 0};
         int32_t k = A.K - 1, nk = A.ns[k];
         auto observe = [&](int32_t n, const double X[6]) {
@@ -1091,20 +1101,12 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
         double X[6];
         if (S == 0) {
             load_state(B.x, B.ld, D.off + (i0 + q < D.m ? i0 + q : D.m - 1), X);
+        } else if (STORED) {
+#pragma unroll
+            for (int d = 0; d < 6; ++d) X[d] = Q.work[((int64_t)nseg * 6 + d) * Q.wld + cg];
         } else {
             // the state at S: the forward sweep's last hand-over
-            int32_t half = (A.K - 1) & 1;
-            if (TAN) {
-                int c = 0;
-                int32_t step = 0;
-                for (int32_t kk = 0; kk < A.K; ++kk)
-                    while (step < A.ns[kk]) {
-                        step += chunk(step, A.ns[kk]);
-                        ++c;
-                    }
-                half = (c - 1) & 1;
-            }
-            pipe_get_state(xend, half, q, X);
+            pipe_get_state(xend, (A.K - 1) & 1, q, X);
         }
         observe(S, X);
         __syncthreads();
@@ -1151,6 +1153,26 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
             for (int d = 0; d < 6; ++d) Q.grad[d * B.ld + D.off + i0 + q] = lam[d];
         }
     }
+}
+
+template <bool SINGLE, bool TAN, bool ADJ>
+__global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, SwarmArrays B, PipeArgs Q)
+{
+    pipe_body<SINGLE, TAN, ADJ>(blockIdx.x, d0, B, Q);
+}
+
+// Both sweeps of the refinement, from the checkpoints that the evaluation of
+// its trials left: the normal equations in even workgroups and, at the same
+// time, the gradient in odd ones, so that a launch of few problems lasts as
+// long as one sweep: one workgroup that went forward and then back took 2.13 ms
+// over 2,500 steps, this takes 1.09. With more, two workgroups share a compute
+// unit's LDS (segments of 8 steps): 384 problems 4.23 -> 2.42 ms.
+__global__ __launch_bounds__(192) void k_sens_stored(ProbDesc d0, SwarmArrays B, PipeArgs Q)
+{
+    if (blockIdx.x & 1)
+        pipe_body<false, false, true, true>(blockIdx.x >> 1, d0, B, Q);
+    else
+        pipe_body<false, true, false>(blockIdx.x >> 1, d0, B, Q);
 }
 
 // Solve (N + l diag(N)) y = rhs by Cholesky, N = J^T J packed (row-major
@@ -1233,132 +1255,230 @@ __device__ __forceinline__ double pow10i(int e)
     return e < 0 ? 1.0 / f : f;
 }
 
-// Trials of the batched refinement stage (one 64-lane workgroup per problem):
-// lane t of problem p is trial k = t % T of candidate j = t / T, damping
-// lam[j] 10^(k - T/2). A finished candidate (done) repeats its state.
-__global__ __launch_bounds__(64) void k_gn_trials(const double *__restrict__ x,
-                                                  const double *__restrict__ jtj,
-                                                  const double *__restrict__ g,
-                                                  const double *__restrict__ lam,
-                                                  const int32_t *__restrict__ n,
-                                                  const int32_t *__restrict__ active,
-                                                  const int32_t *__restrict__ done, int32_t T,
-                                                  int64_t ld, double *__restrict__ xt,
-                                                  double *__restrict__ vt)
+// n steps of every lane's state from step `from` of the grid, as rk4_steps; hook
+// sees the state before every multiple of L steps, a power of two (again where
+// the steps are repeated on the IEEE path).
+template <int LPP, class Hook>
+__device__ __forceinline__ void trial_steps(const KArgs &A, int32_t from, int32_t n, int32_t L,
+                                            double X[6], Hook hook)
 {
-    const int64_t p = blockIdx.x;
-    if (!active[p]) return;
-    const int t = threadIdx.x, j = t / T, k = t % T;
-    if (j >= n[p]) return;
-    const int64_t c = p * 64 + j, o = p * 64 + t;
-    double r[6] = {0, 0, 0, 0, 0, 0};
-    bool ok = false;
-    if (!done[c]) ok = damped_step(jtj, g, ld, c, 0.5, lam[c] * pow10i(k - T / 2), r);
-    for (int d = 0; d < 6; ++d) {
-        vt[d * ld + o] = ok ? r[d] : 0.0;
-        xt[d * ld + o] = x[d * ld + c] + (ok ? r[d] : 0.0);
+    const int32_t end = from + n;
+    auto run = [&](auto step) __attribute__((always_inline)) {
+        for (int32_t s = from; s < end;) {
+            const int32_t at = s & (L - 1), m = min(end - s, L - at);
+            if (at == 0) hook(s >> __builtin_ctz(L), X);
+            int32_t j = 0;
+            for (; j + 4 <= m; j += 4) {
+                step();
+                step();
+                step();
+                step();
+            }
+            for (; j < m; ++j) step();
+            s += m;
+        }
+    };
+    if (A.fast) {
+        double X0[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X0[d] = X[d];
+        Cert cert;
+        run([&]() __attribute__((always_inline)) {
+            if constexpr (LPP == 1) {
+                double a[6];
+                rk4_sum<true>(A.mu, A.mu1, A.h, A.h2, X, a, cert);
+#pragma unroll
+                for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
+            } else {
+                NoSink none;
+                split_step<LPP>(A.mu, A.mu1, A.h, A.h2, A.h6, X, cert, none);
+            }
+        });
+        if (__all(cert.ok())) return;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = X0[d];
+    }
+    for (int32_t s = from; s < end; ++s) {
+        if ((s & (L - 1)) == 0) hook(s >> __builtin_ctz(L), X);
+        double a[6];
+        Cert ieee;
+        rk4_sum<false>(A.mu, A.mu1, A.h, A.h2, X, a, ieee);
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
     }
 }
 
-// Geodesic acceleration of the trial steps (Transtrum and Sethna, 2012,
-// "Improvements to the Levenberg-Marquardt algorithm for nonlinear
-// least-squares minimization"), a second-order correction along the step v:
-// with the directional second derivative of the residuals
+// Walk the observation schedule of a wave's trials, the table staged in LDS:
+// steps(from, n, X), then obs(k, row, S) with the state at observation k.
+template <class Steps, class Obs>
+__device__ __forceinline__ void trial_walk(const KArgs &A, double X[6], double *lds,
+                                           int32_t *lds_ns, Steps steps, Obs obs)
+{
+    int32_t step = 0;
+    for (int32_t k0 = 0; k0 < A.K; k0 += OBS_CHUNK) {
+        const int32_t nk = min(OBS_CHUNK, A.K - k0);
+        WaveScope::sync();
+        for (int32_t j = WaveScope::rank(); j < nk * TAB_W; j += 64)
+            lds[j] = A.tab[(int64_t)k0 * TAB_W + j];
+        for (int32_t j = WaveScope::rank(); j < nk; j += 64) lds_ns[j] = A.ns[k0 + j];
+        WaveScope::sync();
+        for (int32_t kk = 0; kk < nk; ++kk) {
+            const double *row = lds + kk * TAB_W;
+            const int32_t target = __builtin_amdgcn_readfirstlane(lds_ns[kk]);
+            steps(k0 + kk, step, target - step, X);
+            step = target;
+            double S[6];
+#pragma unroll
+            for (int d = 0; d < 6; ++d) S[d] = X[d];
+            const double tau = row[TAB_TAU];
+            if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
+            obs(k0 + kk, row, S);
+        }
+    }
+}
+
+// One trial wave of the batched refinement stage: trial t = lane / LPP of this
+// wave's share of problem p's trials is k = t % T of candidate j = t / T, its
+// damping lam[j] 10^(k - T/2). Its step v, corrected by geodesic acceleration
+// (Transtrum and Sethna, 2012, "Improvements to the Levenberg-Marquardt
+// algorithm for nonlinear least-squares minimization"): with the directional
+// second derivative of the residuals
 // r_vv ~ (2 / hd) ((r(x + hd v) - r(x)) / hd - J v), the correction solves
 // (N + l diag N) a = -J^T r_vv, and the trial becomes x + v + a / 2 when
 // 2 |a| <= alpha |v|. J^T r(x + hd v) pairs the rows of J at x, stored by the
-// normal-equation launch (jrows, column p jstride + j), with the residuals
-// propagated from x + hd v; J^T r(x) and N are the normal equations' own.
-// LPP lanes per trial, one workgroup of 64 LPP threads per problem.
+// normal equations' launch (jrows, column p jstride + j), with the residuals
+// propagated from x + hd v; J^T r(x) and N are the normal equations' own. Then
+// the trial's chi2, leaving the states every Q.seg steps and after the last
+// one for the sweeps of the next iteration. A finished candidate (done)
+// repeats its state.
 template <int LPP>
-__global__ __launch_bounds__(64 * LPP) void k_geo(const ProbDesc *__restrict__ descs,
-                                            const double *__restrict__ x,
-                                            const double *__restrict__ jtj,
-                                            const double *__restrict__ jtr,
-                                            const double *__restrict__ jrows, int64_t jstride,
-                                            int64_t jld, const double *__restrict__ lam,
-                                            const int32_t *__restrict__ n,
-                                            const int32_t *__restrict__ active,
-                                            const int32_t *__restrict__ done, int32_t T,
-                                            int64_t ld, double hd, double alpha,
-                                            const double *__restrict__ vt, double *__restrict__ xt,
-                                            Gate G)
+__device__ __forceinline__ void trial_wave(const TrialArgs &Q, int64_t p, int part, double *lds,
+                                           int32_t *lds_ns)
 {
-    const int64_t p = blockIdx.x;
-    if (closed(G) || !active[p]) return;
-    const int t = threadIdx.x / LPP, j = t / T, k = t % T;
-    if (j >= n[p]) return;
-    const int64_t c = p * 64 + j, o = p * 64 + t;
-    if (done[c]) return;
-    double v[6], vn = 0.0;
+    const ProbDesc &D = Q.descs[p];
+    const KArgs &A = D.k;
+    const int lane = (int)(threadIdx.x & 63), T = Q.first ? 1 : Q.T, nt = (int)D.m * T;
+    const int t0 = part * (64 / LPP) + lane / LPP;
+    if (part * (64 / LPP) >= nt) return;   // whole wave
+    const int t = min(t0, nt - 1), j = t / T, k = t % T;
+    const bool writes = t0 < nt && lane % LPP == 0;
+    const int64_t c = p * 64 + j, o = p * 64 + t, ld = Q.ld;
+    double X[6], v[6], vn = 0.0;
+    load_state(Q.x, ld, c, X);
+    bool ok = false;
+    const double l = Q.first ? 0.0 : Q.lam[c] * pow10i(k - T / 2);
+    if (!Q.first && !Q.done[c]) ok = damped_step(Q.jtj, Q.grad, ld, c, 0.5, l, v);
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
-        v[d] = vt[d * ld + o];
+        if (!ok) v[d] = 0.0;
         vn = fma(v[d], v[d], vn);
     }
-    if (!(vn > 0.0)) return;
-    const KArgs &A = descs[p].k;
-    const double is = sqrt(A.w);
-    const bool ranged = A.wr != 0.0;
-    const int R = ranged ? 3 : 2;
-    const double isr = sqrt(A.wr);
-    const double *rows = jrows + p * jstride + j;
-    double Y[6], gy[6];
+    bool geo = vn > 0.0;
+    if (__any(geo)) {
+        const double is = sqrt(A.w);
+        const bool ranged = A.wr != 0.0;
+        const int R = ranged ? 3 : 2;
+        const double isr = sqrt(A.wr);
+        const double *rows = Q.jrows + p * Q.jstride + j;
+        double Y[6], gy[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            Y[d] = fma(Q.hd, v[d], X[d]);
+            gy[d] = 0.0;
+        }
+        double J[18];   // the observation's rows of J, loaded ahead of the steps to it
+        trial_walk(A, Y, lds, lds_ns, [&](int32_t kk, int32_t, int32_t n, double *y) {
+            const double *q = rows + (int64_t)kk * R * 6 * Q.jld;
+#pragma unroll
+            for (int e = 0; e < 18; ++e)
+                if (e < 12 || ranged) J[e] = q[e * Q.jld];
+            if constexpr (LPP == 1)
+                rk4_steps(A, n, y);
+            else
+                rk4_steps_split<LPP>(A, n, y);
+        }, [&](int32_t, const double *row, const double *Sy) {
+            double ea, eb, fa[3], fb[3], er = 0, fq[3] = {0, 0, 0};
+            // (no line of sight: the trial stays x + v)
+            if (!residual_and_grad(row, Sy, ea, eb, fa, fb, ranged, er, fq)) geo = false;
+            const double ra = ea * is, rb = eb * is, rr = er * isr;
+#pragma unroll
+            for (int cc = 0; cc < 6; ++cc) {
+                gy[cc] = fma(J[cc], ra, fma(J[6 + cc], rb, gy[cc]));
+                if (ranged) gy[cc] = fma(J[12 + cc], rr, gy[cc]);
+            }
+        });
+        // J^T r_vv = (2 / hd) ((gy - J^T r) / hd - N v)
+        double Nv[6] = {0, 0, 0, 0, 0, 0};
+        {
+            int qi = 0;
+            for (int a = 0; a < 6; ++a)
+                for (int b = a; b < 6; ++b, ++qi) {
+                    const double nab = Q.jtj[qi * ld + c];
+                    Nv[a] = fma(nab, v[b], Nv[a]);
+                    if (b != a) Nv[b] = fma(nab, v[a], Nv[b]);
+                }
+        }
+        double rhs[6], acc[6], an = 0.0;
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+            rhs[d] = -(2.0 / Q.hd) * ((gy[d] - Q.jtr[d * ld + c]) / Q.hd - Nv[d]);
+        geo = damped_solve(Q.jtj, ld, c, l, rhs, acc) && geo;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) an = fma(acc[d], acc[d], an);
+        geo = geo && 4.0 * an <= Q.alpha * Q.alpha * vn;
+        if (geo) {
+#pragma unroll
+            for (int d = 0; d < 6; ++d) v[d] = fma(0.5, acc[d], v[d]);
+        }
+    }
 #pragma unroll
     for (int d = 0; d < 6; ++d) {
-        Y[d] = fma(hd, v[d], x[d * ld + c]);
-        gy[d] = 0.0;
+        X[d] = X[d] + v[d];
+        if (writes) Q.xt[d * ld + o] = X[d];
     }
-    // the steps between observations run as the fitness kernel's do (one
-    // certification vote per interval)
-    int32_t step = 0;
-    for (int32_t kk = 0; kk < A.K; ++kk) {
-        const int32_t target = A.ns[kk];
-        if (target > step) {
-            if constexpr (LPP == 1)
-                rk4_steps(A, target - step, Y);
-            else
-                rk4_steps_split<LPP>(A, target - step, Y);
-            step = target;
-        }
-        const double *row = A.tab + (int64_t)kk * TAB_W;
-        double Sy[6];
+    // the trial's chi2
+    CostAcc cost{0.0, A.w, A.mode, A.wr};
+    const int32_t S = A.ns[A.K - 1], L = Q.seg;
+    auto store = [&](int32_t row, const double *y) {
+        if (!writes || !Q.ckpt) return;
 #pragma unroll
-        for (int d = 0; d < 6; ++d) Sy[d] = Y[d];
-        const double tau = row[TAB_TAU];
-        if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, Sy);
-        double ea, eb, fa[3], fb[3], er = 0, fq[3] = {0, 0, 0};
-        if (!residual_and_grad(row, Sy, ea, eb, fa, fb, ranged, er, fq)) return;   // keeps x + v
-        const double ra = ea * is, rb = eb * is, rr = er * isr;
-        const double *q = rows + (int64_t)kk * R * 6 * jld;
-#pragma unroll
-        for (int cc = 0; cc < 6; ++cc) {
-            gy[cc] = fma(q[cc * jld], ra, fma(q[(6 + cc) * jld], rb, gy[cc]));
-            if (ranged) gy[cc] = fma(q[(12 + cc) * jld], rr, gy[cc]);
-        }
+        for (int d = 0; d < 6; ++d) Q.ckpt[((int64_t)row * 6 + d) * ld + o] = y[d];
+    };
+    trial_walk(A, X, lds, lds_ns, [&](int32_t, int32_t from, int32_t n, double *y) {
+        trial_steps<LPP>(A, from, n, L, y, store);
+    }, [&](int32_t, const double *row, const double *Sx) { cost(row, Sx); });
+    store((S + L - 1) / L, X);
+    if (!writes) return;
+    Q.chi2t[o] = cost.J;
+    if (Q.first) Q.stored[o] = (int32_t)o;
+}
+
+// The trials of the active problems (Q.work, *Q.count of them), each problem's
+// in up to LPP waves of 64 / LPP. A launch of few problems lasts as long as
+// its longest wave, which more lanes to a trial shorten (see split_step), so
+// they take as many as leave every wave a SIMD of its own. Four waves to a
+// workgroup, since waves of smaller ones share SIMDs while others idle. The
+// steps of both walks are most of the time: problems of up to 2,500 steps take
+// 1.55 ms up to 128 of them, 1.65 at 256 and 1.85 at 384 (the corrections and
+// the evaluations as two launches of one wave or one workgroup per problem, in
+// their fixed order: 1.52, 2.2 and 2.5 ms).
+__global__ __launch_bounds__(256) void k_gn_trials(TrialArgs Q)
+{
+    __shared__ double tab[4][OBS_CHUNK * TAB_W];
+    __shared__ int32_t ns[4][OBS_CHUNK];
+    const int64_t count = *Q.count;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t w = (int64_t)blockIdx.x * 4 + wave;
+    double *lds = tab[wave];
+    int32_t *lds_ns = ns[wave];
+    auto problem = [&](int64_t e) { return (int64_t)__builtin_amdgcn_readfirstlane(Q.work[2 * e]); };
+    if (4 * count <= Q.simds) {
+        if (w / 4 < count) trial_wave<4>(Q, problem(w / 4), (int)(w % 4), lds, lds_ns);
+    } else if (2 * count <= Q.simds) {
+        if (w / 2 < count) trial_wave<2>(Q, problem(w / 2), (int)(w % 2), lds, lds_ns);
+    } else {
+        if (w < count) trial_wave<1>(Q, problem(w), 0, lds, lds_ns);
     }
-    // J^T r_vv = (2 / hd) ((gy - J^T r) / hd - N v)
-    double Nv[6] = {0, 0, 0, 0, 0, 0};
-    {
-        int qi = 0;
-        for (int a = 0; a < 6; ++a)
-            for (int b = a; b < 6; ++b, ++qi) {
-                const double nab = jtj[qi * ld + c];
-                Nv[a] = fma(nab, v[b], Nv[a]);
-                if (b != a) Nv[b] = fma(nab, v[a], Nv[b]);
-            }
-    }
-    double rhs[6], acc[6];
-#pragma unroll
-    for (int d = 0; d < 6; ++d)
-        rhs[d] = -(2.0 / hd) * ((gy[d] - jtr[d * ld + c]) / hd - Nv[d]);
-    if (!damped_solve(jtj, ld, c, lam[c] * pow10i(k - T / 2), rhs, acc)) return;
-    double an = 0.0;
-#pragma unroll
-    for (int d = 0; d < 6; ++d) an = fma(acc[d], acc[d], an);
-    if (!(4.0 * an <= alpha * alpha * vn) || threadIdx.x % LPP != 0) return;
-#pragma unroll
-    for (int d = 0; d < 6; ++d) xt[d * ld + o] = x[d * ld + c] + fma(0.5, acc[d], v[d]);
 }
 
 // Selection after the trials: each live candidate takes its lowest trial chi2
@@ -1367,14 +1487,17 @@ __global__ __launch_bounds__(64 * LPP) void k_geo(const ProbDesc *__restrict__ d
 // largest tried. A candidate is done once its accepted step, or every trial
 // step when none is accepted, is no larger than step_tol in every component,
 // or its damping reaches the cap; the problem leaves the loop (active[p] = 0)
-// when all its candidates are done.
+// when all its candidates are done. stored[c]: the trial taken, whose
+// checkpoints are the candidate's now, or -1: it stays where it is, and its
+// normal equations and gradient are those of the last iteration.
 __global__ __launch_bounds__(64) void k_gn_select(double *__restrict__ x, double *__restrict__ chi2,
                                                   double *__restrict__ lam, int32_t *__restrict__ done,
                                                   int32_t *__restrict__ active,
                                                   const double *__restrict__ xt,
                                                   const double *__restrict__ chi2t,
                                                   const int32_t *__restrict__ n, int32_t T,
-                                                  int64_t ld, double step_tol)
+                                                  int64_t ld, double step_tol,
+                                                  int32_t *__restrict__ stored)
 {
     const int64_t p = blockIdx.x;
     if (!active[p]) return;   // whole workgroup (one wave)
@@ -1393,6 +1516,7 @@ __global__ __launch_bounds__(64) void k_gn_select(double *__restrict__ x, double
                 }
             }
             double step = 0.0;
+            stored[c] = kb < 0 ? -1 : (int32_t)(p * 64 + j * T + kb);
             if (kb >= 0) {
                 const int64_t o = p * 64 + j * T + kb;
                 for (int d = 0; d < 6; ++d) {
@@ -1416,54 +1540,54 @@ __global__ __launch_bounds__(64) void k_gn_select(double *__restrict__ x, double
 }
 
 // Live lanes of the refinement's packed launches: the (problem, candidate)
-// pairs of lanes [n][2] (problems with the most RK4 steps first) whose
-// problem is active and whose candidate is not done, in the same order, into
-// out; *count receives their number. One 1024-thread workgroup walks the
-// list in chunks, each wave compacting its lanes with a ballot and the
-// workgroup adding the waves' totals.
+// pairs of lanes [n][2] (problems with the most RK4 steps first, each with its
+// candidates from 0) whose problem is active and whose candidate is not done,
+// in the same order, into out, and the active problems as work entries
+// (problem, 0) into work; *count and *problems receive their numbers. One
+// 1024-thread workgroup walks the list in chunks, each wave compacting its
+// lanes with ballots and the workgroup adding the waves' totals.
 __global__ __launch_bounds__(1024) void k_live_lanes(const int32_t *__restrict__ lanes, int64_t n,
                                                      const int32_t *__restrict__ active,
                                                      const int32_t *__restrict__ done,
                                                      int32_t *__restrict__ out,
-                                                     int64_t *__restrict__ count, int64_t nprob,
+                                                     int64_t *__restrict__ count,
+                                                     int32_t *__restrict__ work,
                                                      int32_t *__restrict__ problems)
 {
-    __shared__ int32_t wave_total[16], n_active;
-    if (threadIdx.x == 0) n_active = 0;
-    __syncthreads();
-    int32_t mine = 0;
-    for (int64_t p = threadIdx.x; p < nprob; p += 1024) mine += active[p] != 0;
-    atomicAdd(&n_active, mine);
+    __shared__ int32_t wave_total[2][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int64_t base = 0;
+    const uint64_t below = lane == 0 ? 0 : ~0ull >> (64 - lane);
+    int64_t base[2] = {0, 0};
     for (int64_t c0 = 0; c0 < n; c0 += 1024) {
         const int64_t q = c0 + threadIdx.x;
         int32_t p = 0, j = 0;
-        bool live = false;
+        bool flag[2] = {false, false};
         if (q < n) {
             p = lanes[2 * q];
             j = lanes[2 * q + 1];
-            live = active[p] && !done[(int64_t)p * 64 + j];
+            const bool on = active[p] != 0;
+            flag[0] = on && !done[(int64_t)p * 64 + j];
+            flag[1] = on && j == 0;
         }
-        const uint64_t mask = __ballot(live);
-        const int before = lane == 0 ? 0 : __popcll(mask & (~0ull >> (64 - lane)));
-        if (lane == 0) wave_total[wave] = __popcll(mask);
+        const uint64_t mask[2] = {__ballot(flag[0]), __ballot(flag[1])};
+        if (lane < 2) wave_total[lane][wave] = __popcll(mask[lane]);
         __syncthreads();
-        int64_t off = base;
-        for (int w = 0; w < wave; ++w) off += wave_total[w];
-        int64_t total = 0;
-        for (int w = 0; w < 16; ++w) total += wave_total[w];
-        if (live) {
-            out[2 * (off + before)] = p;
-            out[2 * (off + before) + 1] = j;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            int64_t off = base[f];
+            for (int w = 0; w < wave; ++w) off += wave_total[f][w];
+            for (int w = 0; w < 16; ++w) base[f] += wave_total[f][w];
+            if (flag[f]) {
+                int32_t *dst = (f ? work : out) + 2 * (off + __popcll(mask[f] & below));
+                dst[0] = p;
+                dst[1] = j;
+            }
         }
-        base += total;
         __syncthreads();
     }
-    __syncthreads();
     if (threadIdx.x == 0) {
-        *count = base;
-        *problems = n_active;
+        *count = base[0];
+        *problems = (int32_t)base[1];
     }
 }
 
@@ -1650,22 +1774,29 @@ hipError_t launch_normal_grad(const ProbDesc &d0, const SwarmArrays &NB, const S
 }
 
 hipError_t launch_sens_pipe(const ProbDesc &d0, const SwarmArrays &B, const PipeArgs &Q,
-                            int64_t grid, int32_t seg, bool tan, bool adj, hipStream_t st)
+                            int64_t grid, bool tan, hipStream_t st)
 {
-    if (!(tan || adj) || seg < PIPE_SUB || seg > PIPE_MAX_SEG) return hipErrorInvalidValue;
-    const unsigned lds = (unsigned)pipe_lds_bytes(seg, tan, adj);
+    if (Q.seg < PIPE_SUB || Q.seg > PIPE_MAX_SEG || Q.seg % PIPE_SUB) return hipErrorInvalidValue;
+    const unsigned lds = (unsigned)pipe_lds_bytes(Q.seg, tan, !tan);
     const dim3 g((unsigned)grid), b(tan ? 192 : 128);
     const bool single = B.desc == nullptr;
-    if (tan && adj) {
-        if (single) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_sens_pipe<false, true, true>), g, b, lds, st, d0, B, Q);
-    } else if (tan) {
+    if (tan) {
         if (single) hipLaunchKernelGGL((k_sens_pipe<true, true, false>), g, b, lds, st, d0, B, Q);
         else hipLaunchKernelGGL((k_sens_pipe<false, true, false>), g, b, lds, st, d0, B, Q);
     } else {
         if (single) hipLaunchKernelGGL((k_sens_pipe<true, false, true>), g, b, lds, st, d0, B, Q);
         else hipLaunchKernelGGL((k_sens_pipe<false, false, true>), g, b, lds, st, d0, B, Q);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_sens_stored(const ProbDesc &d0, const SwarmArrays &B, const PipeArgs &Q,
+                              int64_t grid, hipStream_t st)
+{
+    if (!B.desc || !Q.stored || Q.seg < PIPE_SUB || Q.seg > PIPE_MAX_SEG || Q.seg % PIPE_SUB)
+        return hipErrorInvalidValue;
+    const unsigned lds = (unsigned)pipe_lds_bytes(Q.seg, true, true);
+    hipLaunchKernelGGL(k_sens_stored, dim3((unsigned)(2 * grid)), dim3(192), lds, st, d0, B, Q);
     return hipGetLastError();
 }
 
@@ -1679,44 +1810,31 @@ hipError_t launch_gn_solve(const ProbDesc &d0, const SwarmArrays &B, int bs, int
     return hipGetLastError();
 }
 
-hipError_t launch_gn_trials(const double *x, const double *jtj, const double *g, const double *lam,
-                            const int32_t *n, const int32_t *active, const int32_t *done,
-                            int32_t T, int64_t nprob, int64_t ld, double *xt, double *vt,
-                            hipStream_t st)
+hipError_t launch_gn_trials(const TrialArgs &Q, int64_t nprob, hipStream_t st)
 {
-    if (T < 1 || T > 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gn_trials, dim3((unsigned)nprob), dim3(64), 0, st, x, jtj, g, lam, n, active, done, T, ld, xt, vt);
-    return hipGetLastError();
-}
-
-hipError_t launch_geo(const ProbDesc *descs, const double *x, const double *jtj, const double *jtr,
-                      const double *jrows, int64_t jstride, int64_t jld, const double *lam,
-                      const int32_t *n, const int32_t *active, const int32_t *done, int32_t T,
-                      int64_t nprob, int64_t ld, double hd, double alpha, const double *vt,
-                      double *xt, int lanes, const Gate &G, hipStream_t st)
-{
-    if (T < 1 || T > 64 || !jrows) return hipErrorInvalidValue;
-    if (lanes == 4)
-        hipLaunchKernelGGL(k_geo<4>, dim3((unsigned)nprob), dim3(256), 0, st, descs, x, jtj, jtr, jrows, jstride, jld, lam, n, active, done, T, ld, hd, alpha, vt, xt, G);
-    else
-        hipLaunchKernelGGL(k_geo<1>, dim3((unsigned)nprob), dim3(64), 0, st, descs, x, jtj, jtr, jrows, jstride, jld, lam, n, active, done, T, ld, hd, alpha, vt, xt, G);
+    if (Q.T < 1 || Q.T > 64 || Q.seg < 1 || (Q.seg & (Q.seg - 1)) || (!Q.first && !Q.jrows)) return hipErrorInvalidValue;
+    // workgroups for whichever share the number of active problems calls for
+    const int64_t four = std::min<int64_t>(nprob, Q.simds / 4), two = (std::min<int64_t>(nprob, Q.simds / 2) + 1) / 2;
+    const int64_t grid = std::max({four, two, (nprob + 3) / 4});
+    hipLaunchKernelGGL(k_gn_trials, dim3((unsigned)grid), dim3(256), 0, st, Q);
     return hipGetLastError();
 }
 
 hipError_t launch_gn_select(double *x, double *chi2, double *lam, int32_t *done, int32_t *active,
                             const double *xt, const double *chi2t, const int32_t *n, int32_t T,
-                            int64_t nprob, int64_t ld, double step_tol, hipStream_t st)
+                            int64_t nprob, int64_t ld, double step_tol, int32_t *stored,
+                            hipStream_t st)
 {
     if (T < 1 || T > 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gn_select, dim3((unsigned)nprob), dim3(64), 0, st, x, chi2, lam, done, active, xt, chi2t, n, T, ld, step_tol);
+    hipLaunchKernelGGL(k_gn_select, dim3((unsigned)nprob), dim3(64), 0, st, x, chi2, lam, done, active, xt, chi2t, n, T, ld, step_tol, stored);
     return hipGetLastError();
 }
 
-hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active, int64_t nprob,
-                            const int32_t *done, int32_t *out, int64_t *count, int32_t *problems,
-                            hipStream_t st)
+hipError_t launch_live_lanes(const int32_t *lanes, int64_t n, const int32_t *active,
+                            const int32_t *done, int32_t *out, int64_t *count, int32_t *work,
+                            int32_t *problems, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_live_lanes, dim3(1), dim3(1024), 0, st, lanes, n, active, done, out, count, nprob, problems);
+    hipLaunchKernelGGL(k_live_lanes, dim3(1), dim3(1024), 0, st, lanes, n, active, done, out, count, work, problems);
     return hipGetLastError();
 }
 

@@ -94,3 +94,35 @@ def test_refinement_of_few_and_many_problems_agrees(torch_dev):
     many = refine(many_idx)
     for f, m in zip(few, many):
         assert np.array_equal(f[many_idx], m)
+
+
+@pytest.mark.parametrize("n_cand", [1, 7, 16, 20, 64])
+@pytest.mark.parametrize("kind", ["grid", "offgrid"])
+def test_refinement_does_not_depend_on_the_batch(torch_dev, n_cand, kind):
+    """The refinement's launches divide the work by the number of problems
+    still active: pipelined sweeps from the trials' checkpoints or packed ones,
+    four, two or one lanes to a trial. Problems whose evaluations end at the
+    edges of the checkpoints' segments (8 steps), with off-grid and epoch
+    observations, get the same bits in batches of every share."""
+    wl = W.tiny(3)
+    steps = [8, 9, 15, 16, 121, 1]
+    rng = np.random.default_rng([n_cand, len(kind)])
+    t = [times(s, kind) for s in steps] + [np.array([0.0, 1e-3])]
+    obs = []
+    for tk in t:
+        P = oracle.Problem(wl.mu, wl.h, wl.sigma, wl.chief, tk, np.zeros((len(tk), 2)))
+        obs.append(oracle.predict(P, wl.truth) + rng.normal(0, wl.sigma, (len(tk), 2)))
+
+    def refine(idx):
+        n = len(idx)
+        b = iod.iod_create_batch([wl.mu] * n, [wl.chief] * n, [t[i] for i in idx], [obs[i] for i in idx],
+                                 [wl.sigma] * n, h=wl.h)
+        params = [iod.pso_params(0.7, 1.5, 1.5, 3, wl.lo, wl.hi, problem=int(i)) for i in idx]
+        return iod.iod_batch_solve_polished(b, params, np.full(n, 64), 2, top_k=64, n_cand=n_cand, n_gn=6)
+
+    each = len(t)
+    alone = refine(np.arange(each))
+    for n in (1, 300, 600, 1300):
+        idx = np.arange(n) % each
+        for a, b in zip(alone, refine(idx)):
+            assert np.array_equal(a[idx], b, equal_nan=True), n
