@@ -1330,7 +1330,8 @@ int batch_run(iod_batch *b, const iod_pso_params *params, const int64_t *m, int6
     auto iterate = [&](int64_t n) -> hipError_t {
         if (top_k == 0) return launch_swarm_iter(d0, B, bs, L.grid, n, st, cfg.waves);
         hipError_t e = launch_mixed_iter(d0, B, bs, L.grid, n, rel, st);
-        if (e == hipSuccess) e = launch_topk(B, B.jp, top_k, cand, st);
+        // (iteration 1's candidates are those of the initial evaluation)
+        if (e == hipSuccess && n > 1) e = launch_topk(B, B.jp, top_k, cand, st);
         if (e == hipSuccess) e = launch_reeval64(B, cand, top_k, n, re_lanes, st);
         return e;
     };

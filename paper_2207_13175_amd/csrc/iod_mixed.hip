@@ -850,6 +850,16 @@ __device__ __forceinline__ void reeval_stopped(const ProbDesc &D, const SwarmArr
     if (rank == 0 && D.hist && n < D.hist_len) D.hist[n] = NAN;
 }
 
+// Iteration 1 evaluates nothing (the swarm moves after its first evaluation), so
+// its personal bests and candidates are those of iteration 0, none of them
+// below the record that they set: the record stays.
+__device__ __forceinline__ void reeval_same(const ProbDesc &D, const SwarmArrays &B, int64_t p,
+                                            int64_t n, int rank)
+{
+    const double none[6] = {0, 0, 0, 0, 0, 0};
+    reeval_record(D, B, p, n, INFINITY, INFINITY, none, rank);
+}
+
 // FP64 re-evaluation, one wave per problem; RE_WAVES problems to a workgroup,
 // so they run on the SIMDs of one compute unit instead of sharing one. The
 // waves never wait for each other: each stages its own problem's observation
@@ -871,6 +881,10 @@ __global__ __launch_bounds__(64 * RE_WAVES) void k_reeval64(SwarmArrays B,
     const ProbDesc &D = B.desc[p];
     if (B.stop[p] >= 0.0) {
         reeval_stopped(D, B, p, n, lane);
+        return;
+    }
+    if (n == 1) {
+        reeval_same(D, B, p, n, lane);
         return;
     }
     double bkey, bidx, bst[6];
@@ -905,6 +919,10 @@ __global__ __launch_bounds__(64 * LPP) void k_reeval64_split(SwarmArrays B,
     const ProbDesc &D = B.desc[p];
     if (B.stop[p] >= 0.0) {
         reeval_stopped(D, B, p, n, (int)threadIdx.x);
+        return;
+    }
+    if (n == 1) {
+        reeval_same(D, B, p, n, (int)threadIdx.x);
         return;
     }
     double bkey, bidx, bst[6];

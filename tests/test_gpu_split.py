@@ -97,3 +97,21 @@ def test_chief_tables_of_the_offset_formulation(steps, tau):
     a, b = a.cpu().numpy(), b.cpu().numpy()
     assert np.array_equal(a[:, :, 0], b[:, :, 0])
     assert np.max(np.abs(a[:, :, 1] - b[:, :, 1])) <= 2 * steps * 2.0 ** -24 * 1e-3
+
+
+@pytest.mark.parametrize("lanes_one", [False, True])
+def test_first_mixed_iteration_keeps_the_initial_record(lanes_one):
+    """The first iteration only moves the swarm: the record and the history
+    entry of the initial evaluation stay (few problems: four lanes to a
+    candidate; 1,100: one)."""
+    n = 1100 if lanes_one else 3
+    wls = [W.tiny(s % 3, K=2, T=0.01) for s in range(n)]
+    b = iod.iod_create_batch([w.mu for w in wls], [w.chief for w in wls], [w.t for w in wls],
+                             [np.zeros((w.K, 2)) for w in wls], [w.sigma for w in wls], h=wls[0].h)
+    params = [iod.pso_params(0.7, 1.5, 1.5, 3, w.lo, w.hi, problem=i) for i, w in enumerate(wls)]
+    m = np.full(n, 64)
+    out = [iod.iod_batch_solve_mixed(b, params, m, k, top_k=8) for k in (0, 1, 3)]
+    for a, c in zip(out[0][:2], out[1][:2]):
+        assert np.array_equal(a, c)
+    assert np.array_equal(out[1][2], out[2][2][:, :2])
+    assert np.array_equal(out[1][2][:, 0], out[1][2][:, 1])
