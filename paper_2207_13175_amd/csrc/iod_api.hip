@@ -242,6 +242,7 @@ ProbDesc desc_of(const KArgs &A, const double chief[6], const iod_pso_params *p)
     std::memcpy(D.chief, chief, sizeof D.chief);
     D.kappa = 1.0;
     D.lanes = 1;
+    D.solo = 0;
     if (p) {
         D.omega = p->omega;
         D.eta1 = p->eta1;
@@ -312,6 +313,46 @@ struct SplitLoad {
             total += (double)n * (double)w.first;
         }
         return SPLIT_COST[l] * std::max(t, total / simds);
+    }
+    // Estimates for at most two workgroups of bs threads to their SIMDs, longest
+    // first (work in that order; INFINITY if there are more). alone: one after
+    // the other, the second ones, longest first, where the first ends first, and
+    // 10% longer, since nothing fills a wave's waits. Else side by side in the
+    // order of dispatch, so that the longest has the longest of the second ones
+    // beside it.
+    double paired(int l, int bs, int simds, bool alone) const
+    {
+        const size_t places = (size_t)std::max(1, simds / (bs / 64));
+        std::vector<int64_t> len;
+        for (const auto &w : work) {
+            const int64_t n = ceil_div(w.second, bs >> l);
+            if (len.size() + (size_t)n > 2 * places) return INFINITY;
+            len.insert(len.end(), (size_t)n, w.first);
+        }
+        if (len.empty()) return INFINITY;
+        if (len.size() <= places) return SPLIT_COST[l] * (double)len[0];
+        if (!alone) return SPLIT_COST[l] * (double)(len[0] + len[places]);
+        int64_t t = len[0];
+        for (size_t j = places; j < len.size(); ++j) t = std::max(t, len[j] + len[2 * places - 1 - j]);
+        return 1.1 * SPLIT_COST[l] * (double)t;
+    }
+    // Lanes of a batch's FP64 swarm launches, whose workgroups of one lane per
+    // particle have bs threads; solo: they run one wave to a SIMD.
+    int swarm_lanes(int bs, int simds, bool &solo)
+    {
+        int best = lanes(simds);
+        const double side = paired(best >> 1, best > 1 ? SPLIT_BS : bs, simds, false);
+        double t0 = side < INFINITY ? side : estimate(best >> 1, simds);
+        solo = false;
+        for (int l = 0; l < 3; ++l) {
+            const double t = paired(l, l ? SPLIT_BS : bs, simds, true);
+            if (t <= t0) {
+                best = 1 << l;
+                t0 = t;
+                solo = true;
+            }
+        }
+        return best;
     }
     // two: whether two lanes per particle are to be had
     int lanes(int simds, bool two = true)
@@ -719,7 +760,7 @@ void single_view(const iod_handle *h, const iod_swarm *s, const iod_pso_params *
     D.slot_off = 0;
     D.nslots = nslots;
     D.block = block;
-    D.lanes = lanes;
+    D.lanes = (int16_t)lanes;
     B.desc = nullptr;
     B.work = nullptr;
     B.x = s->x;
@@ -917,7 +958,7 @@ int iod_eval_swarm(iod_handle *h, const double *x, int64_t ld, int64_t m, double
     const int bs = block_of(h->cfg);
     ProbDesc D = desc_of(h->kargs(), h->P.chief, nullptr);
     D.m = m;
-    D.lanes = h->lanes(m);
+    D.lanes = (int16_t)h->lanes(m);
     D.block = D.lanes > 1 ? SPLIT_BS / D.lanes : bs;
     D.nslots = ceil_div(m, D.block);
     SwarmArrays B;
@@ -1216,8 +1257,9 @@ struct BatchLayout {
 
 // split: the launches are FP64 evaluations or swarms, which may give each
 // particle several lanes (the same number for all problems).
+// swarm: the launches are swarm launches, which may also run one wave to a SIMD.
 int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t *m, int bs,
-                 int order, BatchLayout &L, bool split = false)
+                 int order, BatchLayout &L, bool split = false, bool swarm = false)
 {
     std::vector<int64_t> off(b->P + 1);
     int64_t ld = iod_batch_offsets(b, m, off.data());
@@ -1225,10 +1267,12 @@ int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t
     L.ld = ld;
     L.descs.resize(b->P);
     int lanes = 1;
+    bool solo = false;
     if (split) {
         SplitLoad S;
         for (int32_t p = 0; p < b->P; ++p) S.add(m[p], b->probs[p].steps);
-        lanes = S.lanes(b->simds);
+        lanes = swarm && order == IOD_ORDER_LONGEST_FIRST ? S.swarm_lanes(bs, b->simds, solo)
+                                                          : S.lanes(b->simds);
         if (lanes > 1) bs = SPLIT_BS / lanes;
     }
     int64_t slots = 0;
@@ -1241,7 +1285,8 @@ int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t
         D.slot_off = slots;
         D.nslots = ceil_div(m[p], bs);
         D.block = bs;
-        D.lanes = lanes;
+        D.lanes = (int16_t)lanes;
+        D.solo = solo;
         slots += D.nslots;
     }
     L.total_slots = slots;
@@ -1285,7 +1330,7 @@ int batch_run(iod_batch *b, const iod_pso_params *params, const int64_t *m, int6
     int rc = rel ? ensure_chief_tables(b) : IOD_OK;
     if (rc != IOD_OK) return rc;
     BatchLayout L;
-    rc = batch_layout(b, params, m, bs, cfg.order, L, top_k == 0);
+    rc = batch_layout(b, params, m, bs, cfg.order, L, top_k == 0, top_k == 0);
     if (rc != IOD_OK) return rc;
     Phase swarm_phase(top_k ? "iod_batch: mixed-precision swarm" : "iod_batch: FP64 swarm");
     const int64_t P = b->P, ld = L.ld;

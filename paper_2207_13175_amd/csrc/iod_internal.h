@@ -81,7 +81,8 @@ struct ProbDesc {
     int64_t slot_off;           // first argmin slot
     int64_t nslots;             // ceil(m / block)
     int32_t block;              // particles per workgroup of the swarm kernels (and per argmin slot)
-    int32_t lanes;              // adjacent lanes per particle of the FP64 propagations: 1, 2 or 4
+    int16_t lanes;              // adjacent lanes per particle of the FP64 propagations: 1, 2 or 4
+    int16_t solo;               // FP64 swarm launches of a batch: one wave per SIMD at a time
 };
 
 // Swarm storage of one launch. desc/work are null for a single problem.

@@ -226,10 +226,27 @@ __global__ __launch_bounds__(BS) void k_eval(ProbDesc d0, SwarmArrays B)
 // SIMD between waves, and keep 2 (8 measured 0.4% slower there).
 constexpr int steps_per_trip(bool single) { return single ? 8 : 2; }
 
+// A wave that takes all registers of its SIMD, so that no other shares it. Two
+// long waves side by side end when both are done, at half the rate each, while
+// the SIMDs of the short ones idle; with one wave at a time, the SIMDs that end
+// first take the next longest ones. A lone wave runs about 13% slower than its
+// share of two (nothing fills its waits), so this is for batches whose waves
+// the SIMDs take in one or two rounds. (Limiting the waves by LDS left
+// single-wave workgroups in pairs on a SIMD beside idle ones, and a higher wave
+// priority for longer waves changed nothing.) Problems of 512 to 8,192 particles
+// and 200 to 3,000 steps, 4 iterations: 16 of them 4.5 -> 3.8 ms, 40 8.7 -> 6.2,
+// 48 8.8 -> 7.4; forced on 96 and 256, 13.3 -> 14.5 and 33.8 -> 38.3.
+template <bool SOLO>
+__device__ __forceinline__ void occupy_simd()
+{
+    if constexpr (SOLO) asm volatile("" ::: "v255", "a255");
+}
+
 // Algorithm 1 initialisation.
-template <int BS, bool SINGLE, int LPP = 1>
+template <int BS, bool SINGLE, int LPP = 1, bool SOLO = false>
 __global__ __launch_bounds__(BS) void k_swarm_init(ProbDesc d0, SwarmArrays B)
 {
+    occupy_simd<SOLO>();
     __shared__ double lds[OBS_CHUNK * TAB_W];
     __shared__ int32_t lds_ns[OBS_CHUNK];
     __shared__ double red[2 * (BS / 64)];
@@ -340,9 +357,10 @@ __device__ __forceinline__ void swarm_iter(const ProbDesc &d0, const SwarmArrays
 }
 
 // The iteration kernel with the compiler's register allocation ...
-template <int BS, bool SINGLE, int LPP = 1>
+template <int BS, bool SINGLE, int LPP = 1, bool SOLO = false>
 __global__ __launch_bounds__(BS) void k_swarm_iter(ProbDesc d0, SwarmArrays B, int64_t n)
 {
+    occupy_simd<SOLO>();
     swarm_iter<BS, SINGLE, LPP>(d0, B, n);
 }
 
@@ -454,6 +472,14 @@ hipError_t launch_eval(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t
 hipError_t launch_swarm_init(const ProbDesc &d0, const SwarmArrays &B, int bs, int64_t grid,
                              hipStream_t st)
 {
+    if (d0.solo && B.desc) {
+        if (d0.lanes > 1) {
+            IOD_DISPATCH_SPLIT(d0.lanes, hipLaunchKernelGGL((k_swarm_init<SPLIT_BS, false, LPP_, true>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B));
+        } else {
+            IOD_DISPATCH_BS(bs, hipLaunchKernelGGL((k_swarm_init<BS_, false, 1, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B));
+        }
+        return hipGetLastError();
+    }
     if (d0.lanes > 1) {
         IOD_DISPATCH_SPLIT(d0.lanes, if (B.desc) hipLaunchKernelGGL((k_swarm_init<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B);
                            else hipLaunchKernelGGL((k_swarm_init<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B));
@@ -470,6 +496,14 @@ hipError_t launch_swarm_iter(const ProbDesc &d0, const SwarmArrays &B, int bs, i
 {
     const bool single = B.desc == nullptr;
     if (waves != 0 && waves != 3) return hipErrorInvalidValue;
+    if (d0.solo && !single && (waves == 0 || d0.lanes > 1)) {
+        if (d0.lanes > 1) {
+            IOD_DISPATCH_SPLIT(d0.lanes, hipLaunchKernelGGL((k_swarm_iter<SPLIT_BS, false, LPP_, true>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, n));
+        } else {
+            IOD_DISPATCH_BS(bs, hipLaunchKernelGGL((k_swarm_iter<BS_, false, 1, true>), dim3((unsigned)grid), dim3(BS_), 0, st, d0, B, n));
+        }
+        return hipGetLastError();
+    }
     if (d0.lanes > 1) {
         IOD_DISPATCH_SPLIT(d0.lanes, if (single) hipLaunchKernelGGL((k_swarm_iter<SPLIT_BS, true, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, n);
                            else hipLaunchKernelGGL((k_swarm_iter<SPLIT_BS, false, LPP_>), dim3((unsigned)grid), dim3(SPLIT_BS), 0, st, d0, B, n));

@@ -115,3 +115,29 @@ def test_first_mixed_iteration_keeps_the_initial_record(lanes_one):
         assert np.array_equal(a, c)
     assert np.array_equal(out[1][2], out[2][2][:, :2])
     assert np.array_equal(out[1][2][:, 0], out[1][2][:, 1])
+
+
+@pytest.mark.parametrize("block", [64, 128, 256])
+@pytest.mark.parametrize("top", [40, 700, 6000])
+def test_uneven_batches_do_not_depend_on_their_neighbours(block, top):
+    """Batches whose workgroups the SIMDs take in one or two rounds run one wave
+    to a SIMD, with one, two or four lanes to a particle: every problem's
+    result is that of the problem in a batch of its own."""
+    rng = np.random.default_rng([block, top])
+    n = 24
+    wls = [W.tiny(s % 4, K=3, T=float(rng.uniform(0.01, 0.06))) for s in range(n)]
+    m = np.exp(rng.uniform(np.log(20), np.log(top), n)).astype(int)
+    m[0], m[1] = top, 1
+    obs = [rng.normal(0, 0.3, (w.K, 2)) for w in wls]
+    par = [iod.pso_params(0.7, 1.5, 1.5, 3, w.lo, w.hi, problem=i) for i, w in enumerate(wls)]
+
+    def solve(idx):
+        b = iod.iod_create_batch([wls[i].mu for i in idx], [wls[i].chief for i in idx], [wls[i].t for i in idx],
+                                 [obs[i] for i in idx], [wls[i].sigma for i in idx], h=wls[0].h)
+        iod.iod_batch_set_config(b, block=block)
+        return iod.iod_batch_solve(b, [par[i] for i in idx], m[idx], 3)
+
+    whole = solve(np.arange(n))
+    for i in range(n):
+        for a, w in zip(solve(np.array([i])), whole):
+            assert np.array_equal(a[0], w[i]), i
