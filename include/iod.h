@@ -105,13 +105,15 @@ typedef struct {
 /* Launch configuration of the swarm kernels (see iod_set_config,
  * iod_batch_set_config, iod_batch_autotune). Results do not depend on it. */
 typedef struct {
-    int32_t block;     /* threads per workgroup: 64, 128 or 256; 0 = default (256) */
+    int32_t block;     /* threads per workgroup: 64, 128 or 256; 0 = default (256). FP64 swarms
+                          small enough to take several lanes per particle use 256 */
     int32_t order;     /* batches: IOD_ORDER_LONGEST_FIRST (default) or IOD_ORDER_PROBLEM */
     int32_t graph;     /* iod_solve / iod_batch_solve: 1 = replay the iteration launches
                           from one captured hipGraph, 0 = launch them directly */
     int32_t waves;     /* FP64 swarm iteration kernel: 0 = the compiler's register allocation,
                           3 = registers capped so that at least 3 waves fit per SIMD (an
-                          occupancy choice for iod_batch_autotune); other values are rejected */
+                          occupancy choice for iod_batch_autotune; no effect with several
+                          lanes per particle); other values are rejected */
 } iod_launch_config;
 
 #define IOD_ORDER_LONGEST_FIRST 0 /* workgroups of problems with more RK4 steps dispatch first */
@@ -476,15 +478,16 @@ int iod_batch_autotune(iod_batch *b, const iod_pso_params *params, const int64_t
 /* vanishes at zero residual, that of the whitened residuals does not.      */
 /* ------------------------------------------------------------------------ */
 
-/* Doubles of workspace iod_grad needs for a leading dimension ld (checkpoints
- * every 64 RK4 steps plus one 64-step segment, 6 doubles each, per column),
- * or a negative code. */
+/* Doubles of workspace iod_grad needs for a leading dimension ld (a row per 64
+ * RK4 steps and 64 more, 6 doubles each, per column: checkpoints every 64 steps
+ * and one segment, or, for few particles, checkpoints as close as fit), or a
+ * negative code. */
 int64_t iod_grad_work_len(const iod_handle *h, int64_t ld);
 
 /* Cost (the handle's cost mode) and its gradient with respect to the initial
  * state, by the discrete adjoint of the RK4 propagation and the angle model:
- * a forward pass storing the state every 64 steps, then a reverse sweep that
- * recomputes each 64-step segment and applies the transposed step
+ * a forward pass storing checkpoints, then a reverse sweep that recomputes
+ * each segment between them and applies the transposed step
  * derivative, adding each observation's contribution at its step. The
  * gradient is that of the computed (discrete) cost.
  *   x     device [6][ld]     cost device [ld]     grad device [6][ld]
