@@ -1658,10 +1658,10 @@ constexpr int64_t POLISH_CKPT_BYTES = (int64_t)2 << 30;
 // problem) have a compute unit each, and the launch grows with every further
 // one to a unit: the normal equations by about half, the gradient by a third
 // if their LDS lets several share a unit, else by its whole time.
-// Over 2,000 steps the normal equations take 0.94, 1.48, 2.16 and 2.81 ms with
-// one to four workgroups to a unit against 4.1 ms otherwise; the gradient 1.60,
-// 3.18 and 4.7 ms against 4.7 ms, and over 500 steps (two share a unit) 0.45,
-// 0.60 and 0.95 ms against 1.2 ms.
+// Over 2,000 steps the normal equations take 0.84, 1.20, 1.87, 2.29, 2.78 and
+// 3.27 ms with one to six workgroups to a unit against 4.1 ms otherwise; the
+// gradient 1.59, 3.14 and 4.7 ms against 4.7 ms, and over 500 steps (two share a
+// unit) 0.45, 0.60 and 0.95 ms against 1.2 ms.
 struct PipePlan {
     int64_t groups = 0, steps = 0, grid = 0;
     int32_t sub = 1, seg = PIPE_SUB;
@@ -1682,7 +1682,7 @@ struct PipePlan {
     void decide(int simds)
     {
         if (steps > PIPE_MAX_STEPS) return;
-        tan = groups <= 4 * (simds / 4);
+        tan = groups <= 6 * (simds / 4);
         adj = groups <= adj_limit(simds);
     }
 };

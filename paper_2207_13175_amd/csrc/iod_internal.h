@@ -121,9 +121,12 @@ constexpr int ADJ_CKPT = 64;
 constexpr int PIPE_P = 16;
 constexpr int PIPE_FWD = 8, PIPE_SUB = 8;
 constexpr int32_t PIPE_MAX_STEPS = 4096, PIPE_MAX_SEG = 32;
-// One step of stage data and the two hand-over states, in double2.
+// One step of stage data and the three hand-over states, in double2: going
+// forward without the velocities, in three chunks (produced, made Jacobians,
+// used).
 constexpr int PIPE_STEP = 12 * PIPE_P + PIPE_P + PIPE_P / 2;
-constexpr int PIPE_XEND = 2 * 6 * PIPE_P / 2;
+constexpr int PIPE_TSTEP = 12 * PIPE_P, PIPE_SLOTS = 3;
+constexpr int PIPE_XEND = 3 * 6 * PIPE_P / 2;
 
 // Steps between its checkpoints: as few as the adjoint's scratch rows (one per
 // ADJ_CKPT steps and ADJ_CKPT more) can hold, in whole blocks; at most 32.
@@ -146,8 +149,9 @@ struct Gate {
 // LDS of a workgroup whose longest segment has seg steps.
 inline int64_t pipe_lds_bytes(int32_t seg, bool tan, bool adj)
 {
-    const int64_t fwd = tan ? 2 * PIPE_FWD : 0, rev = adj ? seg + PIPE_SUB : 0;
-    return (PIPE_XEND + (fwd > rev ? fwd : rev) * PIPE_STEP) * 16;
+    const int64_t fwd = tan ? PIPE_SLOTS * PIPE_FWD * PIPE_TSTEP : 0;
+    const int64_t rev = adj ? (seg + PIPE_SUB) * PIPE_STEP : 0;
+    return (PIPE_XEND + (fwd > rev ? fwd : rev)) * 16;
 }
 
 struct PipeArgs {

@@ -688,22 +688,25 @@ __global__ __launch_bounds__(64) void k_normal_grad(ProbDesc d0, SwarmArrays NB,
 // and once more per reversed step (1,460), while most SIMDs idle. Here a
 // workgroup holds PIPE_P particles and its waves share the work of each step
 // through LDS:
-//   - wave 0 propagates the states, four lanes per particle, and leaves the
-//     stage Jacobians of each step (three numbers and the position per stage)
-//     in LDS: about 185 slots per step;
-//   - two waves carry the tangent, one lane per column (eight lanes per
-//     particle, six in use), a chunk of steps behind: about 165 slots;
-//   - for the adjoint, wave 0 then goes back segment by segment: it recomputes
-//     the segment's steps from the checkpoint while wave 1 applies the
-//     transposed steps of the segment after it, in reverse order.
+//   - wave 0 propagates the states, four lanes per particle: about 172 slots
+//     per step, and 25 cycles for every LDS write, whatever its width;
+//   - for the tangent it leaves the stages' positions (two writes a step), which
+//     wave 3 turns into gravity blocks, one lane per particle and stage, a chunk
+//     of steps behind, and two waves carry the tangent another chunk behind, one
+//     lane per column (eight lanes per particle, six in use): about 75 slots;
+//   - for the adjoint it leaves the stages' Jacobian data itself (six writes),
+//     going back segment by segment: it recomputes the segment's steps from the
+//     checkpoint while wave 1 applies the transposed steps of the segment after
+//     it, in reverse order.
 // Each operation on a particle is the one of the sweeps above, on the same
 // operands, so the bits are the same. 96 particles over 2,520 steps: normal
-// equations 5.02 -> 1.13 ms; 1,000 over 2,000: cost gradient 5.03 -> 1.60 ms.
-// The hand-over costs about 60 slots a step (a barrier every 8 steps and the
-// wait for LDS); longer chunks, masking the duplicate LDS writes and reading a
-// step ahead were slower. A workgroup's LDS (up to 140 KB) may keep it alone on
-// a compute unit, so with more particles than the host's rule allows the
-// other sweeps win.
+// equations 5.02 -> 1.01 ms (1.13 with the Jacobian data from the producer and
+// the blocks formed by every column); 1,000 over 2,000: cost gradient 5.03 ->
+// 1.58 ms. Wave 0 bounds both, with its hand-over (a barrier every 8 steps and
+// the wait for LDS); longer chunks, packed writes and reading a step ahead
+// gained nothing. A workgroup's LDS (76 to 140 KB) lets one or two share a
+// compute unit, so with more particles than the host's rule allows the other
+// sweeps win.
 // ---------------------------------------------------------------------------
 
 // One step in LDS, PIPE_STEP double2: per stage the position (x, y), (z, cs) and
@@ -722,6 +725,91 @@ struct PipeSink {
         ((double *)(s + 2 * PIPE_P))[prim] = o.ej;
     }
 };
+
+// Positions of the own stage only: (x, y) by the lane of primary 1, z by the other.
+struct PosSink {
+    static constexpr bool JAC = false;
+    double2 *own;   // the lane's entry at the own stage of half 0
+    bool second;
+    __device__ __forceinline__ void operator()(int half, const double *q, const Attraction &)
+    {
+        own[half * (6 * PIPE_P)] = make_double2(second ? q[2] : q[0], q[1]);
+    }
+};
+
+// n steps from X by the producer wave of the tangent, the positions of their
+// stages into slots ring + j PIPE_TSTEP; the vote and the redo as pipe_produce.
+__device__ __forceinline__ void pipe_positions(const KArgs &A, int32_t n, double X[6],
+                                               double2 *ring, int pp)
+{
+    if (A.fast) {
+        double X0[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X0[d] = X[d];
+        Cert cert;
+        const int j = threadIdx.x & 1;
+        PosSink sink{ring + (Quad<4>::is_late() ? 3 * PIPE_P : 0) + j * PIPE_P + pp, j != 0};
+        auto step = [&]() __attribute__((always_inline)) {
+            split_step<4>(A.mu, A.mu1, A.h, A.h2, A.h6, X, cert, sink);
+            sink.own += PIPE_TSTEP;
+        };
+        int32_t i = 0;
+        for (; i + 4 <= n; i += 4) {
+            step();
+            step();
+            step();
+            step();
+        }
+        for (; i < n; ++i) step();
+        if (__all(cert.ok())) return;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = X0[d];
+    }
+    for (int32_t j = 0; j < n; ++j) {
+        double a[6], k[6], s[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) s[d] = X[d];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double2 *q = ring + j * PIPE_TSTEP + 3 * i * PIPE_P + pp;
+            q[0] = make_double2(s[0], s[1]);
+            q[PIPE_P] = make_double2(s[2], 0.0);
+            rhs<false>(A.mu, A.mu1, s, k);
+#pragma unroll
+            for (int d = 0; d < 6; ++d) {
+                a[d] = i == 0 ? k[d] : i < 3 ? fma(2.0, k[d], a[d]) : a[d] + k[d];
+                if (i < 3) s[d] = fma(i == 2 ? A.h : A.h2, k[d], X[d]);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
+    }
+}
+
+// The positions of n steps in ring become their gravity blocks in place, one
+// lane per particle and stage: (g00, g01), (g02, g11), (g12, g22). A step with a
+// lane that is not certified takes the IEEE path.
+__device__ __forceinline__ void pipe_jacobians(const KArgs &A, int32_t n, double2 *ring)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    double2 *cell = ring + 3 * (lane / PIPE_P) * PIPE_P + lane % PIPE_P;
+    for (int32_t j = 0; j < n; ++j, cell += PIPE_TSTEP) {
+        const double2 xy = cell[0];
+        const double s[6] = {xy.x, xy.y, cell[PIPE_P].x, 0.0, 0.0, 0.0};
+        double f[6];
+        JacData J;
+        Cert cert;
+        if (A.fast) {
+            const Mark m = rhs_jac<true, true>(A.mu, A.mu1, s, f, J);
+            cert.add(m, m);
+        }
+        if (!A.fast || !__all(cert.ok())) rhs_jac<false, true>(A.mu, A.mu1, s, f, J);
+        const GMat G = gmat(J);
+        cell[0] = make_double2(G.g00, G.g01);
+        cell[PIPE_P] = make_double2(G.g02, G.g11);
+        cell[2 * PIPE_P] = make_double2(G.g12, G.g22);
+    }
+}
 
 __device__ __forceinline__ void pipe_put_velocity(double2 *slot, int pp, const double X[6])
 {
@@ -752,11 +840,13 @@ __device__ __forceinline__ void pipe_produce(const KArgs &A, int32_t n, double X
             slot += PIPE_STEP;
         };
         int32_t j = 0;
-        for (; j + 2 <= n; j += 2) {
+        for (; j + 4 <= n; j += 4) {
+            step();
+            step();
             step();
             step();
         }
-        if (j < n) step();
+        for (; j < n; ++j) step();
         if (__all(cert.ok())) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
@@ -882,7 +972,7 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
         return i < D.m && !(Q.done && Q.done[D.off + i]) && !(Q.stored && Q.stored[D.off + i] < 0);
     };
     if (!__any(wanted(i0 + (lane & (PIPE_P - 1))))) return;   // the same in every wave
-    if (wave > (TAN ? 2 : 1)) return;
+    if (wave > (TAN ? 3 : 1)) return;
     const int pp = wave == 0 ? lane >> 2 : TAN ? (wave - 1) * 8 + (lane >> 3) : lane & (PIPE_P - 1);
     const int64_t i = i0 + pp;
     const int64_t g = D.off + (i < D.m ? i : D.m - 1);
@@ -893,14 +983,21 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
     const int32_t S = A.ns[A.K - 1];
     const int32_t L = Q.seg, nseg = (S + L - 1) / L;
 
-    // forward sweep: chunks of up to PIPE_FWD steps, ending at each observation
-    // (and each checkpoint)
-    auto chunk = [&](int32_t step, int32_t target) {
-        int32_t n = target - step;
-        if (TAN) n = min(n, PIPE_FWD);
-        if (ADJ) n = min(n, L - step % L);
-        return n;
+    // Forward sweep of the tangent: an interval between observations goes in equal
+    // chunks of up to PIPE_FWD steps. The waves hand over in lockstep: while chunk
+    // c is produced, c - 1 becomes Jacobians and c - 2 moves the tangent.
+    struct Chunks {
+        int32_t base, extra;
+        __device__ __forceinline__ explicit Chunks(int32_t steps)
+        {
+            const int32_t parts = max(1, (steps + PIPE_FWD - 1) / PIPE_FWD);
+            base = steps / parts;
+            extra = steps - base * parts;
+        }
+        __device__ __forceinline__ int32_t next() { return base + (extra-- > 0 ? 1 : 0); }
     };
+    auto tslot = [&](int c) { return ring + c * (PIPE_FWD * PIPE_TSTEP); };
+    auto after = [](int c) { return c == PIPE_SLOTS - 1 ? 0 : c + 1; };
     if constexpr (STORED) {
         // no forward sweep
     } else if (wave == 0) {
@@ -910,18 +1007,19 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
         int c = 0;
         for (int32_t k = 0; k < A.K; ++k) {
             const int32_t target = A.ns[k];
+            Chunks chunks(TAN ? target - step : 0);
             while (step < target) {
-                const int32_t n = chunk(step, target);
+                const int32_t n = TAN ? chunks.next() : min(target - step, L - step % L);
                 if (ADJ && step % L == 0 && (lane & 3) == 0 && i < D.m) {
 #pragma unroll
                     for (int d = 0; d < 6; ++d)
                         Q.work[((int64_t)(step / L) * 6 + d) * Q.wld + g] = X[d];
                 }
                 if (TAN) {
-                    pipe_produce(A, n, X, ring + (c & 1) * (PIPE_FWD * PIPE_STEP), pp, false);
-                    pipe_put_state(xend, c & 1, pp, X);
+                    pipe_positions(A, n, X, tslot(c), pp);
+                    if (step + n == target) pipe_put_state(xend, c, pp, X);
                     __syncthreads();
-                    ++c;
+                    c = after(c);
                 } else {
                     rk4_steps_split<4>(A, n, X);
                 }
@@ -932,8 +1030,24 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
                 __syncthreads();
             }
         }
+        __syncthreads();   // (ADJ: the others are done with the forward sweep's data)
         if (!ADJ) return;
-        __syncthreads();   // the others are done with the forward sweep's data
+    } else if (TAN && wave == 3) {
+        int32_t step = 0;
+        int c = 0;
+        __syncthreads();
+        for (int32_t k = 0; k < A.K; ++k) {
+            const int32_t target = A.ns[k];
+            Chunks chunks(target - step);
+            while (step < target) {
+                const int32_t n = chunks.next();
+                pipe_jacobians(A, n, tslot(c));
+                __syncthreads();
+                c = after(c);
+                step += n;
+            }
+        }
+        return;
     } else if (TAN) {
         const int cl = min(lane & 7, 5);   // column (lanes 6 and 7 repeat the last)
         const double is = sqrt(A.w);       // 1 / sigma
@@ -947,25 +1061,27 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
             N[d] = 0.0;
         }
         int32_t step = 0;
-        int c = 0;
+        int c = 0, last = 0;
+        __syncthreads();
         for (int32_t k = 0; k < A.K; ++k) {
             const int32_t target = A.ns[k];
+            Chunks chunks(target - step);
             while (step < target) {
-                const int32_t n = chunk(step, target);
+                const int32_t n = chunks.next();
                 __syncthreads();
-                const double2 *slot = ring + (c & 1) * (PIPE_FWD * PIPE_STEP);
-                auto advance = [&](const PipeRow &r) {
-                    JacData J[4];
-                    r.jac(A, J);
-                    const GMat G[4] = {gmat(J[0]), gmat(J[1]), gmat(J[2]), gmat(J[3])};
+                const double2 *slot = tslot(c) + pp;
+                for (int32_t j = 0; j < n; ++j, slot += PIPE_TSTEP) {
+                    GMat G[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const double2 a = slot[3 * i * PIPE_P], b = slot[(3 * i + 1) * PIPE_P],
+                                      d = slot[(3 * i + 2) * PIPE_P];
+                        G[i] = GMat{a.x, a.y, b.x, b.y, d.x, d.y};
+                    }
                     tangent_column(G, A.h, A.h2, A.h6, u);
-                };
-                for (int32_t j = 0; j < n; ++j, slot += PIPE_STEP) {
-                    PipeRow r;
-                    r.get(slot, pp);
-                    advance(r);
                 }
-                ++c;
+                last = c;
+                c = after(c);
                 step += n;
             }
             // residuals and their rows of J at this observation
@@ -973,7 +1089,7 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
             if (step == 0)
                 load_state(B.x, B.ld, g, X);
             else
-                pipe_get_state(xend, (c - 1) & 1, pp, X);
+                pipe_get_state(xend, last, pp, X);
 #pragma unroll
             for (int d = 0; d < 6; ++d) su[d] = u[d];
             const double *row = A.tab + (int64_t)k * TAB_W;
@@ -1156,7 +1272,7 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
 }
 
 template <bool SINGLE, bool TAN, bool ADJ>
-__global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, SwarmArrays B, PipeArgs Q)
+__global__ __launch_bounds__(TAN ? 256 : 128) void k_sens_pipe(ProbDesc d0, SwarmArrays B, PipeArgs Q)
 {
     pipe_body<SINGLE, TAN, ADJ>(blockIdx.x, d0, B, Q);
 }
@@ -1166,8 +1282,10 @@ __global__ __launch_bounds__(TAN ? 192 : 128) void k_sens_pipe(ProbDesc d0, Swar
 // time, the gradient in odd ones, so that a launch of few problems lasts as
 // long as one sweep: one workgroup that went forward and then back took 2.13 ms
 // over 2,500 steps, this takes 1.09. With more, two workgroups share a compute
-// unit's LDS (segments of 8 steps): 384 problems 4.23 -> 2.42 ms.
-__global__ __launch_bounds__(192) void k_sens_stored(ProbDesc d0, SwarmArrays B, PipeArgs Q)
+// unit, its LDS (segments of 8 steps) and its registers (at most 256 to a lane:
+// with 261, which the compiler took by itself, 384 problems' refinement was 5%
+// longer): 384 problems 4.23 -> 1.77 ms.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_sens_stored(ProbDesc d0, SwarmArrays B, PipeArgs Q)
 {
     if (blockIdx.x & 1)
         pipe_body<false, false, true, true>(blockIdx.x >> 1, d0, B, Q);
@@ -1778,7 +1896,7 @@ hipError_t launch_sens_pipe(const ProbDesc &d0, const SwarmArrays &B, const Pipe
 {
     if (Q.seg < PIPE_SUB || Q.seg > PIPE_MAX_SEG || Q.seg % PIPE_SUB) return hipErrorInvalidValue;
     const unsigned lds = (unsigned)pipe_lds_bytes(Q.seg, tan, !tan);
-    const dim3 g((unsigned)grid), b(tan ? 192 : 128);
+    const dim3 g((unsigned)grid), b(tan ? 256 : 128);
     const bool single = B.desc == nullptr;
     if (tan) {
         if (single) hipLaunchKernelGGL((k_sens_pipe<true, true, false>), g, b, lds, st, d0, B, Q);
@@ -1796,7 +1914,7 @@ hipError_t launch_sens_stored(const ProbDesc &d0, const SwarmArrays &B, const Pi
     if (!B.desc || !Q.stored || Q.seg < PIPE_SUB || Q.seg > PIPE_MAX_SEG || Q.seg % PIPE_SUB)
         return hipErrorInvalidValue;
     const unsigned lds = (unsigned)pipe_lds_bytes(Q.seg, true, true);
-    hipLaunchKernelGGL(k_sens_stored, dim3((unsigned)(2 * grid)), dim3(192), lds, st, d0, B, Q);
+    hipLaunchKernelGGL(k_sens_stored, dim3((unsigned)(2 * grid)), dim3(256), lds, st, d0, B, Q);
     return hipGetLastError();
 }
 
