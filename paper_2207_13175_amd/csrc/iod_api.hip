@@ -1901,12 +1901,16 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     for (int64_t p = 0; p < P; ++p)
         plan.add(std::min<int64_t>(S.n_cand, L.descs[p].m), b->probs[p].ns[b->probs[p].K - 1]);
     plan.decide(b->simds);
+    // The trials' segments are powers of two, not those that the adjoint's own
+    // checkpoints call for; without checkpoints (a problem of more steps) any
+    // will do.
+    plan.seg = PIPE_SUB;
     if (plan.steps <= PIPE_MAX_STEPS) {
         // Checkpoints of the trials: the shortest segments (of which two
         // workgroups share a compute unit's LDS), or longer ones where many
         // problems' checkpoints would take gigabytes.
         const auto ckpt_rows = [&] { return ceil_div(plan.steps, plan.seg) + 1; };
-        for (plan.seg = PIPE_SUB; plan.seg < PIPE_MAX_SEG; plan.seg *= 2)
+        for (; plan.seg < PIPE_MAX_SEG; plan.seg *= 2)
             if (ckpt_rows() * 6 * ldp * (int64_t)sizeof(double) <= POLISH_CKPT_BYTES) break;
         rows = std::max(rows, ckpt_rows());
     }

@@ -126,3 +126,29 @@ def test_refinement_does_not_depend_on_the_batch(torch_dev, n_cand, kind):
         idx = np.arange(n) % each
         for a, b in zip(alone, refine(idx)):
             assert np.array_equal(a[idx], b, equal_nan=True), n
+
+
+@pytest.mark.parametrize("steps", [(2000, 4097), (1377, 3000, 4097, 4096), (4097,), (2473, 5000, 8)])
+def test_refinement_with_a_problem_beyond_the_pipelined_sweeps(torch_dev, steps):
+    """One problem of more than 4,096 steps: its batch refines without the
+    trials' checkpoints, whatever segments the other problems' own sweeps would
+    take, and every problem gets the bits that it gets in a batch of its own."""
+    wl = W.tiny(5)
+    rng = np.random.default_rng(list(steps))
+    t = [times(s, "grid")[1:] for s in steps]
+    obs = []
+    for tk in t:
+        P = oracle.Problem(wl.mu, wl.h, wl.sigma, wl.chief, tk, np.zeros((len(tk), 2)))
+        obs.append(oracle.predict(P, wl.truth) + rng.normal(0, wl.sigma, (len(tk), 2)))
+
+    def refine(idx):
+        n = len(idx)
+        b = iod.iod_create_batch([wl.mu] * n, [wl.chief] * n, [t[i] for i in idx], [obs[i] for i in idx],
+                                 [wl.sigma] * n, h=wl.h)
+        params = [iod.pso_params(0.7, 1.5, 1.5, 3, wl.lo, wl.hi, problem=int(i)) for i in idx]
+        return iod.iod_batch_solve_polished(b, params, np.full(n, 64), 2, top_k=16, n_cand=4, n_gn=3)
+
+    together = refine(range(len(steps)))
+    for i in range(len(steps)):
+        for a, b in zip(together, refine([i])):
+            assert np.array_equal(a[i], b[0], equal_nan=True), steps[i]
