@@ -61,14 +61,17 @@ __device__ __forceinline__ double rcp_from_roots(double D, double h1, double h2,
 
 // What certifies in-range results, from every D = D1 D2 and the residual e of
 // its reciprocal: D < 2^1000 and e < 2^-53, on the high words as integers
-// (which order as the values do where they matter: an infinite or NaN D is
-// above the range, and a NaN e, which is what a D too small for the
-// reciprocal or a zero D leaves, is above any residual). A NaN that came in
-// with the state may pass: the IEEE path returns NaN there as well. Two
-// three-way maxima per two values, 4 issue slots per RK4 step, where two
-// comparisons per value took 8. With the reciprocal above a step takes 262
-// slots instead of 274: an iteration of the single large swarm went from
-// 2.01 to 1.90 ms, and the uneven batch (two waves to a SIMD) gained 2%.
+// (which order as the values do for numbers and infinities; a NaN's sign bit,
+// set in those that this device makes, puts it below all of them, so NaNs need
+// a test of their own). A D too small for the reciprocal, whose seed overflows,
+// and a zero D leave a NaN reciprocal where IEEE division gives an infinity. It
+// makes every component of the acceleration NaN, and with it whatever the
+// caller hands to ok(): a value that the accelerations of all certified stages
+// have reached, such as a velocity after the steps. Two three-way maxima per
+// two values, 4 issue slots per RK4 step, where two comparisons per value took
+// 8, and one comparison per certified interval. With the reciprocal above a
+// step takes 262 slots instead of 274: an iteration of the single large swarm
+// went from 2.01 to 1.90 ms, and the uneven batch (two waves to a SIMD) gained 1%.
 struct Mark {
     double D, e;
 };
@@ -80,9 +83,9 @@ struct Cert {
         D = max(max(__double2hiint(a.D), __double2hiint(b.D)), D);
         e = max(max(__double2hiint(a.e), __double2hiint(b.e)), e);
     }
-    __device__ __forceinline__ bool ok() const
+    __device__ __forceinline__ bool ok(double reached) const
     {
-        return D < ((1023 + 1000) << 20) && e < ((1023 - 53) << 20);
+        return D < ((1023 + 1000) << 20) && e < ((1023 - 53) << 20) && !isnan(reached);
     }
 };
 
@@ -95,8 +98,8 @@ struct Cert {
 // correctly rounded.
 //
 // INRANGE = true uses the in-range sequences; the result is certified equal
-// to the IEEE one if the returned mark passes Cert. A residual that is a
-// number says that the reciprocal's seed neither overflowed nor lost bits
+// to the IEEE one if the returned mark passes Cert. A reciprocal that is a
+// number says that its seed neither overflowed nor lost bits
 // below (D < 2^1000), so D >= 2^-1024 and x1 x2 = D^(2/3) >= 2^-683. Both
 // radicands are then in range as well: r_j^2 < 2^-767 would need the other
 // one above 2^84, but the primaries are one unit apart, so r_j ~ 0 puts the
@@ -175,7 +178,7 @@ __device__ __forceinline__ void rk4(double mu, double mu1, bool fast, double h, 
     if (fast) {
         Cert cert;
         rk4_sum<true>(mu, mu1, h, h2, X, a, cert);
-        ok = cert.ok();
+        ok = cert.ok(a[5]);
     }
     if (!__all(ok)) {
         Cert ieee;
@@ -210,7 +213,7 @@ __device__ __forceinline__ void rk4_steps(const KArgs &A, int32_t n, double X[6]
 #pragma unroll
             for (int d = 0; d < 6; ++d) X[d] = fma(A.h6, a[d], X[d]);
         }
-        if (__all(cert.ok())) return;
+        if (__all(cert.ok(X[5]))) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
     }
@@ -412,7 +415,7 @@ __device__ __forceinline__ void rk4_steps_split(const KArgs &A, int32_t n, doubl
             step();
         }
         for (; j < n; ++j) step();
-        if (__all(cert.ok())) return;
+        if (__all(cert.ok(X[5]))) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
     }

@@ -566,7 +566,7 @@ __global__ __launch_bounds__(64) void k_chief_stages(const ProbDesc *__restrict_
                 sink.pos += 12;
             }
             WaveScope::sync();
-            if (A.fast && __all(cert.ok())) {
+            if (A.fast && __all(cert.ok(X[5]))) {
                 if (lane < 4 * n) chief_row(A.mu, A.mu1, pos + 3 * lane, cst + (int64_t)step * CST_STEP + lane * CST_W);
             } else {
 #pragma unroll

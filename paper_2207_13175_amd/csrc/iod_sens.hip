@@ -194,7 +194,8 @@ __device__ __forceinline__ void stages_jac(double mu, double mu1, bool fast, dou
     if (fast) {
         Cert cert;
         stages_jac<true, ROOTS>(mu, mu1, h, h2, h6, X, J, Y, cert);
-        ok = cert.ok();
+        // (a NaN of stage 1 or 2 reaches the position of stage 3 or 4)
+        ok = cert.ok(Y ? Y[5] : J[2].cs + J[3].cs);
     }
     if (!__all(ok)) {
         Cert ieee;
@@ -408,7 +409,7 @@ __device__ __forceinline__ void grad_body(int64_t blk, const ProbDesc &d0, const
                     for (int d = 0; d < 6; ++d) Z[d] = fma(A.h6, q[d], Z[d]);
                 }
             }
-            ok = b - a < 2 || cert.ok();
+            ok = b - a < 2 || cert.ok(Z[5]);
         }
         if (!__all(ok)) {
             for (int32_t j = a; j < b; ++j) {
@@ -761,7 +762,7 @@ __device__ __forceinline__ void pipe_positions(const KArgs &A, int32_t n, double
             step();
         }
         for (; i < n; ++i) step();
-        if (__all(cert.ok())) return;
+        if (__all(cert.ok(X[5]))) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
     }
@@ -803,7 +804,7 @@ __device__ __forceinline__ void pipe_jacobians(const KArgs &A, int32_t n, double
             const Mark m = rhs_jac<true, true>(A.mu, A.mu1, s, f, J);
             cert.add(m, m);
         }
-        if (!A.fast || !__all(cert.ok())) rhs_jac<false, true>(A.mu, A.mu1, s, f, J);
+        if (!A.fast || !__all(cert.ok(J.cs))) rhs_jac<false, true>(A.mu, A.mu1, s, f, J);
         const GMat G = gmat(J);
         cell[0] = make_double2(G.g00, G.g01);
         cell[PIPE_P] = make_double2(G.g02, G.g11);
@@ -847,7 +848,7 @@ __device__ __forceinline__ void pipe_produce(const KArgs &A, int32_t n, double X
             step();
         }
         for (; j < n; ++j) step();
-        if (__all(cert.ok())) return;
+        if (__all(cert.ok(X[5]))) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
     }
@@ -1412,7 +1413,7 @@ __device__ __forceinline__ void trial_steps(const KArgs &A, int32_t from, int32_
                 split_step<LPP>(A.mu, A.mu1, A.h, A.h2, A.h6, X, cert, none);
             }
         });
-        if (__all(cert.ok())) return;
+        if (__all(cert.ok(X[5]))) return;
 #pragma unroll
         for (int d = 0; d < 6; ++d) X[d] = X0[d];
     }

@@ -81,3 +81,26 @@ def test_mantissa_of_all_ones():
     assert (r1 * np.sqrt(r1)) * (r2 * np.sqrt(r2)) == 2.0 - 2.0 ** -52
     xs = np.concatenate([p, [0.0, 0.1, 0.0]])[None]
     assert np.array_equal(first_step(0.5, xs), reference(0.5, xs))
+
+
+@pytest.mark.parametrize("m", [1, 20000, 40000])
+def test_last_stage_next_to_a_primary(m):
+    """A step whose fourth stage alone comes within 2^-345 to 2^-350 of the second
+    primary (a tiny mass: x and y are chosen such that the stage lands on its x
+    and y exactly), where 1 / (D1 D2) is infinite. The position after the step is
+    a number and the velocity along z an infinity, not NaN, with one, two or
+    four lanes per particle."""
+    import torch
+    h, mu = 2.0 ** -10, 1e-300
+    xs = np.array([[1.000739122972962, 0.0009516530515198243, 2.0 ** e, -0.7559108123501284,
+                    -0.9752318481629676, 0.0] for e in (-350, -345, -341, -330)])
+    want = np.stack([oracle.propagate(mu, h, x, [h])[0] for x in xs])
+    assert np.array_equal(want[:, 5] == -np.inf, [True, True, False, False])
+    assert np.all(np.isfinite(want[:, :3]))
+    hd = iod.iod_create(mu, [0.9, 0.1, 0, 0, 0.2, 0], [h], np.zeros((1, 2)), 1e-5, h=h)
+    for x, w in zip(xs, want):
+        d = torch.from_numpy(np.tile(x[:, None], (1, m))).cuda()
+        out = torch.zeros((1, 6, m), dtype=torch.float64, device="cuda")
+        iod.iod_propagate(hd, d, m, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out[0].cpu().numpy(), np.tile(w[:, None], (1, m)), equal_nan=True), (x, w)
