@@ -844,6 +844,18 @@ __device__ __forceinline__ const ProbDesc &locate(const ProbDesc &d0, const Swar
 // Launch helpers.
 // ---------------------------------------------------------------------------
 
+// N s_nop (4 bytes each) at a kernel's entry shift every later instruction of
+// the kernel, and so where its loops start (each kernel's code starts on a
+// 256-byte boundary, so a kernel's padding moves nothing else).
+template <int N>
+__device__ __forceinline__ void entry_pad()
+{
+    if constexpr (N > 0) {
+        __asm__ volatile("s_nop 0");
+        entry_pad<N - 1>();
+    }
+}
+
 __device__ __forceinline__ bool closed(const Gate &g)
 {
     return g.count && !(*g.count > g.above && *g.count <= g.upto);

@@ -295,18 +295,6 @@ __device__ __forceinline__ void walk32_rel(const KArgs &A, float D[6], float C[6
     }
 }
 
-// N s_nop (4 bytes each) at a kernel's entry shift every later instruction of
-// the kernel, and so where its loops start (each kernel's code starts on a
-// 256-byte boundary, so a kernel's padding moves nothing else).
-template <int N>
-__device__ __forceinline__ void entry_pad()
-{
-    if constexpr (N > 0) {
-        __asm__ volatile("s_nop 0");
-        entry_pad<N - 1>();
-    }
-}
-
 // Entry padding of the mixed iteration kernel per (block size,
 // formulation). The absolute formulation's iteration on the uneven batch
 // takes 15.8-16.5 ms when its RK4 loop starts at 8 or 16 mod 32 bytes and

@@ -74,7 +74,9 @@ __device__ __forceinline__ double rcp_inrange(double b)
 // e2, with no further square root or division. ROOTS: the reciprocal from the
 // inverse roots (as rhs), else from the hardware's seed, which frees the roots
 // early: the one-thread tangent sweep, at its register limit, is 3% faster
-// with it (65,536 particles over 2,000 steps: 4.20 against 4.35 ms).
+// with it (65,536 particles over 2,000 steps: 4.20 against 4.35 ms). That one is
+// the compiler's own sequence for every D in the range, so its mark carries no
+// residual; a D below the range shows in its NaN (Cert).
 template <bool INRANGE, bool ROOTS>
 __device__ __forceinline__ Mark rhs_jac(double mu, double mu1, const double s[6], double f[6],
                                         JacData &J)
@@ -651,12 +653,17 @@ __device__ __forceinline__ void normal_body(int64_t blk, const ProbDesc &d0,
     }
 }
 
+// The single problem's instances of the sweep are fastest when their step loop
+// starts on a multiple of 8 bytes: 65,536 particles over 2,000 steps 4.05-4.08 ms,
+// and 4.10-4.20 at the offsets between, with the same instructions; the padding
+// puts them there (the placement test names one that has left).
 template <int BS, int PLACE>
 __global__ __launch_bounds__(BS) void k_normal(ProbDesc d0, SwarmArrays B, Lanes L,
                                                double *__restrict__ chi2, double *__restrict__ jtj,
                                                double *__restrict__ jtr, double *__restrict__ jrows,
                                                int64_t jstride, int64_t jld)
 {
+    if constexpr (PLACE == PLACE_SINGLE) entry_pad<1>();
     normal_body<BS, PLACE>(blockIdx.x, d0, B, L, chi2, jtj, jtr, jrows, jstride, jld);
 }
 

@@ -76,3 +76,21 @@ def test_absolute_iteration_loops_start_at_fast_offsets(tmp_path):
     off = {re.search(r"ILi(\d+)E", f).group(1): a % 32 for f, a in absolute.items()}
     bad = {bs: o for bs, o in off.items() if o not in FAST}
     assert not bad, f"k_mixed_iter<BS, false> hot loop at {bad} mod 32 (fast: {sorted(FAST)})"
+
+
+def test_tangent_loops_start_on_multiples_of_8(tmp_path):
+    """The one-thread tangent sweep of a single problem (k_normal) loses 1-3%
+    where its step loop starts between multiples of 8 bytes; entry_pad puts it
+    on one."""
+    hipcc, bundler, objdump = _tools()
+    obj, co = tmp_path / "sens.o", tmp_path / "sens.co"
+    subprocess.run([hipcc, *B.ARCH, *B.FLAGS, *dict(B.UNITS)["iod_sens.hip"], "--offload-device-only",
+                    "-c", "-o", str(obj), os.path.join(B.CSRC, "iod_sens.hip")],
+                   check=True, capture_output=True)
+    subprocess.run([bundler, "--unbundle", "--type=o", f"--input={obj}",
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--output={co}"],
+                   check=True, capture_output=True)
+    dis = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(co)], check=True,
+                         capture_output=True, text=True).stdout
+    off = {f: a % 8 for f, a in _hot_loops(dis).items() if re.search(r"k_normalILi\d+ELi0E", f)}
+    assert len(off) == 3 and not any(off.values()), off

@@ -104,3 +104,46 @@ def test_last_stage_next_to_a_primary(m):
         iod.iod_propagate(hd, d, m, out)
         torch.cuda.synchronize()
         assert np.array_equal(out[0].cpu().numpy(), np.tile(w[:, None], (1, m)), equal_nan=True), (x, w)
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.25, 0.5])
+def test_tangent_of_many_particles_at_the_edges_of_the_certificate(mu):
+    """The one-thread tangent sweep (many particles) takes its reciprocals from
+    the hardware's seed and is certified by their residuals alone. States next to
+    the second primary and far out (mu = 0: next to where it would be, with no
+    attraction, so that a tiny D goes with finite results) and the D with a
+    mantissa of all ones, one to a wave, against the pipelined sweep."""
+    import torch
+    rng = np.random.default_rng(9)
+    xs = []
+    for e in (-1, -60, -126, -200, -253, -254, -255, -300, -333, -334, -340, -341, -342, -350, -384, -400,
+              30, 110, 166, 167, 168, 169, 170, 171, 172, 250, 340):
+        s = rng.normal(0, 1, 6)
+        s[:3] *= 2.0 ** e
+        s[3:] *= 0.1
+        if e < 0:
+            s[0] += 1.0 - mu
+            if e < -60:   # (the offset in x is lost)
+                s[0] = 1.0 - mu
+        xs.append(s)
+    xs.append(np.array([1.0 - mu, 0.0, 0.0, 0.0, 0.1, 0.0]))
+    if mu == 0.5:
+        xs.append(np.concatenate([all_ones_state()[0], [0.0, 0.1, 0.0]]))
+    n, many = len(xs), 24640
+    x = np.tile(np.array([0.9, 0.12, 0.01, 0.0, 0.1, 0.0]), (many, 1))
+    x[:64 * n:64] = xs
+    t = np.array([0.0, 1e-3, 2.4e-3, 4e-3])
+    h = iod.iod_create(mu, [0.9, 0.1, 0, 0, 0.2, 0], t, np.zeros((len(t), 2)), 1e-5, h=1e-3, cost_mode=1)
+
+    def normal(x):
+        m = len(x)
+        kw = dict(dtype=torch.float64, device="cuda")
+        out = [torch.zeros((k, m), **kw) for k in (1, 21, 6)]
+        iod.iod_normal_eq(h, torch.from_numpy(np.ascontiguousarray(x.T)).cuda(), m, out[0][0], out[1], out[2])
+        torch.cuda.synchronize()
+        return [o.cpu().numpy() for o in out]
+
+    got = [o[:, :64 * n:64] for o in normal(x)]
+    for i, s in enumerate(xs):   # one at a time: each decides its own wave's path
+        for a, b in zip(got, normal(s[None])):
+            assert np.array_equal(a[:, i], b[:, 0], equal_nan=True), (i, s)
