@@ -10,17 +10,16 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <functional>
 #include <mutex>
 #include <new>
 #include <numeric>
-#include <utility>
 #include <vector>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "../../include/iod.h"
 #include "iod_launch.h"
+#include "iod_plan.h"
 
 using namespace iodk;
 
@@ -79,7 +78,6 @@ bool finite6(const double *v)
 constexpr int64_t MAX_M = (int64_t)1 << 40;
 constexpr int DEFAULT_BLOCK = 256;
 
-int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t round64(int64_t a) { return ceil_div(a, 64) * 64; }
 
 // Host-side description of one problem, validated, with its observation
@@ -282,94 +280,6 @@ int check_pso(const iod_pso_params *p)
     if (p->tol > 0.0 && p->tol_lag < 1) return fail(IOD_EINVAL, "tol_lag must be >= 1");
     return IOD_OK;
 }
-
-// Lanes per particle of the FP64 propagations. A wave of one, two or four
-// lanes per particle holds 64, 32 or 16 of them, and its steps take about
-// SPLIT_COST times those of one lane per particle (measured on 500 steps to
-// 10 observations: 243, 184 and 165 us). So more lanes shorten a launch while
-// its waves have a SIMD each, and lengthen it once they share them: take the
-// number with the shortest estimate; several lanes must gain 5%. The estimate
-// is the largest of the longest wave, the SIMDs' mean load, and, since a wave
-// is not divided, n times the n-th wave that some SIMD must take: the
-// ((n - 1) simds + 1)-th longest (32,769 particles of one problem on 1,024
-// SIMDs: 316 us with two lanes each, 252 us with one).
-constexpr double SPLIT_COST[3] = {1.0, 0.76, 0.68};
-
-struct SplitLoad {
-    std::vector<std::pair<int64_t, int64_t>> work;   // (steps, particles) of each problem
-    void add(int64_t m, int64_t steps)
-    {
-        if (m > 0) work.emplace_back(std::max<int64_t>(steps, 1), m);
-    }
-    double estimate(int l, int simds) const
-    {
-        double total = 0.0, t = 0.0;
-        int64_t waves = 0;
-        for (const auto &w : work) {   // longest first
-            const int64_t n = ceil_div(w.second, 64 >> l);
-            // waves waves + 1 .. waves + n are of this length
-            t = std::max(t, (double)((waves + n - 1) / simds + 1) * (double)w.first);
-            waves += n;
-            total += (double)n * (double)w.first;
-        }
-        return SPLIT_COST[l] * std::max(t, total / simds);
-    }
-    // Estimates for at most two workgroups of bs threads to their SIMDs, longest
-    // first (work in that order; INFINITY if there are more). alone: one after
-    // the other, the second ones, longest first, where the first ends first, and
-    // 10% longer, since nothing fills a wave's waits. Else side by side in the
-    // order of dispatch, so that the longest has the longest of the second ones
-    // beside it.
-    double paired(int l, int bs, int simds, bool alone) const
-    {
-        const size_t places = (size_t)std::max(1, simds / (bs / 64));
-        std::vector<int64_t> len;
-        for (const auto &w : work) {
-            const int64_t n = ceil_div(w.second, bs >> l);
-            if (len.size() + (size_t)n > 2 * places) return INFINITY;
-            len.insert(len.end(), (size_t)n, w.first);
-        }
-        if (len.empty()) return INFINITY;
-        if (len.size() <= places) return SPLIT_COST[l] * (double)len[0];
-        if (!alone) return SPLIT_COST[l] * (double)(len[0] + len[places]);
-        int64_t t = len[0];
-        for (size_t j = places; j < len.size(); ++j) t = std::max(t, len[j] + len[2 * places - 1 - j]);
-        return 1.1 * SPLIT_COST[l] * (double)t;
-    }
-    // Lanes of a batch's FP64 swarm launches, whose workgroups of one lane per
-    // particle have bs threads; solo: they run one wave to a SIMD.
-    int swarm_lanes(int bs, int simds, bool &solo)
-    {
-        int best = lanes(simds);
-        const double side = paired(best >> 1, best > 1 ? SPLIT_BS : bs, simds, false);
-        double t0 = side < INFINITY ? side : estimate(best >> 1, simds);
-        solo = false;
-        for (int l = 0; l < 3; ++l) {
-            const double t = paired(l, l ? SPLIT_BS : bs, simds, true);
-            if (t <= t0) {
-                best = 1 << l;
-                t0 = t;
-                solo = true;
-            }
-        }
-        return best;
-    }
-    // two: whether two lanes per particle are to be had
-    int lanes(int simds, bool two = true)
-    {
-        std::sort(work.begin(), work.end(), std::greater<std::pair<int64_t, int64_t>>());
-        int best = 1;
-        double t0 = 0.95 * estimate(0, simds);
-        for (int l = two ? 1 : 2; l < 3; ++l) {
-            const double t = estimate(l, simds);
-            if (t < t0) {
-                best = 1 << l;
-                t0 = t;
-            }
-        }
-        return best;
-    }
-};
 
 // SIMDs of the current device (four per compute unit).
 int device_simds(int device)
@@ -1651,41 +1561,6 @@ int64_t adj_rows(const HostProblem &P)
 constexpr int64_t POLISH_COLS = 42;
 // Most scratch for which the trials' checkpoints are the closest.
 constexpr int64_t POLISH_CKPT_BYTES = (int64_t)2 << 30;
-
-// The problems of a sensitivity launch, and which of its sweeps are pipelined.
-// The pipelined form shortens a step about four times (normal equations) or
-// three times (gradient) while its workgroups (PIPE_P particles of one
-// problem) have a compute unit each, and the launch grows with every further
-// one to a unit: the normal equations by about half, the gradient by a third
-// if their LDS lets several share a unit, else by its whole time.
-// Over 2,000 steps the normal equations take 0.84, 1.20, 1.87, 2.29, 2.78 and
-// 3.27 ms with one to six workgroups to a unit against 4.1 ms otherwise; the
-// gradient 1.59, 3.14 and 4.7 ms against 4.7 ms, and over 500 steps (two share a
-// unit) 0.45, 0.60 and 0.95 ms against 1.2 ms.
-struct PipePlan {
-    int64_t groups = 0, steps = 0, grid = 0;
-    int32_t sub = 1, seg = PIPE_SUB;
-    bool tan = false, adj = false;
-    void add(int64_t m, int64_t s)
-    {
-        if (m < 1) return;
-        groups += ceil_div(m, PIPE_P);
-        steps = std::max(steps, s);
-        if (s <= PIPE_MAX_STEPS) seg = std::max(seg, pipe_segment((int32_t)s));
-    }
-    // the most workgroups for which the gradient's sweep is pipelined
-    int64_t adj_limit(int simds, bool tan_too = false) const
-    {
-        const int64_t shared = (160 << 10) / pipe_lds_bytes(seg, tan_too, true);
-        return (shared > 1 ? 3 : 2) * (simds / 4);
-    }
-    void decide(int simds)
-    {
-        if (steps > PIPE_MAX_STEPS) return;
-        tan = groups <= 6 * (simds / 4);
-        adj = groups <= adj_limit(simds);
-    }
-};
 
 // Damped Gauss-Newton on the columns of B.x (in place): the normal matrix
 // from the forward tangent, the gradient from the discrete adjoint; d0 / the
