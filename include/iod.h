@@ -572,7 +572,12 @@ int iod_batch_polish(iod_batch *b, double *x, int64_t ld, const int64_t *m, int3
  * chi2 is too noisy to decide the last steps along weakly observed
  * directions; the steps themselves are not). Outputs (host): best_states
  * [P][6], best_chi2 [P] (may be NULL) and best_costs [P] (the problem's own
- * cost mode, may be NULL). Synchronous. */
+ * cost mode, may be NULL). Synchronous. The batch keeps the refinement's
+ * scratch: 64 columns per problem of 42 + 6 r doubles, with S the steps of
+ * the longest problem r = ceil(S/64) + 64, and, up to S = 4,096, at least
+ * ceil(S/8) + 1 (checkpoints every 8 steps, every 16 or 32 where they would
+ * take more than 2 GiB). Where device memory does not suffice, the
+ * checkpoints lie further apart, or there are none: the same results, later. */
 int iod_batch_solve_polished(iod_batch *b, const iod_pso_params *params, const int64_t *m,
                              int64_t n_iter, int32_t top_k, int32_t n_cand, int32_t n_gn,
                              double *best_states, double *best_chi2, double *best_costs);

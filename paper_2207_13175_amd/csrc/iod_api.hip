@@ -1559,8 +1559,6 @@ int64_t adj_rows(const HostProblem &P)
 // Doubles of polish workspace per column besides the adjoint rows:
 // jtj 21, jtr 6, grad 6, trial 6, chi2 at trial 1, damping 1, cost 1.
 constexpr int64_t POLISH_COLS = 42;
-// Most scratch for which the trials' checkpoints are the closest.
-constexpr int64_t POLISH_CKPT_BYTES = (int64_t)2 << 30;
 
 // Damped Gauss-Newton on the columns of B.x (in place): the normal matrix
 // from the forward tangent, the gradient from the discrete adjoint; d0 / the
@@ -1653,7 +1651,7 @@ int polish_trials_run(const ProbDesc &d0, SwarmArrays PB, const int32_t *n, int6
     // exits at once) unless even all problems are few.
     int32_t *problems = (int32_t *)(live_count + 1);
     const int32_t sub = plan.sub;
-    const bool pipe = plan.steps <= PIPE_MAX_STEPS;
+    const bool pipe = plan.ckpt;
     Gate few, many;
     few.count = many.count = problems;
     few.upto = many.above = pipe ? (int32_t)(plan.adj_limit(simds, true) / sub) : 0;
@@ -1776,19 +1774,6 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     for (int64_t p = 0; p < P; ++p)
         plan.add(std::min<int64_t>(S.n_cand, L.descs[p].m), b->probs[p].ns[b->probs[p].K - 1]);
     plan.decide(b->simds);
-    // The trials' segments are powers of two, not those that the adjoint's own
-    // checkpoints call for; without checkpoints (a problem of more steps) any
-    // will do.
-    plan.seg = PIPE_SUB;
-    if (plan.steps <= PIPE_MAX_STEPS) {
-        // Checkpoints of the trials: the shortest segments (of which two
-        // workgroups share a compute unit's LDS), or longer ones where many
-        // problems' checkpoints would take gigabytes.
-        const auto ckpt_rows = [&] { return ceil_div(plan.steps, plan.seg) + 1; };
-        for (; plan.seg < PIPE_MAX_SEG; plan.seg *= 2)
-            if (ckpt_rows() * 6 * ldp * (int64_t)sizeof(double) <= POLISH_CKPT_BYTES) break;
-        rows = std::max(rows, ckpt_rows());
-    }
     // trials per candidate: the free lanes of the problem's 64-lane wave, at most 8
     const int32_t T = std::max(1, std::min(8, 64 / S.n_cand));
     // rows of J of every candidate: max over problems of K R (R = 3 with ranges, else 2)
@@ -1800,7 +1785,6 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     HIP_TRY(Q.cand.ensure((size_t)P * S.n_cand * sizeof(int32_t)));
     HIP_TRY(Q.x.ensure((size_t)6 * ldp * sizeof(double)));
     HIP_TRY(Q.chi.ensure((size_t)ldp * sizeof(double)));
-    HIP_TRY(Q.work.ensure((size_t)(POLISH_COLS + rows * 6) * ldp * sizeof(double)));
     HIP_TRY(Q.order.ensure((size_t)2 * P * sizeof(int32_t)));
     HIP_TRY(Q.stored.ensure((size_t)ldp * sizeof(int32_t)));
     HIP_TRY(Q.best.ensure((size_t)6 * P * sizeof(double)));
@@ -1857,6 +1841,14 @@ int polish_stage_run(iod_batch *b, const BatchLayout &L, const SwarmArrays &B,
     HIP_TRY(Q.lanes.upload(lanes, st));
     HIP_TRY(Q.live.ensure(std::max<size_t>(lanes.size(), 2) * sizeof(int32_t)));
     HIP_TRY(Q.live_count.ensure(2 * sizeof(int64_t)));   // live pairs, active problems
+    // the scratch last, so that its checkpoints take only what the rest leaves
+    hipError_t se = hipSuccess;
+    plan.trial_scratch(rows, 6 * ldp * (int64_t)sizeof(double), [&](int64_t n) {
+        se = Q.work.ensure((size_t)(POLISH_COLS + n * 6) * ldp * sizeof(double));
+        if (se == hipErrorOutOfMemory) (void)hipGetLastError();   // (not the next launch's)
+        return se != hipErrorOutOfMemory;
+    });
+    if (se != hipSuccess) return hip_fail(se, "refinement scratch");
     // the retirement flags start cleared on every call (the kernels change them)
     HIP_TRY(hipMemsetD32Async((hipDeviceptr_t)Q.act.p, 1, (size_t)P, st));
     HIP_TRY(hipMemsetAsync(Q.done.p, 0, (size_t)ldp * sizeof(int32_t), st));

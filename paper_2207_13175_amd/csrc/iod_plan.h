@@ -104,6 +104,9 @@ struct SplitLoad {
     }
 };
 
+// Most scratch for which the trials' checkpoints are the closest.
+constexpr int64_t TRIAL_CKPT_BYTES = (int64_t)2 << 30;
+
 // The problems of a sensitivity launch, and which of its sweeps are pipelined.
 // The pipelined form shortens a step about four times (normal equations) or
 // three times (gradient) while its workgroups (PIPE_P particles of one
@@ -118,6 +121,7 @@ struct PipePlan {
     int64_t groups = 0, steps = 0, grid = 0;
     int32_t sub = 1, seg = PIPE_SUB;
     bool tan = false, adj = false;
+    bool ckpt = false;   // the refinement's trials leave checkpoints
     void add(int64_t m, int64_t s)
     {
         if (m < 1) return;
@@ -136,6 +140,30 @@ struct PipePlan {
         if (steps > PIPE_MAX_STEPS) return;
         tan = groups <= 6 * (simds / 4);
         adj = groups <= adj_limit(simds);
+    }
+    // Scratch of the batched refinement and the segments of its trials'
+    // checkpoints: states every seg steps and after the last one, in the rows
+    // (of row_bytes) that the one-thread adjoint has `rows` of. The shortest
+    // segments are the fastest (two workgroups share a compute unit's LDS); longer
+    // ones where many problems' checkpoints would take gigabytes, and where the
+    // scratch cannot be had: fits(n) says whether there is memory for n rows. The
+    // last resort is the adjoint's own rows, without checkpoints. Returns
+    // whether something fitted. seg is a power of two whatever the outcome (the
+    // trials' kernel needs one), not what add() found for the adjoint's own.
+    template <class Fits>
+    bool trial_scratch(int64_t rows, int64_t row_bytes, Fits fits)
+    {
+        const auto ckpt_rows = [&] { return ceil_div(steps, seg) + 1; };
+        seg = PIPE_SUB;
+        ckpt = steps <= PIPE_MAX_STEPS;
+        if (ckpt) {
+            while (seg < PIPE_MAX_SEG && ckpt_rows() * row_bytes > TRIAL_CKPT_BYTES) seg *= 2;
+            for (; seg <= PIPE_MAX_SEG; seg *= 2)
+                if (fits(std::max(rows, ckpt_rows()))) return true;
+            seg = PIPE_SUB;
+            ckpt = false;
+        }
+        return fits(rows);
     }
 };
 

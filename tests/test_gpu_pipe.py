@@ -152,3 +152,31 @@ def test_refinement_with_a_problem_beyond_the_pipelined_sweeps(torch_dev, steps)
     for i in range(len(steps)):
         for a, b in zip(together, refine([i])):
             assert np.array_equal(a[i], b[0], equal_nan=True), steps[i]
+
+
+@pytest.mark.parametrize("problems", [2048, 4096])
+def test_refinement_with_longer_checkpoint_segments(torch_dev, problems):
+    """Checkpoints every 8 steps would take more than 2 GiB: the trials leave them
+    every 16 (2,048 problems of up to 3,000 steps) or 32 steps (4,096). The
+    packed sweeps begin, and as the short problems retire, those from the
+    checkpoints take over; each problem's bits are those of a small batch."""
+    wl = W.tiny(5)
+    rng = np.random.default_rng(problems)
+    steps = [3000, 2993, 120, 121, 122, 123, 124, 125, 126, 127, 128, 129]
+    t = [times(s, "grid")[1:] for s in steps]
+    obs = []
+    for tk in t:
+        P = oracle.Problem(wl.mu, wl.h, wl.sigma, wl.chief, tk, np.zeros((len(tk), 2)))
+        obs.append(oracle.predict(P, wl.truth) + rng.normal(0, wl.sigma, (len(tk), 2)))
+
+    def refine(idx):
+        n = len(idx)
+        b = iod.iod_create_batch([wl.mu] * n, [wl.chief] * n, [t[i] for i in idx], [obs[i] for i in idx],
+                                 [wl.sigma] * n, h=wl.h)
+        params = [iod.pso_params(0.7, 1.5, 1.5, 3, wl.lo, wl.hi, problem=int(i)) for i in idx]
+        return iod.iod_batch_solve_polished(b, params, np.full(n, 64), 2, top_k=16, n_cand=2, n_gn=30)
+
+    few = refine(range(len(steps)))
+    idx = np.concatenate([np.arange(problems - 64) % 10 + 2, np.arange(64) % len(steps)])
+    for a, b in zip(few, refine(idx)):
+        assert np.array_equal(a[idx], b)
