@@ -120,8 +120,9 @@ typedef struct {
 #define IOD_ORDER_PROBLEM 1       /* workgroups in problem order */
 
 /* Swarm state in caller-owned device memory. Fill the pointers, ld and m,
- * then call iod_swarm_init; the library keeps `iter` (iterations done) and
- * `block` (the workgroup size fixed at initialisation). */
+ * then call iod_swarm_init; the library keeps `iter` (iterations done),
+ * `block` and `reserved` (the workgroup size and the lanes per particle, fixed
+ * at initialisation: the layout of work depends on them). */
 typedef struct {
     double *x;        /* device [6][ld] current positions */
     double *v;        /* device [6][ld] velocities */
@@ -135,7 +136,7 @@ typedef struct {
     int64_t m;        /* particles, >= 1 */
     int64_t iter;     /* iterations completed since iod_swarm_init (set by the library) */
     int32_t block;    /* workgroup size used by this swarm (set by iod_swarm_init) */
-    int32_t reserved;
+    int32_t reserved; /* lanes per particle used by this swarm (set by iod_swarm_init) */
 } iod_swarm;
 
 typedef struct iod_batch iod_batch;

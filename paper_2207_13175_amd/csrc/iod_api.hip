@@ -657,9 +657,11 @@ int check_swarm(const iod_swarm *s, bool need_init)
 void single_view(const iod_handle *h, const iod_swarm *s, const iod_pso_params *p, ProbDesc &D,
                  SwarmArrays &B)
 {
-    // the lanes per particle follow from the problem, m and the device alone,
-    // so that every call on the swarm finds the slots of the one before
-    const int lanes = h->lanes(s->m);
+    // The lanes per particle shape the slots, so every call on the swarm takes
+    // those of its initialisation, also where another device, with other compute
+    // units, continues it. A view that a caller filled anew without them has
+    // those of this device.
+    const int lanes = s->reserved == 1 || s->reserved == 2 || s->reserved == 4 ? s->reserved : h->lanes(s->m);
     const int32_t block = lanes > 1 ? SPLIT_BS / lanes : s->block;
     const int64_t nslots = ceil_div(s->m, block);
     D = desc_of(h->kargs(), h->P.chief, p);
@@ -895,6 +897,7 @@ int iod_swarm_init(iod_handle *h, iod_swarm *s, const iod_pso_params *p, void *s
     if (rc != IOD_OK) return rc;
     s->iter = -1;
     s->block = block_of(h->cfg);
+    s->reserved = h->lanes(s->m);
     ProbDesc D;
     SwarmArrays B;
     single_view(h, s, p, D, B);

@@ -141,3 +141,45 @@ def test_uneven_batches_do_not_depend_on_their_neighbours(block, top):
     for i in range(n):
         for a, w in zip(solve(np.array([i])), whole):
             assert np.array_equal(a[0], w[i]), i
+
+
+@pytest.mark.parametrize("m,lanes", [(200, 4), (20000, 2), (40000, 1)])
+@pytest.mark.parametrize("other", [1, 2, 4])
+def test_swarm_goes_on_with_the_lanes_it_was_initialised_with(m, lanes, other):
+    """The slots of a swarm's work buffer follow its lanes per particle, and a
+    device with other compute units would choose others. A swarm whose buffer is
+    laid out for `other` lanes, as such a device leaves it, goes on from there:
+    states, personal bests, history and global best of the one left alone."""
+    import torch
+    wl = W.tiny(4, K=4, T=0.02)
+    ang = np.random.default_rng(3).normal(0, 0.3, (wl.K, 2))
+    h = iod.iod_create(wl.mu, wl.chief, wl.t, ang, wl.sigma, h=wl.h)
+    p = iod.pso_params(0.7, 1.5, 1.5, 5, wl.lo, wl.hi)
+
+    def start():
+        w = iod.Swarm(m, hist_len=8)
+        iod.iod_swarm_init(h, w, p)
+        iod.iod_step(h, w, p, 3)
+        return w
+
+    ref = start()
+    assert ref.s.reserved == lanes and ref.s.block == 256
+    moved = start()
+    # the records and the stop flag, and the slots of iteration 3, for other lanes
+    per = 256 // other
+    n0, n = -(-m // (256 // lanes)), -(-m // per)
+    old, new = moved.work.clone(), torch.full_like(moved.work, float("nan"))
+    new[2 * n * 8:2 * n * 8 + 17] = old[2 * n0 * 8:2 * n0 * 8 + 17]
+    key = torch.nan_to_num(moved.jp[:m], nan=float("inf"))
+    for s in range(n):
+        i = s * per + int(torch.argmin(key[s * per:(s + 1) * per]))
+        row = torch.cat([key[i:i + 1], torch.tensor([float(i)], dtype=torch.float64, device="cuda"), moved.p[:, i]])
+        new[(n + s) * 8:(n + s + 1) * 8] = row
+    moved.work.copy_(new)
+    moved.s.reserved = other
+    for w in (ref, moved):
+        iod.iod_step(h, w, p, 4)
+    a, b = (iod.iod_swarm_best(h, w) for w in (ref, moved))
+    assert np.array_equal(a[0], b[0]) and a[1:] == b[1:]
+    for f in ("x", "v", "p", "jp", "cost", "hist"):
+        assert torch.equal(getattr(ref, f), getattr(moved, f)), f
