@@ -501,12 +501,12 @@ struct iod_handle {
         return kargs_of(P, d_tab, d_ns, T);
     }
 
-    // lanes per particle of a launch over m particles
+    // lanes per particle of a launch over m particles (allocates nothing: the
+    // calls that ask are C entries without any other allocation)
     int lanes(int64_t m) const
     {
-        SplitLoad L;
-        L.add(m, P.steps);
-        return L.lanes(simds);
+        const Load one = load_of(m, P.steps);
+        return split_lanes(&one, 1, simds);
     }
 };
 

@@ -28,24 +28,45 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // SIMDs: 316 us with two lanes each, 252 us with one).
 constexpr double SPLIT_COST[3] = {1.0, 0.76, 0.68};
 
+using Load = std::pair<int64_t, int64_t>;   // (steps, particles) of a problem
+
+inline Load load_of(int64_t m, int64_t steps) { return {std::max<int64_t>(steps, 1), m}; }
+
+// work[0 .. n): the problems, longest first.
+inline double split_estimate(const Load *work, size_t n, int l, int simds)
+{
+    double total = 0.0, t = 0.0;
+    int64_t waves = 0;
+    for (size_t p = 0; p < n; ++p) {
+        const int64_t nw = ceil_div(work[p].second, 64 >> l);
+        // waves waves + 1 .. waves + nw are of this length
+        t = std::max(t, (double)((waves + nw - 1) / simds + 1) * (double)work[p].first);
+        waves += nw;
+        total += (double)nw * (double)work[p].first;
+    }
+    return SPLIT_COST[l] * std::max(t, total / simds);
+}
+
+// two: whether two lanes per particle are to be had
+inline int split_lanes(const Load *work, size_t n, int simds, bool two = true)
+{
+    int best = 1;
+    double t0 = 0.95 * split_estimate(work, n, 0, simds);
+    for (int l = two ? 1 : 2; l < 3; ++l) {
+        const double t = split_estimate(work, n, l, simds);
+        if (t < t0) {
+            best = 1 << l;
+            t0 = t;
+        }
+    }
+    return best;
+}
+
 struct SplitLoad {
-    std::vector<std::pair<int64_t, int64_t>> work;   // (steps, particles) of each problem
+    std::vector<Load> work;   // each problem
     void add(int64_t m, int64_t steps)
     {
-        if (m > 0) work.emplace_back(std::max<int64_t>(steps, 1), m);
-    }
-    double estimate(int l, int simds) const
-    {
-        double total = 0.0, t = 0.0;
-        int64_t waves = 0;
-        for (const auto &w : work) {   // longest first
-            const int64_t n = ceil_div(w.second, 64 >> l);
-            // waves waves + 1 .. waves + n are of this length
-            t = std::max(t, (double)((waves + n - 1) / simds + 1) * (double)w.first);
-            waves += n;
-            total += (double)n * (double)w.first;
-        }
-        return SPLIT_COST[l] * std::max(t, total / simds);
+        if (m > 0) work.push_back(load_of(m, steps));
     }
     // Estimates for at most two workgroups of bs threads to their SIMDs, longest
     // first (work in that order; INFINITY if there are more). alone: one after
@@ -75,7 +96,7 @@ struct SplitLoad {
     {
         int best = lanes(simds);
         const double side = paired(best >> 1, best > 1 ? SPLIT_BS : bs, simds, false);
-        double t0 = side < INFINITY ? side : estimate(best >> 1, simds);
+        double t0 = side < INFINITY ? side : split_estimate(work.data(), work.size(), best >> 1, simds);
         solo = false;
         for (int l = 0; l < 3; ++l) {
             const double t = paired(l, l ? SPLIT_BS : bs, simds, true);
@@ -87,20 +108,10 @@ struct SplitLoad {
         }
         return best;
     }
-    // two: whether two lanes per particle are to be had
     int lanes(int simds, bool two = true)
     {
-        std::sort(work.begin(), work.end(), std::greater<std::pair<int64_t, int64_t>>());
-        int best = 1;
-        double t0 = 0.95 * estimate(0, simds);
-        for (int l = two ? 1 : 2; l < 3; ++l) {
-            const double t = estimate(l, simds);
-            if (t < t0) {
-                best = 1 << l;
-                t0 = t;
-            }
-        }
-        return best;
+        std::sort(work.begin(), work.end(), std::greater<Load>());
+        return split_lanes(work.data(), work.size(), simds, two);
     }
 };
 

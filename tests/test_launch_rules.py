@@ -1,6 +1,6 @@
 """The host's launch rules (iod_plan.h), compiled into a small program: the
 scratch and the checkpoints of the refinement under any mix of evaluation
-lengths and any amount of memory."""
+lengths and any amount of memory, and the lanes per particle of one problem."""
 import os
 import shutil
 import subprocess
@@ -14,8 +14,33 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 using namespace iodk;
+static int64_t allocations = 0;
+void *operator new(size_t n)
+{
+    ++allocations;
+    return malloc(n);
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 int main(int argc, char **argv)
 {
+    if (argc == 2) {
+        // lanes SIMDS: those of one problem by itself, as a batch of it has them,
+        // and the allocations of the first
+        const int simds = atoi(argv[1]);
+        for (int64_t m = 1; m < 40 * 64 * simds; m += 1 + m / 7) {
+            const Load one = load_of(m, 500);
+            allocations = 0;
+            const int lanes = split_lanes(&one, 1, simds);
+            const int64_t n = allocations;
+            SplitLoad L;
+            L.add(m, 500);
+            if (L.lanes(simds) != lanes || n) return 1;
+            printf("%d ", lanes);
+        }
+        printf("\n");
+        return 0;
+    }
     // scratch ROWS ROW_BYTES FREE_BYTES STEPS...: what the refinement takes when
     // FREE_BYTES are to be had, and every size it asked for
     const int64_t rows = atoll(argv[1]), bytes = atoll(argv[2]), have = atoll(argv[3]);
@@ -43,8 +68,11 @@ def scratch(tmp_path_factory):
                     "-isystem", os.path.join(rocm, "include"), "-o", str(d / "main"), str(d / "main.cpp")],
                    check=True)
 
-    def run(steps, problems, have):
+    def run(steps, problems=0, have=0):
         """(rows asked for, fitted, checkpoints, segment, rows of the adjoint, bytes of a row)"""
+        if not problems:   # lanes, steps SIMDs
+            return subprocess.run([str(d / "main"), str(steps)], check=True, capture_output=True,
+                                  text=True).stdout.split()
         row = 6 * 8 * 64 * problems
         adj = max((s + 63) // 64 + 64 for s in steps)
         out = subprocess.run([str(d / "main"), str(adj), str(row), str(have), *map(str, steps)],
@@ -74,3 +102,12 @@ def test_refinement_takes_whatever_memory_there_is(scratch, steps, problems):
     assert ok and tried[-1] == adj and seg in (8, 16, 32)
     tried, ok, ckpt, seg, _, _ = scratch(steps, problems, adj * row - 1)
     assert not ok and not ckpt and tried[-1] == adj
+
+
+@pytest.mark.parametrize("simds", [4, 128, 1024])
+def test_lanes_of_one_problem_need_no_memory(scratch, simds):
+    """Fitness, propagation, prediction and swarm steps of a handle ask for their
+    lanes inside C entries that allocate nothing else, where an exception could
+    not be caught: the same answer as a batch's, without an allocation."""
+    lanes = scratch(simds)
+    assert lanes[0] == "4" and lanes[-1] == "1" and set(lanes) == {"1", "2", "4"}
