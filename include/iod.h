@@ -463,7 +463,9 @@ int iod_batch_solve_mixed(iod_batch *b, const iod_pso_params *params, const int6
  * given it receives the mean time per iteration of each candidate, in the
  * order waves-major, then block, then order, then graph (24 values for the
  * FP64 solve, 12 for the mixed one: ms_per_iter must hold 24);
- * *n_candidates receives the count. Synchronous.
+ * *n_candidates receives the count. FP64 swarms small enough to take several
+ * lanes per particle run alike for every block and waves: such candidates
+ * share one measurement, and of them block 256, waves 0 is chosen. Synchronous.
  * Errors: as iod_batch_solve. */
 int iod_batch_autotune(iod_batch *b, const iod_pso_params *params, const int64_t *m,
                        int64_t trial_iters, int32_t top_k, iod_launch_config *chosen,

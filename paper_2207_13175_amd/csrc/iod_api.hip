@@ -1168,9 +1168,18 @@ struct BatchLayout {
     int64_t ld = 0, total_slots = 0, grid = 0;
 };
 
+// Lanes per particle of a batch's FP64 launches (the same number for all
+// problems); swarm: those of a swarm, which may also run one wave to a SIMD (solo).
+int batch_lanes(const iod_batch *b, const int64_t *m, int bs, int order, bool swarm, bool &solo)
+{
+    SplitLoad S;
+    for (int32_t p = 0; p < b->P; ++p) S.add(m[p], b->probs[p].steps);
+    return swarm && order == IOD_ORDER_LONGEST_FIRST ? S.swarm_lanes(bs, b->simds, solo)
+                                                     : S.lanes(b->simds);
+}
+
 // split: the launches are FP64 evaluations or swarms, which may give each
-// particle several lanes (the same number for all problems).
-// swarm: the launches are swarm launches, which may also run one wave to a SIMD.
+// particle several lanes. swarm: the launches are swarm launches.
 int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t *m, int bs,
                  int order, BatchLayout &L, bool split = false, bool swarm = false)
 {
@@ -1182,10 +1191,7 @@ int batch_layout(const iod_batch *b, const iod_pso_params *params, const int64_t
     int lanes = 1;
     bool solo = false;
     if (split) {
-        SplitLoad S;
-        for (int32_t p = 0; p < b->P; ++p) S.add(m[p], b->probs[p].steps);
-        lanes = swarm && order == IOD_ORDER_LONGEST_FIRST ? S.swarm_lanes(bs, b->simds, solo)
-                                                          : S.lanes(b->simds);
+        lanes = batch_lanes(b, m, bs, order, swarm, solo);
         if (lanes > 1) bs = SPLIT_BS / lanes;
     }
     int64_t slots = 0;
@@ -1522,18 +1528,37 @@ int iod_batch_autotune(iod_batch *b, const iod_pso_params *params, const int64_t
     iod_launch_config best{256, IOD_ORDER_LONGEST_FIRST, 1, 0};
     double best_ms = INFINITY;
     int32_t c = 0;
+    // With several lanes per particle, neither the workgroup size nor the
+    // occupancy has an effect: such candidates that agree otherwise are one
+    // launch, timed once, and of them the default size and occupancy is kept,
+    // since later calls of other sizes may use both.
+    struct Timed {
+        int lanes, solo, order, graph;
+        double ms;
+    };
+    std::vector<Timed> timed;
     for (int wi = 0; wi < n_waves; ++wi)
         for (int bi = 0; bi < 3; ++bi)
             for (int order = 0; order < 2; ++order)
                 for (int graph = 0; graph < 2; ++graph) {
                     iod_launch_config cfg{blocks[bi], order, graph, waves_of[wi]};
-                    double ms = 0;
-                    rc = batch_run(b, params, m, trial_iters, cfg, nullptr, nullptr, nullptr, &ms,
-                                   top_k);
-                    if (rc != IOD_OK) return rc;
+                    bool solo = false;
+                    const int lanes = top_k == 0 ? batch_lanes(b, m, cfg.block, order, true, solo) : 1;
+                    const Timed *same = nullptr;
+                    for (const Timed &t : timed)
+                        if (t.lanes == lanes && t.solo == solo && t.order == order && t.graph == graph)
+                            same = &t;
+                    double ms = same ? same->ms : 0.0;
+                    if (!same) {
+                        rc = batch_run(b, params, m, trial_iters, cfg, nullptr, nullptr, nullptr, &ms,
+                                       top_k);
+                        if (rc != IOD_OK) return rc;
+                        if (lanes > 1) timed.push_back({lanes, solo, order, graph, ms});
+                    }
                     if (ms_per_iter) ms_per_iter[c] = ms;
                     ++c;
-                    if (ms < best_ms) {
+                    const bool standard = cfg.block == DEFAULT_BLOCK && cfg.waves == 0;
+                    if (ms < best_ms || (same && standard && ms == best_ms)) {
                         best_ms = ms;
                         best = cfg;
                     }

@@ -131,6 +131,22 @@ def test_batch_autotune_picks_a_config(torch_dev):
     assert len(ms32) == 12 and cfg32.waves == 0
 
 
+def test_batch_autotune_times_each_launch_once(torch_dev):
+    """A small batch takes several lanes per particle, whose launches are the same
+    for every block and waves: such candidates have one time, and the default
+    block and waves stand for them. At a size of one lane per particle each
+    candidate has its own."""
+    wl = small_batch(3, P=6)
+    _, obs = observe(wl)
+    b = make_batch(wl, obs)
+    cfg, ms = iod.iod_batch_autotune(b, params_of(wl), wl.m, trial_iters=3)
+    ms = ms.reshape(2, 3, 2, 2)   # waves, block, order, graph
+    assert np.all(ms == ms[:1, :1]) and len(np.unique(ms)) > 1
+    assert cfg.block == 256 and cfg.waves == 0
+    _, ms = iod.iod_batch_autotune(b, params_of(wl), np.full(wl.P, 30000), trial_iters=2)
+    assert len(np.unique(ms)) > 12
+
+
 @pytest.mark.parametrize("block", [64, 128, 256])
 def test_single_solve_graph_and_block_sizes_bitwise(torch_dev, block):
     """Graph replay and every workgroup size give the eager result, solve
