@@ -1640,8 +1640,8 @@ int polish_run(const ProbDesc &d0, SwarmArrays B, int bs, int64_t grid, int32_t 
 
 // The batched refinement loop: each iteration forms the normal equations and
 // the adjoint gradient of every live candidate, tries T dampings per candidate
-// side by side (one wave per problem, in the lanes that the candidates leave
-// free) with the geodesic correction, keeps the best trial, and retires
+// side by side with the geodesic correction (a wave per problem while many
+// are active, two or four while few are), keeps the best trial, and retires
 // problems whose candidates have all stopped moving. PB holds the candidate
 // columns (p * 64 + j, j < n[p]); jrows the candidates' rows of J; order [P][2]
 // and stored [columns] are scratch. The adjoint rows of work hold the

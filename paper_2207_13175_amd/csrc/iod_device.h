@@ -71,7 +71,7 @@ __device__ __forceinline__ double rcp_from_roots(double D, double h1, double h2,
 // two values, 4 issue slots per RK4 step, where two comparisons per value took
 // 8, and one comparison per certified interval. With the reciprocal above a
 // step takes 262 slots instead of 274: an iteration of the single large swarm
-// went from 2.01 to 1.90 ms, and the uneven batch (two waves to a SIMD) gained 1%.
+// went from 2.01 to 1.90 ms, and the uneven batch (two waves to a SIMD) gained 1-2%.
 struct Mark {
     double D, e;
 };

@@ -708,7 +708,7 @@ __global__ __launch_bounds__(64) void k_normal_grad(ProbDesc d0, SwarmArrays NB,
 //     it, in reverse order.
 // Each operation on a particle is the one of the sweeps above, on the same
 // operands, so the bits are the same. 96 particles over 2,520 steps: normal
-// equations 5.02 -> 1.01 ms (1.13 with the Jacobian data from the producer and
+// equations 5.02 -> 1.02 ms (1.13 with the Jacobian data from the producer and
 // the blocks formed by every column); 1,000 over 2,000: cost gradient 5.03 ->
 // 1.58 ms. Wave 0 bounds both, with its hand-over (a barrier every 8 steps and
 // the wait for LDS); longer chunks, packed writes and reading a step ahead
@@ -866,7 +866,7 @@ __device__ __forceinline__ void pipe_produce(const KArgs &A, int32_t n, double X
         Cert ieee;
         stages_jac<false, true>(A.mu, A.mu1, A.h, A.h2, A.h6, X, J, Y, ieee);
         if (vel) pipe_put_velocity(slot, pp, X);
-        // the position of stage i from its y, z and the factors' own x
+        // the stages' positions, stepped to once more
         double k[6], s[6];
 #pragma unroll
         for (int d = 0; d < 6; ++d) s[d] = X[d];

@@ -3,8 +3,8 @@
 Few particles take the pipelined form, many the other; a particle's result
 does not depend on how many others it is launched with, so each size is
 compared, bit for bit, with the same particles inside a launch too large to be
-pipelined. Step counts sit at the edges of the hand-over chunks (8 steps), the
-reverse blocks (4), the checkpoints and the largest evaluation that is
+pipelined. Step counts sit at the edges of the hand-over chunks and the reverse
+blocks (8 steps each), the checkpoints' segments and the largest evaluation that is
 pipelined (4,096 steps), with off-grid times, two observations in one step, an
 epoch observation, ranges, and particles whose waves leave the certified
 range."""
@@ -72,6 +72,14 @@ def test_pipelined_sweeps_give_the_same_bits(torch_dev, steps, kind, mode):
     for m in (1, 15, 16, 17, 300):
         for got, want in zip(sweeps(torch, h, x, m), full):
             assert np.array_equal(got, want[..., :m], equal_nan=True), m
+
+
+@pytest.mark.parametrize("kind", ["grid", "offgrid"])
+@pytest.mark.parametrize("steps", [7, 15, 16, 17, 23, 24, 25, 592, 593, 1376, 1377, 2472, 2473])
+def test_pipelined_sweeps_at_the_edges_of_blocks_and_segments(torch_dev, steps, kind):
+    """Blocks of 8 steps; checkpoints every 8, 16, 24 and 32 steps (up to 592,
+    1,376, 2,472 and 4,096 steps)."""
+    test_pipelined_sweeps_give_the_same_bits(torch_dev, steps, kind, 1)
 
 
 def test_refinement_of_few_and_many_problems_agrees(torch_dev):
