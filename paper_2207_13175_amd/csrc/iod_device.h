@@ -62,8 +62,8 @@ __device__ __forceinline__ double rcp_from_roots(double D, double h1, double h2,
 // What certifies in-range results, from every D = D1 D2 and the residual e of
 // its reciprocal: D < 2^1000 and e < 2^-53, on the high words as integers
 // (which order as the values do for numbers and infinities; a NaN's sign bit,
-// set in those that this device makes, puts it below all of them, so NaNs need
-// a test of their own). A D too small for the reciprocal, whose seed overflows,
+// set in those that this device makes, puts it below every positive number, so
+// NaNs need a test of their own). A D too small for the reciprocal, whose seed overflows,
 // and a zero D leave a NaN reciprocal where IEEE division gives an infinity. It
 // makes every component of the acceleration NaN, and with it whatever the
 // caller hands to ok(): a value that the accelerations of all certified stages
