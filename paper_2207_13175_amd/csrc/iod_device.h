@@ -169,7 +169,10 @@ __device__ __forceinline__ void rk4_sum(double mu, double mu1, double h, double 
 // recomputes it from X on the IEEE path. Both give the same bits wherever the
 // first is certified, so the result is always that of correctly rounded
 // sqrt and division. X is updated only once the sum is final, so nothing
-// needs a second copy of the state.
+// needs a second copy of the state. VEL: the velocity is wanted too; otherwise
+// only the position is certified, which the accelerations of stages 1 to 3
+// reach, and the last stage's acceleration is not formed at all (11 instructions).
+template <bool VEL>
 __device__ __forceinline__ void rk4(double mu, double mu1, bool fast, double h, double h2,
                                     double h6, double X[6])
 {
@@ -178,7 +181,7 @@ __device__ __forceinline__ void rk4(double mu, double mu1, bool fast, double h, 
     if (fast) {
         Cert cert;
         rk4_sum<true>(mu, mu1, h, h2, X, a, cert);
-        ok = cert.ok(a[5]);
+        ok = cert.ok(a[VEL ? 5 : 2]);
     }
     if (!__all(ok)) {
         Cert ieee;
@@ -449,7 +452,8 @@ struct WaveScope {
 
 // Walk the observation schedule: advance X on the grid, and at each
 // observation hand the state there (a side copy advanced by the partial step
-// when the time is off the grid) to `obs(row, S)`. Every thread of the scope
+// when the time is off the grid) to `obs(row, S)`, which reads S's velocity
+// only if Obs::VEL. Every thread of the scope
 // (the workgroup, or the wave) must call this: it stages the table through
 // LDS in chunks. LPP adjacent lanes hold the same particle (1, 2 or 4).
 template <class Scope = BlockScope, int U = 2, int LPP = 1, class Obs>
@@ -478,7 +482,7 @@ __device__ __forceinline__ void walk(const KArgs &A, double X[6], double *lds, i
             double S[6];
 #pragma unroll
             for (int d = 0; d < 6; ++d) S[d] = X[d];
-            if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
+            if (tau != 0.0) rk4<Obs::VEL>(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
             obs(row, S);
         }
     }
@@ -498,6 +502,7 @@ __device__ __forceinline__ void walk(const KArgs &A, double X[6], double *lds, i
 // azimuth is atan2(0, 0) = 0; rho = 0 has no line of sight and e = +inf.
 // e_k = w (da^2 + db^2); J = sum e_k^2 (mode 0) or sum e_k (mode 1).
 struct CostAcc {
+    static constexpr bool VEL = false;
     double J, w;
     int32_t mode;
     double wr;   // range weight, 0 = angles only
@@ -767,6 +772,7 @@ __device__ __forceinline__ void write_record(double *rec, const double g[6], dou
 // ---------------------------------------------------------------------------
 
 struct StoreStates {
+    static constexpr bool VEL = true;
     double *out;
     int64_t ld, i;
     int32_t k;
@@ -782,6 +788,7 @@ struct StoreStates {
 };
 
 struct StoreAngles {
+    static constexpr bool VEL = false;
     double *out;
     int64_t ld, i;
     int32_t k;
@@ -808,6 +815,7 @@ struct StoreAngles {
 
 // Chief positions written into the observation table of each problem.
 struct StoreChief {
+    static constexpr bool VEL = false;
     double *tab;
     int32_t k;
     __device__ __forceinline__ void operator()(const double *, const double S[6])

@@ -72,6 +72,7 @@ __global__ __launch_bounds__(256) void k_predict(KArgs A, const double *__restri
 // Predicted angles of one state per problem (one workgroup per problem),
 // written at the problem's observation rows of out [rows][2].
 struct StoreAnglesRow {
+    static constexpr bool VEL = false;
     double *out;
     int32_t k;
     __device__ __forceinline__ void operator()(const double *row, const double S[6])
@@ -127,6 +128,7 @@ __device__ __forceinline__ double range_literal(const double *row, const double 
 }
 
 struct StoreRanges {
+    static constexpr bool VEL = false;
     double *out;
     int64_t ld, i;
     int32_t k;
@@ -140,6 +142,7 @@ struct StoreRanges {
 };
 
 struct StoreRangesRow {
+    static constexpr bool VEL = false;
     double *out;
     int32_t k;
     __device__ __forceinline__ void operator()(const double *row, const double S[6])

@@ -298,7 +298,7 @@ __device__ __forceinline__ void obs_cotangent(const KArgs &A, const double *row,
     double S[6];
 #pragma unroll
     for (int d = 0; d < 6; ++d) S[d] = X[d];
-    if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
+    if (tau != 0.0) rk4<false>(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
     double da = 0, db = 0, ga[3], gb[3], dr = 0, gr[3] = {0, 0, 0};
     double sbar[6] = {0, 0, 0, 0, 0, 0};
     const bool ranged = A.wr != 0.0;
@@ -363,12 +363,12 @@ __device__ __forceinline__ void grad_body(int64_t blk, const ProbDesc &d0, const
 #pragma unroll
             for (int d = 0; d < 6; ++d) Sx[d] = X[d];
             const double tau = row[TAB_TAU];
-            if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, Sx);
+            if (tau != 0.0) rk4<false>(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, Sx);
             acc(row, Sx);
             ++k;
             nk = k < A.K ? A.ns[k] : -1;
         }
-        if (n < S) rk4(A.mu, A.mu1, A.fast, A.h, A.h2, A.h6, X);
+        if (n < S) rk4<true>(A.mu, A.mu1, A.fast, A.h, A.h2, A.h6, X);
     }
     J = acc.J;
     // reverse sweep
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(64) void k_normal_grad(ProbDesc d0, SwarmArrays NB,
 //     it, in reverse order.
 // Each operation on a particle is the one of the sweeps above, on the same
 // operands, so the bits are the same. 96 particles over 2,520 steps: normal
-// equations 5.02 -> 1.02 ms (1.13 with the Jacobian data from the producer and
+// equations 5.02 -> 1.01 ms (1.13 with the Jacobian data from the producer and
 // the blocks formed by every column); 1,000 over 2,000: cost gradient 5.03 ->
 // 1.58 ms. Wave 0 bounds both, with its hand-over (a barrier every 8 steps and
 // the wait for LDS); longer chunks, packed writes and reading a step ahead
@@ -1161,7 +1161,7 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
             pipe_get_state(xend, k & 1, pp, X);
             const double *row = A.tab + (int64_t)k * TAB_W;
             const double tau = row[TAB_TAU];
-            if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, X);
+            if (tau != 0.0) rk4<false>(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, X);
             acc(row, X);
         }
         if (wanted(i) && lane < PIPE_P) B.cost[D.off + i] = acc.J;
@@ -1279,9 +1279,13 @@ __device__ __forceinline__ void pipe_body(int64_t block, const ProbDesc &d0, con
     }
 }
 
+// (The padding: the single problem's tangent takes 1.012 ms instead of 1.033 for
+// 96 particles over 2,520 steps with an odd number of s_nop at its entry, which
+// moves the starts of its waves' step loops by 4 bytes modulo 8.)
 template <bool SINGLE, bool TAN, bool ADJ>
 __global__ __launch_bounds__(TAN ? 256 : 128) void k_sens_pipe(ProbDesc d0, SwarmArrays B, PipeArgs Q)
 {
+    if constexpr (SINGLE && TAN) entry_pad<1>();
     pipe_body<SINGLE, TAN, ADJ>(blockIdx.x, d0, B, Q);
 }
 
@@ -1457,7 +1461,7 @@ __device__ __forceinline__ void trial_walk(const KArgs &A, double X[6], double *
 #pragma unroll
             for (int d = 0; d < 6; ++d) S[d] = X[d];
             const double tau = row[TAB_TAU];
-            if (tau != 0.0) rk4(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
+            if (tau != 0.0) rk4<false>(A.mu, A.mu1, A.fast, tau, 0.5 * tau, tau / 6.0, S);
             obs(k0 + kk, row, S);
         }
     }

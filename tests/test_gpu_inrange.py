@@ -83,21 +83,24 @@ def test_mantissa_of_all_ones():
     assert np.array_equal(first_step(0.5, xs), reference(0.5, xs))
 
 
+@pytest.mark.parametrize("partial", [False, True])
 @pytest.mark.parametrize("m", [1, 20000, 40000])
-def test_last_stage_next_to_a_primary(m):
+def test_last_stage_next_to_a_primary(m, partial):
     """A step whose fourth stage alone comes within 2^-345 to 2^-350 of the second
     primary (a tiny mass: x and y are chosen such that the stage lands on its x
     and y exactly), where 1 / (D1 D2) is infinite. The position after the step is
     a number and the velocity along z an infinity, not NaN, with one, two or
-    four lanes per particle."""
+    four lanes per particle; also where it is the partial step to an off-grid
+    observation, of a grid step twice as long."""
     import torch
-    h, mu = 2.0 ** -10, 1e-300
+    t, mu = 2.0 ** -10, 1e-300
+    h = 2 * t if partial else t
     xs = np.array([[1.000739122972962, 0.0009516530515198243, 2.0 ** e, -0.7559108123501284,
                     -0.9752318481629676, 0.0] for e in (-350, -345, -341, -330)])
-    want = np.stack([oracle.propagate(mu, h, x, [h])[0] for x in xs])
+    want = np.stack([oracle.propagate(mu, h, x, [t])[0] for x in xs])
     assert np.array_equal(want[:, 5] == -np.inf, [True, True, False, False])
     assert np.all(np.isfinite(want[:, :3]))
-    hd = iod.iod_create(mu, [0.9, 0.1, 0, 0, 0.2, 0], [h], np.zeros((1, 2)), 1e-5, h=h)
+    hd = iod.iod_create(mu, [0.9, 0.1, 0, 0, 0.2, 0], [t], np.zeros((1, 2)), 1e-5, h=h)
     for x, w in zip(xs, want):
         d = torch.from_numpy(np.tile(x[:, None], (1, m))).cuda()
         out = torch.zeros((1, 6, m), dtype=torch.float64, device="cuda")
